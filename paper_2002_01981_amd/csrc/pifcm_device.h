@@ -11,7 +11,7 @@ constexpr int kMaxBatchVols = 32; // volumes in one batched launch
 constexpr int kWaveTileX = 16;    // columns of a fused-step tile along x
 constexpr int kWaveTileY = 4;     // and along y (16 x 4 = one wavefront)
 constexpr float kDFloor = 1e-12f; // floor of the squared distance of eq (4)
-constexpr int kFcmVoxPerThread = 8;
+constexpr int kFcmTiles = 1024;   // work groups a volume's pointwise FCM pass is cut into, at most
 
 // Device-side state of one IFCM run (one volume x one particle).
 struct alignas(64) SolveState {
@@ -42,16 +42,16 @@ struct VolDev {
   int32_t zc;          // planes per tile
   int32_t ntx, nty, ntz;
   int32_t tiles;       // ntx * nty * ntz (gather kernels)
-  int32_t tiles1d;     // ceil(active voxels / voxels per block) (pointwise kernels)
+  int32_t tiles1d;     // ceil(active voxels / (256 vpt)) (pointwise kernels)
   int32_t zbeg, zend;  // planes iterated; the others are fixed context
-  int32_t pad;
+  int32_t vpt;         // voxels per thread of the pointwise kernels
   const float* rinv;   // [nz][ny][nx][4] per-ring g_inv and q_inv (two-ring kernel only)
 };
 
 // One (volume, particle) run of a launch.
 struct PairDev {
-  const float* U0;     // U^(0)
-  float* Ua;           // U^(t) for odd t
+  const float* U0;     // U^(0) (plain FCM: NULL = eq (2) from c^(0))
+  float* Ua;           // U^(t) for odd t (plain FCM: U^(T), or NULL)
   float* Ub;           // U^(t) for even t >= 2
   SolveState* st;
   float* partials;     // [tiles][2C + 1] per-tile sums of one launch
@@ -88,13 +88,14 @@ struct LaunchArgs {
                          // [8, 16) its waves that have run out of items;
                          // zero between launches (the last wave resets them)
   int32_t handout;       // 1: the fused step may hand out items by counter
-  int32_t pad3;
+  int32_t fcm_sorted;    // 1: plain FCM stores its final columns by ascending centre
   const RingOff* ring; // general-neighbourhood offsets (ring kernel only)
   int32_t nring;       // number of offsets
   int32_t pad1;
   int32_t pt;          // particles per work item of the fused step (1 or 2):
                        // its items are (volume, group of pt particles, tile)
-  int32_t pad2;
+  int32_t want_j;      // 1: J of an iteration's input state is needed (a stop
+                       // rule or a history)
   float W[kMaxRings + 1];  // eq (10) weight of ring r at W[r]
 };
 

@@ -286,8 +286,11 @@ VolDev make_vol(const pifcm_volume& v, const float* invg, TileShape ts, int zbeg
   d.nty = (v.ny + kWaveTileY - 1) / kWaveTileY;
   d.ntz = (nact + d.zc - 1) / d.zc;
   d.tiles = d.ntx * d.nty * d.ntz;
-  const size_t per = (size_t)256 * kFcmVoxPerThread;
-  d.tiles1d = (int)(((size_t)v.nx * v.ny * nact + per - 1) / per);
+  // Pointwise passes: at most kFcmTiles work groups of 256 threads (four waves
+  // per SIMD of the card, and as few sums to add per iteration).
+  const size_t n1 = (size_t)v.nx * v.ny * nact, most = (size_t)256 * kFcmTiles;
+  d.vpt = (int)std::max<size_t>(1, (n1 + most - 1) / most);
+  d.tiles1d = (int)((n1 + (size_t)256 * d.vpt - 1) / ((size_t)256 * d.vpt));
   return d;
 }
 
@@ -304,16 +307,23 @@ int grid_for(pifcm_ctx* ctx, int nitems, int occupancy, int per_group = 1) {
   return (int)std::max<long>(8, g);
 }
 
-// g_inv of `nv` volumes into invg (volume b at invg + invg_off[b]), the
-// intensity check, and the row check of caller U0 pointers (optional), with
-// flags (device, 2 ints) and stage (host, 2 ints) as workspace.
+// Which step kernel a launch uses.
+// kFcm: plain FCM without states in memory; kFcmStore: with them (adjoint).
+enum Kind { kGather = 0, kFcm = 1, kRing = 2, kRing2 = 3, kFcmStore = 4 };
+
+// g_inv of `nv` volumes into invg (volume b at invg + invg_off[b]; invg NULL:
+// not needed), the intensity check, and the row check of caller U0 pointers
+// (optional), with flags (device, 2 ints) and stage (host, 2 ints) as
+// workspace.
 pifcm_status run_invariants(pifcm_ctx* ctx, const pifcm_volume* vols, int nv, int C,
                             const float* const* U0s, float* invg, const size_t* invg_off, int* flags,
                             int* stage) {
   HIPCHK(hipMemsetAsync(flags, 0, 2 * sizeof(int), ctx->s));
   for (int b = 0; b < nv; ++b) {
-    HIPCHK(launch_invariants(vols[b].x, invg + invg_off[b], vols[b].nx, vols[b].ny, vols[b].nz,
-                             flags, ctx->s));
+    if (invg)
+      HIPCHK(launch_invariants(vols[b].x, invg + invg_off[b], vols[b].nx, vols[b].ny, vols[b].nz, flags,
+                               ctx->s));
+    else HIPCHK(launch_check_finite(vols[b].x, nvox(vols[b]), flags, ctx->s));
     if (U0s && U0s[b]) HIPCHK(launch_check_rows(U0s[b], nvox(vols[b]), C, flags + 1, ctx->s));
   }
   HIPCHK(hipMemcpyAsync(stage, flags, 2 * sizeof(int), hipMemcpyDeviceToHost, ctx->s));
@@ -325,31 +335,33 @@ pifcm_status run_invariants(pifcm_ctx* ctx, const pifcm_volume* vols, int nv, in
   return PIFCM_OK;
 }
 
-// Set up invariants of `nv` volumes into ctx->invg (concatenated) and check
-// intensities; optionally check rows of caller U0 pointers.
+// Set up the invariants a launch of `kind` (or the adjoint) reads, of `nv`
+// volumes concatenated in ctx->invg or ctx->rinv, and check intensities;
+// optionally check rows of caller U0 pointers.
 pifcm_status prepare_volumes(pifcm_ctx* ctx, const pifcm_volume* vols, int nv, int C,
-                             const float* const* U0s, std::vector<size_t>& invg_off,
-                             const pifcm_params* ring2 = nullptr) {
+                             const float* const* U0s, std::vector<size_t>& invg_off, int kind,
+                             const pifcm_params* p) {
   size_t total = 0;
   invg_off.resize(nv);
   for (int b = 0; b < nv; ++b) {
     invg_off[b] = total;
     total += (nvox(vols[b]) + 63) / 64 * 64;
   }
-  TRY(ensure(ctx, ctx->invg, total * sizeof(float), "iteration invariants"));
-  if (ring2) {
+  const bool need_g = kind == kGather || kind == kFcmStore;
+  if (need_g) TRY(ensure(ctx, ctx->invg, total * sizeof(float), "iteration invariants"));
+  if (kind == kRing2) {
     // Per-ring invariants of the fused two-ring kernel (4 floats per voxel,
     // at 4 x the offsets of g_inv).
     TRY(ensure(ctx, ctx->rinv, total * 4 * sizeof(float), "ring invariants"));
     for (int b = 0; b < nv; ++b)
       HIPCHK(launch_ring2_invariants(vols[b].x, (float*)ctx->rinv.p + 4 * invg_off[b], vols[b].nx,
-                                     vols[b].ny, vols[b].nz, (ring2->flags & PIFCM_Q2_SQDIST) ? 1 : 0,
+                                     vols[b].ny, vols[b].nz, (p->flags & PIFCM_Q2_SQDIST) ? 1 : 0,
                                      ctx->s));
   }
   TRY(ensure(ctx, ctx->flags, 64, "flags"));
   TRY(ensure_pinned(ctx, 4096));
-  return run_invariants(ctx, vols, nv, C, U0s, (float*)ctx->invg.p, invg_off.data(), (int*)ctx->flags.p,
-                        (int*)ctx->pinned);
+  return run_invariants(ctx, vols, nv, C, U0s, need_g ? (float*)ctx->invg.p : nullptr, invg_off.data(),
+                        (int*)ctx->flags.p, (int*)ctx->pinned);
 }
 
 SolveState init_state(const float* c0, int C, float lam, float xi, const pifcm_params* p,
@@ -368,9 +380,6 @@ SolveState init_state(const float* c0, int C, float lam, float xi, const pifcm_p
   return s;
 }
 
-// Which step kernel a launch uses.
-enum Kind { kGather = 0, kFcm = 1, kRing = 2, kRing2 = 3 };
-
 bool ring_params(const pifcm_params* p) { return p->V > 1 || (p->flags & PIFCM_SHELL_SQDIST); }
 // The two Chebyshev rings of the 5x5x5 cube with C <= 4 run the fused
 // two-ring kernel; other general neighbourhoods walk the offset table.
@@ -387,7 +396,8 @@ int kind_of(const pifcm_params* p, bool zero_weights) {
 }
 
 int occupancy_of(int kind, int C, int nw, bool m2, bool step, int pt = 1) {
-  if (kind == kFcm) return fcm_occupancy(C, m2, step);
+  if (kind == kFcm) return fcm_x_occupancy(C, m2, step);
+  if (kind == kFcmStore) return fcm_occupancy(C, m2, step);
   if (kind == kRing) return ring_occupancy(C, m2, step);
   if (kind == kRing2) return ring2_occupancy(C, m2, step);
   return gather_occupancy(C, nw, pt, m2, step);
@@ -467,10 +477,11 @@ hipError_t launch_step(int C, const LaunchArgs& a, int grid, int nw, bool m2, in
   const long per = ((long)a.nitems + 7) / 8;
   if ((long)(grid / 8) * items_per_group(kind, nw) >= per)
     for (int k = 0; k <= 8; ++k) b.xcd_begin[k] = (int32_t)std::min<long>(a.nitems, per * k);
-  hipError_t e = kind == kFcm     ? launch_fcm(C, b, grid, m2, step, s)
-                 : kind == kRing  ? launch_ring(C, b, grid, m2, step, s)
-                 : kind == kRing2 ? launch_ring2(C, b, grid, m2, step, s)
-                                  : launch_gather(C, b, grid, nw, m2, step, s);
+  hipError_t e = kind == kFcm        ? launch_fcm_x(C, b, grid, m2, step, s)
+                 : kind == kFcmStore ? launch_fcm(C, b, grid, m2, step, s)
+                 : kind == kRing     ? launch_ring(C, b, grid, m2, step, s)
+                 : kind == kRing2    ? launch_ring2(C, b, grid, m2, step, s)
+                                     : launch_gather(C, b, grid, nw, m2, step, s);
   if (e != hipSuccess) return e;
   return launch_finalize(C, b, b.nvol * b.P, step, s);
 }
@@ -541,7 +552,8 @@ LaunchArgs make_args(const pifcm_ctx* ctx, const VolDev* vols_dev, const PairDev
   a.P = P;
   a.q2_sqdist = (p->flags & PIFCM_Q2_SQDIST) ? 1 : 0;
   a.m = p->m;
-  a.use_1d = kind == kFcm ? 1 : 0;  // the pointwise kernel's 1D tiles
+  a.use_1d = kind == kFcm || kind == kFcmStore ? 1 : 0;  // the pointwise kernels' 1D tiles
+  a.want_j = p->eps > 0.f ? 1 : 0;
   a.work = (int32_t*)ctx->work.p;
   // Items are handed out by counter only when every pair runs every
   // iteration: under a stop rule the items of stopped pairs cost nothing,
@@ -866,7 +878,8 @@ int solve_slots(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_params* p, 
 pifcm_status solve_run(pifcm_ctx* ctx, const SolveWs& ws, const pifcm_volume* vol,
                        const pifcm_params* p, float lambda, float xi, const float* centres_in,
                        const float* U_in, float* U_out, float* centres_out, uint8_t* labels_out,
-                       double* J_out, int32_t* iters_out, double* J_hist_out, int zbeg, int zend) {
+                       double* J_out, int32_t* iters_out, double* J_hist_out, int zbeg, int zend,
+                       bool fcm_sorted = false) {
   const bool slab = zbeg > 0 || zend < vol->nz;
   const int C = p->C;
   const bool m2 = p->m == 2.0f;
@@ -877,18 +890,19 @@ pifcm_status solve_run(pifcm_ctx* ctx, const SolveWs& ws, const pifcm_volume* vo
                                    (p->flags & PIFCM_Q2_SQDIST) ? 1 : 0, ctx->s));
   const size_t off0 = 0;
   const float* u0s[1] = {U_in};
-  TRY(run_invariants(ctx, vol, 1, C, u0s, ws.invg, &off0, ws.flags, (int*)ws.stage));
+  TRY(run_invariants(ctx, vol, 1, C, u0s, kind == kGather ? ws.invg : nullptr, &off0, ws.flags,
+                     (int*)ws.stage));
   const TileShape ts = shape_for(ctx, C, m2, *vol);
   const VolDev vh = make_vol(*vol, ws.invg, ts, zbeg, zend, kind == kRing2 ? ws.rinv : nullptr);
   PairDev pr{};
-  pr.U0 = U_in ? U_in : ws.ubuf;
+  pr.U0 = U_in || kind == kFcm ? U_in : ws.ubuf;
   pr.Ua = U_out;
   pr.Ub = ws.ubuf;
   // Odd iterations write Ua, even ones Ub: when the run is expected to end
   // on an even iteration (no stop rule, an even count) and ws.ubuf is free
   // at the start (U_in given), the buffers swap so the last state lands in
   // U_out without a copy.
-  if (U_in && p->eps == 0.f && (p->max_iter & 1) == 0) std::swap(pr.Ua, pr.Ub);
+  if (kind != kFcm && U_in && p->eps == 0.f && (p->max_iter & 1) == 0) std::swap(pr.Ua, pr.Ub);
   pr.st = ws.st;
   pr.partials = ws.partials;
 
@@ -901,14 +915,17 @@ pifcm_status solve_run(pifcm_ctx* ctx, const SolveWs& ws, const pifcm_volume* vo
   HIPCHK(hipMemcpyAsync(ws.tpair, pin + sizeof(SolveState), sizeof pr, hipMemcpyHostToDevice, ctx->s));
   HIPCHK(hipMemcpyAsync(ws.tvol, pin + sizeof(SolveState) + sizeof(PairDev), sizeof(VolDev),
                         hipMemcpyHostToDevice, ctx->s));
-  if (!U_in) HIPCHK(launch_init_u(C, vol->x, N, ws.st, p->m, m2, ws.ubuf, ctx->s));
+  if (!U_in && kind != kFcm) HIPCHK(launch_init_u(C, vol->x, N, ws.st, p->m, m2, ws.ubuf, ctx->s));
   if (slab) {
     // Planes outside the slab keep U_in in both iteration buffers.
     HIPCHK(hipMemcpyAsync(U_out, U_in, N * C * sizeof(float), hipMemcpyDeviceToDevice, ctx->s));
-    HIPCHK(hipMemcpyAsync(ws.ubuf, U_in, N * C * sizeof(float), hipMemcpyDeviceToDevice, ctx->s));
+    if (kind != kFcm)
+      HIPCHK(hipMemcpyAsync(ws.ubuf, U_in, N * C * sizeof(float), hipMemcpyDeviceToDevice, ctx->s));
   }
 
   LaunchArgs a = make_args(ctx, ws.tvol, ws.tpair, &vh, 1, 1, kind, p);
+  a.want_j = p->eps > 0.f || J_hist_out ? 1 : 0;
+  a.fcm_sorted = fcm_sorted ? 1 : 0;
   const int occ = occupancy_of(kind, C, ts.nw, m2, true);
   const int grid = grid_for(ctx, a.nitems, occ, items_per_group(kind, ts.nw));
   int t = 0;
@@ -934,7 +951,7 @@ pifcm_status solve_run(pifcm_ctx* ctx, const SolveWs& ws, const pifcm_volume* vo
   HIPCHK(hipStreamSynchronize(ctx->s));
   const int T = hst->iter;
   TRY(timing_collect(ctx, t));
-  const float* Ufin = u_state_of(pr, T);
+  const float* Ufin = kind == kFcm ? U_out : u_state_of(pr, T);
   if (labels_out) HIPCHK(launch_labels(Ufin, N, C, labels_out, ctx->s));
   if (Ufin != U_out) HIPCHK(hipMemcpyAsync(U_out, Ufin, N * C * sizeof(float), hipMemcpyDeviceToDevice, ctx->s));
   double* jh = ws.jh_stage ? ws.jh_stage : J_hist_out;
@@ -954,7 +971,8 @@ pifcm_status solve_run(pifcm_ctx* ctx, const SolveWs& ws, const pifcm_volume* vo
 pifcm_status solve_impl(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_params* p,
                         float lambda, float xi, const float* centres_in, const float* U_in,
                         float* U_out, float* centres_out, uint8_t* labels_out, double* J_out,
-                        int32_t* iters_out, double* J_hist_out, int zbeg = 0, int zend = -1) {
+                        int32_t* iters_out, double* J_hist_out, int zbeg = 0, int zend = -1,
+                        bool fcm_sorted = false) {
   if (zend < 0) zend = vol->nz;
   const int C = p->C;
   const int kind = kind_of(p, lambda == 0.0f && xi == 0.0f);
@@ -962,10 +980,10 @@ pifcm_status solve_impl(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_par
   const size_t Np = (N + 63) / 64 * 64;
   if (is_ring(kind)) TRY(prepare_ring(ctx, p));
   const int slots = solve_slots(ctx, vol, p, zbeg, zend);
-  TRY(ensure(ctx, ctx->invg, Np * sizeof(float), "iteration invariants"));
+  if (kind == kGather) TRY(ensure(ctx, ctx->invg, Np * sizeof(float), "iteration invariants"));
   if (kind == kRing2) TRY(ensure(ctx, ctx->rinv, Np * 4 * sizeof(float), "ring invariants"));
   TRY(ensure(ctx, ctx->flags, 64, "flags"));
-  TRY(ensure(ctx, ctx->ubuf, N * C * sizeof(float), "memberships"));
+  if (kind != kFcm) TRY(ensure(ctx, ctx->ubuf, N * C * sizeof(float), "memberships"));
   TRY(ensure(ctx, ctx->partials, (size_t)slots * (2 * C + 1) * sizeof(float), "tile sums"));
   TRY(ensure(ctx, ctx->states, sizeof(SolveState), "solve state"));
   TRY(ensure(ctx, ctx->jhist, (size_t)std::max(1, p->max_iter) * sizeof(double), "objective history"));
@@ -983,7 +1001,7 @@ pifcm_status solve_impl(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_par
   ws.stage = (char*)ctx->pinned;
   ws.jh_stage = (double*)((char*)ctx->pinned + kStageBytes);
   return solve_run(ctx, ws, vol, p, lambda, xi, centres_in, U_in, U_out, centres_out, labels_out, J_out,
-                   iters_out, J_hist_out, zbeg, zend);
+                   iters_out, J_hist_out, zbeg, zend, fcm_sorted);
 }
 
 pifcm_status check_solve_args(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_params* p,
@@ -1129,12 +1147,10 @@ pifcm_status pifcm_fcm_init(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm
   TRY(begin(ctx));
   float c1[kMaxC];
   int32_t T = 0;
-  TRY(solve_impl(ctx, vol, p, 0.f, 0.f, c0, nullptr, U0_out, c1, nullptr, nullptr, &T, nullptr));
+  TRY(solve_impl(ctx, vol, p, 0.f, 0.f, c0, nullptr, U0_out, c1, nullptr, nullptr, &T, nullptr, 0, -1, true));
   int32_t perm[kMaxC];
   for (int j = 0; j < C; ++j) perm[j] = j;
   std::stable_sort(perm, perm + C, [&](int a, int b) { return c1[a] < c1[b]; });
-  HIPCHK(launch_permute(U0_out, nvox(*vol), C, perm, U0_out, ctx->s));
-  HIPCHK(hipStreamSynchronize(ctx->s));
   TRY(finish(ctx));
   for (int j = 0; j < C; ++j) centres_out[j] = c1[perm[j]];
   if (iters_out) *iters_out = T;
@@ -1162,7 +1178,7 @@ pifcm_status swarm_core(pifcm_ctx* ctx, const pifcm_volume* vols, int32_t B, con
   for (long k = 0; k < 2L * B * P; ++k) zero = zero && particles[k] == 0.0f;
   const int kind = kind_of(p, zero);
   std::vector<size_t> off;
-  TRY(prepare_volumes(ctx, vols, B, C, U0_check, off, kind == kRing2 ? p : nullptr));
+  TRY(prepare_volumes(ctx, vols, B, C, U0_check, off, kind, p));
 
   // Tile shape: one per launch (the batched kernel has one TY).
   const TileShape ts0 = shape_for(ctx, C, m2, vols[0]);
@@ -1172,7 +1188,7 @@ pifcm_status swarm_core(pifcm_ctx* ctx, const pifcm_volume* vols, int32_t B, con
   for (int b = 0; b < B; ++b) {
     TileShape ts = shape_for(ctx, C, m2, vols[b]);
     ts.nw = ts0.nw;
-    vh[b] = make_vol(vols[b], (const float*)ctx->invg.p + off[b], ts);
+    vh[b] = make_vol(vols[b], nullptr, ts);
     uoff[b] = ubytes;
     ubytes += (size_t)P * 2 * ((nvox(vols[b]) * C + 63) / 64 * 64) * sizeof(float);
     soff[b] = slots;
@@ -1185,13 +1201,13 @@ pifcm_status swarm_core(pifcm_ctx* ctx, const pifcm_volume* vols, int32_t B, con
   // the end of a range.
   if (slots > (size_t)INT32_MAX - ((size_t)1 << 20))
     return fail(ctx, PIFCM_E_UNSUPPORTED, "%zu tiles in one launch: more than 2^31 - 2^20", slots);
-  TRY(ensure(ctx, ctx->ubuf, ubytes, "swarm memberships"));
+  if (kind != kFcm) TRY(ensure(ctx, ctx->ubuf, ubytes, "swarm memberships"));
   TRY(ensure(ctx, ctx->partials, slots * (2 * C + 1) * sizeof(float), "tile sums"));
   TRY(ensure(ctx, ctx->states, npairs * sizeof(SolveState), "solve states"));
   const size_t pin_bytes = npairs * (sizeof(SolveState) + sizeof(PairDev)) + sizeof(VolDev) * B + 4096;
   TRY(ensure_pinned(ctx, pin_bytes));
   for (int b = 0; b < B; ++b) {
-    vh[b].invg = (const float*)ctx->invg.p + off[b];
+    vh[b].invg = kind == kGather ? (const float*)ctx->invg.p + off[b] : nullptr;
     vh[b].rinv = kind == kRing2 ? (const float*)ctx->rinv.p + 4 * off[b] : nullptr;
   }
 
@@ -1210,8 +1226,13 @@ pifcm_status swarm_core(pifcm_ctx* ctx, const pifcm_volume* vols, int32_t B, con
       hs[k] = init_state(centres_pp + k * C, C, particles[2 * k], particles[2 * k + 1], p, nullptr);
       PairDev& pr = hp[k];
       pr.U0 = U0_pp[k];
-      pr.Ua = (float*)((char*)ctx->ubuf.p + uoff[b]) + (size_t)q * 2 * ustride;
-      pr.Ub = pr.Ua + ustride;
+      if (kind == kFcm) {
+        pr.Ua = state_out ? state_out[k] : nullptr;
+        pr.Ub = nullptr;
+      } else {
+        pr.Ua = (float*)((char*)ctx->ubuf.p + uoff[b]) + (size_t)q * 2 * ustride;
+        pr.Ub = pr.Ua + ustride;
+      }
       pr.st = st_dev + k;
       pr.partials = (float*)ctx->partials.p + (soff[b] + (size_t)q * tb) * (2 * C + 1);
     }
@@ -1317,7 +1338,7 @@ pifcm_status swarm_core(pifcm_ctx* ctx, const pifcm_volume* vols, int32_t B, con
   HIPCHK(hipMemcpyAsync(hs, st_dev, npairs * sizeof(SolveState), hipMemcpyDeviceToHost, ctx->s));
   HIPCHK(hipStreamSynchronize(ctx->s));
   TRY(timing_collect(ctx, launches));
-  if (state_out) {
+  if (state_out && kind != kFcm) {
     for (int b = 0; b < B; ++b)
       for (int q = 0; q < P; ++q) {
         const size_t k = (size_t)b * P + q;
@@ -1401,14 +1422,13 @@ pifcm_status ifcm_backward(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_
     return fail(ctx, PIFCM_E_INVALID, "ckpt_every = %d outside [1, K = %d]", ckpt_every, K);
   const int C = p->C, S = ckpt_every;
   const bool m2 = p->m == 2.0f;
-  const int kind = kind_of(p, lambda == 0.0f && xi == 0.0f);
+  const int kind = lambda == 0.0f && xi == 0.0f ? kFcmStore : kGather;
   const size_t N = nvox(*vol);
-  if (is_ring(kind)) TRY(prepare_ring(ctx, p));
   const size_t UB = N * C * sizeof(float);
   TRY(begin(ctx));
   std::vector<size_t> off;
   const float* u0s[1] = {U0};
-  TRY(prepare_volumes(ctx, vol, 1, C, u0s, off));
+  TRY(prepare_volumes(ctx, vol, 1, C, u0s, off, kind, p));
   const TileShape ts = shape_for(ctx, C, m2, *vol);
   std::vector<VolDev> vh{make_vol(*vol, (const float*)ctx->invg.p, ts)};
   const int slots = std::max(vh[0].tiles, vh[0].tiles1d);

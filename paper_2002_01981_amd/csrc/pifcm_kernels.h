@@ -24,7 +24,11 @@ hipError_t launch_gather(int C, const LaunchArgs& a, int grid, int ty, bool m2, 
 // Per-pair fp64 sum of the tile slots of the preceding step / objective
 // launch and the state update (one work group per pair).
 hipError_t launch_finalize(int C, const LaunchArgs& a, int npairs, bool step, hipStream_t s);
-// Pointwise FCM step / objective (lambda = xi = 0).
+// Plain FCM (lambda = xi = 0): an iteration from x and the centres alone, or
+// (step = false) the final memberships and their objective.
+hipError_t launch_fcm_x(int C, const LaunchArgs& a, int grid, bool m2, bool step, hipStream_t s);
+int fcm_x_occupancy(int C, bool m2, bool step);
+// The same iteration with its states kept in memory / the objective of one.
 hipError_t launch_fcm(int C, const LaunchArgs& a, int grid, bool m2, bool step, hipStream_t s);
 // Waves (one tile each) per work group of the general-neighbourhood kernel
 // and of the fused two-ring kernel.
@@ -43,14 +47,13 @@ hipError_t launch_init_u(int C, const float* x, size_t N, const SolveState* st, 
                          float* U, hipStream_t s);
 hipError_t launch_invariants(const float* x, float* invg, int nx, int ny, int nz, int* flag,
                              hipStream_t s);
+hipError_t launch_check_finite(const float* x, size_t n, int* flag, hipStream_t s);
 hipError_t launch_check_rows(const float* U, size_t N, int C, int* flag, hipStream_t s);
 hipError_t launch_labels(const float* U, size_t N, int C, uint8_t* out, hipStream_t s);
 // counts (device, C * K + 1 entries, zeroed by the caller) += confusion of
 // labels against truth; the last entry counts out-of-range pairs.
 hipError_t launch_confusion(const uint8_t* labels, const uint8_t* truth, size_t N, int C, int K,
                             unsigned long long* counts, hipStream_t s);
-hipError_t launch_permute(const float* U, size_t N, int C, const int32_t* perm, float* out,
-                          hipStream_t s);
 // Min-max normalisation: exact min/max keys into mm[0..1] (mm preset to
 // {0xffffffff, 0}) and a non-finite flag, then the scaling pass.
 hipError_t launch_minmax(const float* raw, size_t n, uint32_t* mm, int* flag, hipStream_t s);

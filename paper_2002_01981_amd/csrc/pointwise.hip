@@ -9,6 +9,179 @@ namespace pifcm {
 // ------------------------------------------------ pointwise FCM (lambda=xi=0)
 // With lambda = xi = 0 the attraction factor of eq (4) is exactly 1, so H and
 // F are not needed and the step is plain FCM (eqs (1)-(3)).
+//
+// Its new memberships are then a function of x and the centres alone, so a
+// run needs none of them in memory but the last: k_fcm_x forms U^(t-1) of
+// iteration t from the centres it came from (c^(t-2), still in the other half
+// of the pair's double buffer; only iteration 1 may read a caller's U^(0)),
+// and k_fcm_last forms and stores U^(T).  An iteration reads 4 B per voxel
+// where k_fcm_point moves 8 C + 4: 181x217x181 voxels, C = 4, take 14 us
+// instead of 31 us, bound by VALU issue (two memberships per voxel).
+// k_fcm_point remains for the adjoint, which keeps every state.
+template <int C, bool M2>
+__device__ __forceinline__ void fcm_memberships(float xv, const float (&c)[C], float m, float (&u)[C]) {
+  float d2[C];
+#pragma unroll
+  for (int j = 0; j < C; ++j) {
+    const float dd = xv - c[j];
+    d2[j] = fmaxf(dd * dd, kDFloor);
+  }
+  memberships<C, M2>(d2, m, u);
+}
+
+// Voxels in flight per thread (their loads are issued together).
+constexpr int kFcmAhead = 4;
+
+// One iteration; WJ: J of its input state is wanted (a stop rule or a
+// history).
+template <int C, bool M2, bool WJ>
+__global__ __launch_bounds__(256) void k_fcm_x(const LaunchArgs a) {
+  constexpr int NT = 256;
+  constexpr int NV = 2 * C + 1;
+  __shared__ float s_red[(NT / 64) * NV];
+  const int xcd = blockIdx.x & 7;
+  const int it_end = a.xcd_begin[xcd + 1];
+  for (int it = a.xcd_begin[xcd] + (blockIdx.x >> 3); it < it_end; it += gridDim.x >> 3) {
+    const int b = vol_of_item(a, it);
+    const VolDev vd = ld_const(a.vols + b);
+    const int r = it - a.item_begin[b];
+    const int pidx = r / vd.tiles1d;
+    const int tile = r - pidx * vd.tiles1d;
+    const PairDev pr = ld_const(a.pairs + b * a.P + pidx);
+    const SolveState* st = pr.st;
+    if (ld_const(&st->stop)) continue;
+    const int t = ld_const(&st->iter) + 1;
+    const gfloat* X = as_global(vd.x);
+    const gfloat* U0 = t == 1 && pr.U0 ? as_global(pr.U0) : nullptr;
+    float c[C], cp[C];  // c^(t-1), c^(t-2) (both c^(0) at t = 1)
+#pragma unroll
+    for (int j = 0; j < C; ++j) {
+      c[j] = ld_const(&st->c[(t - 1) & 1][j]);
+      cp[j] = ld_const(&st->c[t & 1][j]);
+    }
+    const size_t psz = (size_t)vd.nx * vd.ny;
+    const size_t N = (size_t)vd.zend * psz;  // end of the planes iterated
+    float acc[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) acc[k] = 0.f;
+    const size_t base = (size_t)vd.zbeg * psz + (size_t)tile * NT * vd.vpt + threadIdx.x;
+    for (int k = 0; k < vd.vpt; k += kFcmAhead) {
+      float xs[kFcmAhead];
+#pragma unroll
+      for (int q = 0; q < kFcmAhead; ++q) xs[q] = X[min(base + (size_t)(k + q) * NT, N - 1)];
+#pragma unroll
+      for (int q = 0; q < kFcmAhead; ++q) {
+        const size_t i = base + (size_t)(k + q) * NT;
+        if (k + q >= vd.vpt || i >= N) break;
+        const float xv = xs[q];
+        float d2[C];
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+          const float dd = xv - c[j];
+          d2[j] = fmaxf(dd * dd, kDFloor);
+        }
+        if constexpr (WJ) {
+          float uo[C];
+          if (U0) load_row<C>(U0 + i * C, uo);
+          else fcm_memberships<C, M2>(xv, cp, a.m, uo);
+          float Jv = 0.f;
+#pragma unroll
+          for (int j = 0; j < C; ++j) Jv = fmaf(pow_m<M2>(uo[j], a.m), d2[j], Jv);
+          acc[2 * C] += Jv;
+        }
+        float un[C];
+        memberships<C, M2>(d2, a.m, un);
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+          const float w = pow_m<M2>(un[j], a.m);
+          acc[j] = fmaf(w, xv, acc[j]);
+          acc[C + j] += w;
+        }
+      }
+    }
+    block_tile_store<NV, NT>(pr, tile, acc, s_red);
+  }
+}
+
+// The final state: U^(T) into pr.Ua (if not NULL) and its objective.  With
+// a.fcm_sorted the columns are stored in the order of their centres (ties by
+// index).
+template <int C, bool M2>
+__global__ __launch_bounds__(256) void k_fcm_last(const LaunchArgs a) {
+  constexpr int NT = 256;
+  __shared__ float s_red[NT / 64];
+  const int xcd = blockIdx.x & 7;
+  const int it_end = a.xcd_begin[xcd + 1];
+  for (int it = a.xcd_begin[xcd] + (blockIdx.x >> 3); it < it_end; it += gridDim.x >> 3) {
+    const int b = vol_of_item(a, it);
+    const VolDev vd = ld_const(a.vols + b);
+    const int r = it - a.item_begin[b];
+    const int pidx = r / vd.tiles1d;
+    const int tile = r - pidx * vd.tiles1d;
+    const PairDev pr = ld_const(a.pairs + b * a.P + pidx);
+    const SolveState* st = pr.st;
+    const int T = ld_const(&st->iter);
+    const gfloat* X = as_global(vd.x);
+    const gfloat* U0 = T == 0 && pr.U0 ? as_global(pr.U0) : nullptr;
+    gfloat* out = as_global(pr.Ua);
+    float c[C], cp[C];  // c^(T), c^(T-1)
+    int col[C];         // column of cluster j in the stored rows
+    bool moved = false;
+#pragma unroll
+    for (int j = 0; j < C; ++j) {
+      c[j] = ld_const(&st->c[T & 1][j]);
+      cp[j] = ld_const(&st->c[T == 0 ? 0 : (T - 1) & 1][j]);
+    }
+#pragma unroll
+    for (int j = 0; j < C; ++j) {
+      col[j] = 0;
+#pragma unroll
+      for (int k = 0; k < C; ++k) col[j] += c[k] < c[j] || (c[k] == c[j] && k < j) ? 1 : 0;
+      moved = moved || (a.fcm_sorted && col[j] != j);
+    }
+    const size_t psz = (size_t)vd.nx * vd.ny;
+    const size_t N = (size_t)vd.zend * psz;
+    float acc[1] = {0.f};
+    const size_t base = (size_t)vd.zbeg * psz + (size_t)tile * NT * vd.vpt + threadIdx.x;
+    for (int k = 0; k < vd.vpt; k += kFcmAhead) {
+      float xs[kFcmAhead];
+#pragma unroll
+      for (int q = 0; q < kFcmAhead; ++q) xs[q] = X[min(base + (size_t)(k + q) * NT, N - 1)];
+#pragma unroll
+      for (int q = 0; q < kFcmAhead; ++q) {
+        const size_t i = base + (size_t)(k + q) * NT;
+        if (k + q >= vd.vpt || i >= N) break;
+        const float xv = xs[q];
+        float u[C];
+        if (U0) load_row<C>(U0 + i * C, u);
+        else fcm_memberships<C, M2>(xv, cp, a.m, u);
+        float Jv = 0.f;
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+          const float dd = xv - c[j];
+          Jv = fmaf(pow_m<M2>(u[j], a.m), fmaxf(dd * dd, kDFloor), Jv);
+        }
+        acc[0] += Jv;
+        if (out) {
+          if (moved) {
+            float v[C];
+#pragma unroll
+            for (int p = 0; p < C; ++p) {
+              v[p] = 0.f;
+#pragma unroll
+              for (int j = 0; j < C; ++j) v[p] = col[j] == p ? u[j] : v[p];
+            }
+            store_row<C>(out + i * C, v);
+          } else {
+            store_row<C>(out + i * C, u);
+          }
+        }
+      }
+    }
+    block_tile_store<1, NT>(pr, tile, acc, s_red);
+  }
+}
+
 template <int C, bool M2, bool STEP>
 __global__ __launch_bounds__(256) void k_fcm_point(const LaunchArgs a) {
   constexpr int NT = 256;
@@ -37,9 +210,9 @@ __global__ __launch_bounds__(256) void k_fcm_point(const LaunchArgs a) {
     float acc[NV];
 #pragma unroll
     for (int k = 0; k < NV; ++k) acc[k] = 0.f;
-    const size_t base = (size_t)vd.zbeg * psz + (size_t)tile * NT * kFcmVoxPerThread;
+    const size_t base = (size_t)vd.zbeg * psz + (size_t)tile * NT * vd.vpt;
 #pragma unroll 2
-    for (int k = 0; k < kFcmVoxPerThread; ++k) {
+    for (int k = 0; k < vd.vpt; ++k) {
       const size_t i = base + (size_t)k * NT + threadIdx.x;
       if (i >= N) break;
       const float xv = X[i];
@@ -196,6 +369,11 @@ __global__ __launch_bounds__(256) void k_invariants(const float* __restrict__ x,
   if (bad) atomicOr(flag, 1);
 }
 
+// Elements before the first 16-byte boundary of p (at most n).
+__device__ __forceinline__ size_t head_of(const float* p, size_t n) {
+  return min(n, (size_t)((16 - (reinterpret_cast<uintptr_t>(p) & 15)) & 15) / 4);
+}
+
 // U^(0) from centres (eq (2) with the attraction factor 1).
 template <int C, bool M2>
 __global__ __launch_bounds__(256) void k_init_u(const float* __restrict__ x, size_t N,
@@ -216,6 +394,25 @@ __global__ __launch_bounds__(256) void k_init_u(const float* __restrict__ x, siz
     memberships<C, M2>(d2, m, u);
     store_row<C>(as_global(U) + i * C, u);
   }
+}
+
+// Flags a non-finite intensity (calls that do not need g_inv).  The float4s
+// of the 16-byte aligned body, and the few values around it.
+__global__ __launch_bounds__(256) void k_check_finite(const float* __restrict__ x, size_t n,
+                                                      int* __restrict__ flag) {
+  const size_t head = head_of(x, n), n4 = (n - head) / 4;
+  const float4* body = reinterpret_cast<const float4*>(x + head);
+  const size_t tid = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
+  bool bad = false;
+#pragma unroll 4
+  for (size_t i = tid; i < n4; i += stride) {
+    const float4 v = body[i];
+    bad = bad || !isfinite(v.x) || !isfinite(v.y) || !isfinite(v.z) || !isfinite(v.w);
+  }
+  if (tid < head) bad = bad || !isfinite(x[tid]);
+  const size_t i = head + 4 * n4 + tid;
+  if (i < n) bad = bad || !isfinite(x[i]);
+  if (bad) atomicOr(flag, 1);
 }
 
 // Rows of a caller's U must be memberships: finite, in [0, 1], sum 1 +- 1e-4.
@@ -287,20 +484,6 @@ __global__ __launch_bounds__(256) void k_confusion(const uint8_t* __restrict__ l
     if (h[t]) atomicAdd(&counts[t], (unsigned long long)h[t]);
 }
 
-struct Perm {
-  int32_t p[kMaxC];
-};
-// In place allowed: each row is read whole before it is written.
-__global__ __launch_bounds__(256) void k_permute(const float* U, size_t N, int C, Perm perm,
-                                                 float* out) {
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < N;
-       i += (size_t)gridDim.x * blockDim.x) {
-    float row[kMaxC];
-    for (int j = 0; j < C; ++j) row[j] = U[i * C + perm.p[j]];
-    for (int j = 0; j < C; ++j) out[i * C + j] = row[j];
-  }
-}
-
 // Min-max normalisation (Algorithm 2 step 1).  Floats are mapped to
 // order-preserving unsigned keys so min/max are exact integer atomics.
 __device__ __forceinline__ uint32_t fkey(float f) {
@@ -310,11 +493,6 @@ __device__ __forceinline__ uint32_t fkey(float f) {
 __device__ __forceinline__ float kinv(uint32_t k) {
   return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
-// Elements before the first 16-byte boundary of p (at most n).
-__device__ __forceinline__ size_t head_of(const float* p, size_t n) {
-  return min(n, (size_t)((16 - (reinterpret_cast<uintptr_t>(p) & 15)) & 15) / 4);
-}
-
 // Few, large work groups: each ends in two atomics on the same two words,
 // which are served one after the other.  7.1 M values in 12.7 us (28 us with
 // 1024 work groups of 256 threads and dword loads).
@@ -400,6 +578,21 @@ __global__ __launch_bounds__(256) void k_normalize(const float* raw, size_t n,
 
 // ------------------------------------------------------------- dispatchers
 template <int C>
+static hipError_t launch_fcm_x_c(const LaunchArgs& a, int grid, bool m2, bool step, hipStream_t s) {
+  if (!step) {
+    if (m2) hipLaunchKernelGGL((k_fcm_last<C, true>), dim3(grid), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((k_fcm_last<C, false>), dim3(grid), dim3(256), 0, s, a);
+  } else if (a.want_j) {
+    if (m2) hipLaunchKernelGGL((k_fcm_x<C, true, true>), dim3(grid), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((k_fcm_x<C, false, true>), dim3(grid), dim3(256), 0, s, a);
+  } else {
+    if (m2) hipLaunchKernelGGL((k_fcm_x<C, true, false>), dim3(grid), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((k_fcm_x<C, false, false>), dim3(grid), dim3(256), 0, s, a);
+  }
+  return hipGetLastError();
+}
+
+template <int C>
 static hipError_t launch_fcm_c(const LaunchArgs& a, int grid, bool m2, bool step, hipStream_t s) {
   if (m2) {
     if (step) hipLaunchKernelGGL((k_fcm_point<C, true, true>), dim3(grid), dim3(256), 0, s, a);
@@ -468,6 +661,16 @@ hipError_t launch_fcm(int C, const LaunchArgs& a, int grid, bool m2, bool step, 
   }
 }
 
+hipError_t launch_fcm_x(int C, const LaunchArgs& a, int grid, bool m2, bool step, hipStream_t s) {
+  switch (C) {
+#define CASE(c) \
+  case c: return launch_fcm_x_c<c>(a, grid, m2, step, s);
+    PIFCM_FOR_EACH_C(CASE)
+#undef CASE
+    default: return hipErrorInvalidValue;
+  }
+}
+
 hipError_t launch_finalize(int C, const LaunchArgs& a, int npairs, bool step, hipStream_t s) {
   switch (C) {
 #define CASE(c) \
@@ -519,6 +722,11 @@ static hipError_t launch_check_c(const float* U, size_t N, int* flag, hipStream_
   return hipGetLastError();
 }
 
+hipError_t launch_check_finite(const float* x, size_t n, int* flag, hipStream_t s) {
+  hipLaunchKernelGGL(k_check_finite, dim3(std::min(small_grid((n + 15) / 16), 2048)), dim3(256), 0, s, x, n, flag);
+  return hipGetLastError();
+}
+
 hipError_t launch_check_rows(const float* U, size_t N, int C, int* flag, hipStream_t s) {
   switch (C) {
 #define CASE(c) \
@@ -551,14 +759,6 @@ hipError_t launch_confusion(const uint8_t* labels, const uint8_t* truth, size_t 
   return hipGetLastError();
 }
 
-hipError_t launch_permute(const float* U, size_t N, int C, const int32_t* perm, float* out,
-                          hipStream_t s) {
-  Perm p{};
-  for (int j = 0; j < C; ++j) p.p[j] = perm[j];
-  hipLaunchKernelGGL(k_permute, dim3(small_grid(N)), dim3(256), 0, s, U, N, C, p, out);
-  return hipGetLastError();
-}
-
 hipError_t launch_minmax(const float* raw, size_t n, uint32_t* mm, int* flag, hipStream_t s) {
   // At most one work group per CU (256 on the card), each thread four float4s
   // or more.
@@ -571,6 +771,28 @@ hipError_t launch_minmax(const float* raw, size_t n, uint32_t* mm, int* flag, hi
 hipError_t launch_scale(const float* raw, size_t n, const uint32_t* mm, float* out, hipStream_t s) {
   hipLaunchKernelGGL(k_normalize, dim3(small_grid((n + 3) / 4)), dim3(256), 0, s, raw, n, mm, out);
   return hipGetLastError();
+}
+
+template <int C>
+static int occ_fcm_x_c(bool m2, bool step) {
+  int n = 0;
+  const void* f;
+  if (step) f = m2 ? reinterpret_cast<const void*>(&k_fcm_x<C, true, true>)
+                   : reinterpret_cast<const void*>(&k_fcm_x<C, false, true>);
+  else f = m2 ? reinterpret_cast<const void*>(&k_fcm_last<C, true>)
+              : reinterpret_cast<const void*>(&k_fcm_last<C, false>);
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 256, 0) != hipSuccess) n = 1;
+  return std::max(n, 1);
+}
+
+int fcm_x_occupancy(int C, bool m2, bool step) {
+  switch (C) {
+#define CASE(c) \
+  case c: return occ_fcm_x_c<c>(m2, step);
+    PIFCM_FOR_EACH_C(CASE)
+#undef CASE
+    default: return 1;
+  }
 }
 
 template <int C>
