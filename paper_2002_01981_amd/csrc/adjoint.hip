@@ -397,9 +397,7 @@ __global__ __launch_bounds__(64 * kAdjPW) void k_adj_point(const AdjArgs a) {
       }
     }
   }
-  PairDev pr{};
-  pr.partials = a.partials;
-  wave_tile_store<NV>(pr, blockIdx.x * kAdjPW + wave, acc);
+  wave_tile_store<NV>(a.partials, blockIdx.x * kAdjPW + wave, gridDim.x * kAdjPW, acc);
 }
 
 // The transpose gather on wave-private z-streaming tiles (the layout of the
@@ -660,7 +658,7 @@ __global__ __launch_bounds__(1024) void k_adj_finalize(const float* parts, int n
 #pragma unroll
     for (int u = 0; u < kU; ++u)
 #pragma unroll
-      for (int k = 0; k < NV; ++k) v[u][k] = parts[(size_t)(s + u * 1024) * NV + k];
+      for (int k = 0; k < NV; ++k) v[u][k] = parts[(size_t)k * nslots + s + u * 1024];
 #pragma unroll
     for (int u = 0; u < kU; ++u)
 #pragma unroll
@@ -668,29 +666,24 @@ __global__ __launch_bounds__(1024) void k_adj_finalize(const float* parts, int n
   }
   for (; s < nslots; s += 1024) {
 #pragma unroll
-    for (int k = 0; k < NV; ++k) d[k] += (double)parts[(size_t)s * NV + k];
+    for (int k = 0; k < NV; ++k) d[k] += (double)parts[(size_t)k * nslots + s];
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double sum[kSumRegs<NV>];
+  wave_sums<double, NV>(d, sum);
 #pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    double v = d[k];
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    d[k] = v;
-  }
-  if (lane == 0) {
-#pragma unroll
-    for (int k = 0; k < NV; ++k) s_red[wave * NV + k] = d[k];
+  for (int r = 0; r < kSumRegs<NV>; ++r) {
+    const int k = sum_index(r, lane >> 4);
+    if ((lane & 15) == 0 && k < NV) s_red[wave * NV + k] = sum[r];
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (threadIdx.x < NV) {
+    const int k = threadIdx.x;
+    double t = 0.0;
 #pragma unroll
-    for (int k = 0; k < NV; ++k) {
-      double t = 0.0;
-      for (int w = 0; w < NWF; ++w) t += s_red[w * NV + k];
-      if (k < C) out[k] = t;
-      else acc2[k - C] += t;
-    }
+    for (int w = 0; w < NWF; ++w) t += s_red[w * NV + k];
+    if (k < C) out[k] = t;
+    else acc2[k - C] += t;
   }
 }
 

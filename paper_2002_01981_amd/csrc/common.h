@@ -228,142 +228,190 @@ __device__ __forceinline__ void memberships(const float (&d2)[C], float m, float
 
 // ------------------------------------------------------------ tile sums
 // Every tile of a launch leaves NV fp32 sums in its own slot of the pair's
-// partials ([tile][NV]); a per-pair finalise kernel launched right after adds
-// the slots in fp64 in tile order.  Both reductions have a fixed order, so
-// the results do not depend on scheduling.
+// partials ([NV][slots], so that the slots of one sum are read side by side);
+// a per-pair finalise kernel launched right after adds the slots in fp64 in
+// tile order.  Both reductions have a fixed order, so the results do not
+// depend on scheduling.
 
-// Wave owning a tile: butterfly over the 64 lanes, lane 0 stores the slot.
+// The halves of 32 lanes of a added together in the lower half, those of b in
+// the upper half; alike for the rows of 16 within each half; and each row's
+// lanes added to those N further on.
+__device__ __forceinline__ float swap32_add(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float swap16_add(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+template <int N>
+__device__ __forceinline__ float ror_add(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, false));
+}
+__device__ __forceinline__ double make_f64(uint32_t lo, uint32_t hi) {
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+__device__ __forceinline__ uint32_t lo_of(double v) { return (uint32_t)__double_as_longlong(v); }
+__device__ __forceinline__ uint32_t hi_of(double v) { return (uint32_t)((uint64_t)__double_as_longlong(v) >> 32); }
+__device__ __forceinline__ double swap32_add(double a, double b) {
+  const auto l = __builtin_amdgcn_permlane32_swap(lo_of(a), lo_of(b), false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap(hi_of(a), hi_of(b), false, false);
+  return make_f64(l[0], h[0]) + make_f64(l[1], h[1]);
+}
+__device__ __forceinline__ double swap16_add(double a, double b) {
+  const auto l = __builtin_amdgcn_permlane16_swap(lo_of(a), lo_of(b), false, false);
+  const auto h = __builtin_amdgcn_permlane16_swap(hi_of(a), hi_of(b), false, false);
+  return make_f64(l[0], h[0]) + make_f64(l[1], h[1]);
+}
+template <int N>
+__device__ __forceinline__ double ror_add(double v) {
+  const int l = __builtin_amdgcn_update_dpp(0, (int)lo_of(v), 0x120 + N, 0xf, 0xf, false);
+  const int h = __builtin_amdgcn_update_dpp(0, (int)hi_of(v), 0x120 + N, 0xf, 0xf, false);
+  return v + make_f64((uint32_t)l, (uint32_t)h);
+}
+
+// Sums of NV values over the 64 lanes, each by the tree of a butterfly over
+// l ^ 32, l ^ 16, ..., l ^ 1.  The first two levels put two and then four
+// values into one register, so the rest costs a quarter: about 30
+// instructions for 9 values and no LDS, against 108 and 54 LDS permutes for
+// one butterfly per value.  On return every lane of row q (lanes 16 q ..
+// 16 q + 15) of out[r] holds the sum of value sum_index(r, q), if below NV.
 template <int NV>
-__device__ __forceinline__ void wave_tile_store(const PairDev& pr, int tile, float (&acc)[NV]) {
+constexpr int kSumRegs = (NV + 3) / 4;
+__device__ __forceinline__ int sum_index(int r, int row) { return 4 * r + ((row & 1) << 1 | row >> 1); }
+template <class T, int NV>
+__device__ __forceinline__ void wave_sums(const T (&v)[NV], T (&out)[kSumRegs<NV>]) {
 #pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    float v = acc[k];
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    acc[k] = v;
-  }
-  if ((threadIdx.x & 63) == 0) {
-    gfloat* slot = as_global(pr.partials) + (size_t)tile * NV;
-#pragma unroll
-    for (int k = 0; k < NV; ++k) slot[k] = acc[k];
+  for (int r = 0; r < kSumRegs<NV>; ++r) {
+    auto at = [&](int k) -> T { return k < NV ? v[k < NV ? k : 0] : T(0); };
+    T s = swap16_add(swap32_add(at(4 * r), at(4 * r + 1)), swap32_add(at(4 * r + 2), at(4 * r + 3)));
+    s = ror_add<8>(s);
+    s = ror_add<4>(s);
+    s = ror_add<2>(s);
+    out[r] = ror_add<1>(s);
   }
 }
 
-// Work group owning a tile: butterfly per wave, waves in order through LDS.
+// Wave owning a tile: its sums to slot `tile` of `slots`.
+template <int NV>
+__device__ __forceinline__ void wave_tile_store(float* partials, int tile, int slots, const float (&acc)[NV]) {
+  float sum[kSumRegs<NV>];
+  wave_sums<float, NV>(acc, sum);
+  const int lane = threadIdx.x & 63;
+  gfloat* slot = as_global(partials) + tile;
+#pragma unroll
+  for (int r = 0; r < kSumRegs<NV>; ++r) {
+    const int k = sum_index(r, lane >> 4);
+    if ((lane & 15) == 0 && k < NV) slot[(size_t)k * slots] = sum[r];
+  }
+}
+
+// Work group owning a tile: the sums of its waves, added in order through LDS.
 template <int NV, int NT>
-__device__ __forceinline__ void block_tile_store(const PairDev& pr, int tile, float (&acc)[NV],
+__device__ __forceinline__ void block_tile_store(float* partials, int tile, int slots, const float (&acc)[NV],
                                                  float* s_red) {
   constexpr int NW = NT / 64;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  float sum[kSumRegs<NV>];
+  wave_sums<float, NV>(acc, sum);
 #pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    float v = acc[k];
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    acc[k] = v;
-  }
-  if (lane == 0) {
-#pragma unroll
-    for (int k = 0; k < NV; ++k) s_red[wave * NV + k] = acc[k];
+  for (int r = 0; r < kSumRegs<NV>; ++r) {
+    const int k = sum_index(r, lane >> 4);
+    if ((lane & 15) == 0 && k < NV) s_red[wave * NV + k] = sum[r];
   }
   __syncthreads();
   if (threadIdx.x < NV) {
     float s = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) s += s_red[w * NV + threadIdx.x];
-    as_global(pr.partials)[(size_t)tile * NV + threadIdx.x] = s;
+    as_global(partials)[(size_t)threadIdx.x * slots + tile] = s;
   }
   __syncthreads();
 }
 
-// Advance the state of a pair from its fp64 totals (one thread): new centres
-// (eq (3)), J of the iteration's input state (eq (1)) and the stop rule; or,
-// for the objective-only pass, the fitness.
-template <int C, bool STEP>
-__device__ __forceinline__ void finish_pair(SolveState* st, const double* tot) {
-  if constexpr (STEP) {
-    const int t = st->iter + 1;
-    const int par = t & 1;
-#pragma unroll
-    for (int j = 0; j < C; ++j) {
-      const double den = tot[C + j];
-      st->c[par][j] = den > 0.0 ? (float)(tot[j] / den) : st->c[par ^ 1][j];
-    }
-    if (st->B_hist)
-      for (int j = 0; j < C; ++j) st->B_hist[(size_t)(t - 1) * C + j] = tot[C + j];
-    if (st->c_hist)
-      for (int j = 0; j < C; ++j) st->c_hist[(size_t)t * C + j] = st->c[par][j];
-    const double J = tot[2 * C];
-    if (st->J_hist) st->J_hist[t - 1] = J;
-    int stop = 0;
-    if (t >= 2 && st->eps > 0.f && fabs(J - st->J_prev1) <= (double)st->eps * fabs(st->J_prev1))
-      stop = 1;
-    if (t >= st->max_iter) stop = 1;
-    st->J_prev2 = st->J_prev1;
-    st->J_prev1 = J;
-    st->iter = t;
-    st->stop = stop;
-  } else {
-    st->J_eval = tot[0];
-  }
-}
-
 // One work group per pair: add the pair's tile slots in fp64 (thread t takes
-// tiles t, t + 256, ...; then a fixed butterfly and the waves in order) and
-// advance its state.  Pairs that have stopped are left alone.
-template <int C, bool STEP>
-__global__ __launch_bounds__(256) void k_finalize(const LaunchArgs a) {
+// slots t, t + 1024, ...; then the wave's tree and the waves in order) and
+// advance its state: new centres (eq (3)), J of the iteration's input state
+// (eq (1)) and the stop rule; or, for the objective-only pass, the fitness.
+// Pairs that have stopped are left alone.  A short dependent launch, bound by
+// latency: the state is read while the slots are, one lane finishes each
+// centre.  One step of 16, 2640 and 11556 slots (C = 4): 3.3, 4.9 and 12 us
+// (3.9, 7.2 and 18 us with 256 threads reading slots of 2C + 1 floats).
+// NT = 256, for launches whose pairs have at most 256 slots, starts 1 us
+// sooner than NT = 1024 and gives the same bits (the other threads add zeros).
+template <int C, bool STEP, int NT>
+__global__ __launch_bounds__(NT) void k_finalize(const LaunchArgs a) {
   constexpr int NV = STEP ? 2 * C + 1 : 1;
-  __shared__ double s_red[4 * NV];
-  const int pair = blockIdx.x;
-  const PairDev pr = a.pairs[pair];
+  constexpr int NWF = NT / 64;
+  __shared__ double s_red[NWF * NV];
+  const int pair = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const PairDev pr = ld_const(a.pairs + pair);
   SolveState* st = pr.st;
-  if (STEP && st->stop) return;
-  const VolDev vd = a.vols[pair / a.P];
-  const int tiles = a.use_1d ? vd.tiles1d : vd.tiles;
+  if (STEP && ld_const(&st->stop)) return;
+  const VolDev* vd = a.vols + pair / a.P;
+  const int slots = a.use_1d ? ld_const(&vd->tiles1d) : ld_const(&vd->tiles);
+  const int t = ld_const(&st->iter) + 1;
+  const float c_old = st->c[(t & 1) ^ 1][lane & (kMaxC - 1)];
+  const double J1 = st->J_prev1;
   double d[NV];
 #pragma unroll
   for (int k = 0; k < NV; ++k) d[k] = 0.0;
   const gfloat* parts = as_global(pr.partials);
-  // Each thread adds the slots s, s + 256, s + 512, ... in that order; eight
-  // of them are loaded at once so their latencies overlap (the order of the
-  // additions, and so the result, is that of the plain strided loop).
-  constexpr int kU = 8;
+  // Four slots in flight per thread (the order of the additions, and so the
+  // result, is that of the plain strided loop).
+  constexpr int kU = 4;
   int s = threadIdx.x;
-  for (; s + (kU - 1) * 256 < tiles; s += kU * 256) {
+  for (; s + (kU - 1) * NT < slots; s += kU * NT) {
     float v[kU][NV];
 #pragma unroll
     for (int u = 0; u < kU; ++u)
 #pragma unroll
-      for (int k = 0; k < NV; ++k) v[u][k] = parts[(size_t)(s + u * 256) * NV + k];
+      for (int k = 0; k < NV; ++k) v[u][k] = parts[(size_t)k * slots + s + u * NT];
 #pragma unroll
     for (int u = 0; u < kU; ++u)
 #pragma unroll
       for (int k = 0; k < NV; ++k) d[k] += (double)v[u][k];
   }
-  for (; s < tiles; s += 256) {
+  for (; s < slots; s += NT) {
 #pragma unroll
-    for (int k = 0; k < NV; ++k) d[k] += (double)parts[(size_t)s * NV + k];
+    for (int k = 0; k < NV; ++k) d[k] += (double)parts[(size_t)k * slots + s];
   }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double sum[kSumRegs<NV>];
+  wave_sums<double, NV>(d, sum);
 #pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    double v = d[k];
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    d[k] = v;
-  }
-  if (lane == 0) {
-#pragma unroll
-    for (int k = 0; k < NV; ++k) s_red[wave * NV + k] = d[k];
+  for (int r = 0; r < kSumRegs<NV>; ++r) {
+    const int k = sum_index(r, lane >> 4);
+    if ((lane & 15) == 0 && k < NV) s_red[wave * NV + k] = sum[r];
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double tot[NV];
+  if (wave != 0) return;
+  auto total = [&](int k) -> double {
+    double v = 0.0;
 #pragma unroll
-    for (int k = 0; k < NV; ++k)
-      tot[k] = ((s_red[k] + s_red[NV + k]) + s_red[2 * NV + k]) + s_red[3 * NV + k];
-    finish_pair<C, STEP>(st, tot);
+    for (int w = 0; w < NWF; ++w) v += s_red[w * NV + k];
+    return v;
+  };
+  if constexpr (STEP) {
+    if (lane < C) {
+      const double den = total(C + lane);
+      const float c = den > 0.0 ? (float)(total(lane) / den) : c_old;
+      st->c[t & 1][lane] = c;
+      if (st->B_hist) st->B_hist[(size_t)(t - 1) * C + lane] = den;
+      if (st->c_hist) st->c_hist[(size_t)t * C + lane] = c;
+    }
+    if (lane == 0) {
+      const double J = total(2 * C);
+      if (st->J_hist) st->J_hist[t - 1] = J;
+      int stop = 0;
+      if (t >= 2 && st->eps > 0.f && fabs(J - J1) <= (double)st->eps * fabs(J1)) stop = 1;
+      if (t >= st->max_iter) stop = 1;
+      st->J_prev2 = J1;
+      st->J_prev1 = J;
+      st->iter = t;
+      st->stop = stop;
+    }
+  } else {
+    if (lane == 0) st->J_eval = total(0);
   }
 }
 

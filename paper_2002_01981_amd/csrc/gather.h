@@ -552,7 +552,7 @@ __global__ __launch_bounds__(64 * NW) void k_ifcm_gather(const LaunchArgs a) {
 
 #pragma unroll
     for (int k = 0; k < PT; ++k)
-      if (live[k]) wave_tile_store<NV>(pr[k], tile, acc[k]);
+      if (live[k]) wave_tile_store<NV>(pr[k].partials, tile, vd.tiles, acc[k]);
   }
   if (handout && lane == 0) {
     __threadfence();

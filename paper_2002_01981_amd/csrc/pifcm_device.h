@@ -91,7 +91,8 @@ struct LaunchArgs {
   int32_t fcm_sorted;    // 1: plain FCM stores its final columns by ascending centre
   const RingOff* ring; // general-neighbourhood offsets (ring kernel only)
   int32_t nring;       // number of offsets
-  int32_t pad1;
+  int32_t ring_gen;    // which table `ring` holds (part of the graph cache key)
+  int32_t max_slots;   // most tile slots of a pair of the launch
   int32_t pt;          // particles per work item of the fused step (1 or 2):
                        // its items are (volume, group of pt particles, tile)
   int32_t want_j;      // 1: J of an iteration's input state is needed (a stop

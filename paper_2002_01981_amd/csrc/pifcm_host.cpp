@@ -562,7 +562,7 @@ LaunchArgs make_args(const pifcm_ctx* ctx, const VolDev* vols_dev, const PairDev
   if (is_ring(kind)) {
     a.ring = (const RingOff*)ctx->ring_tab.p;
     a.nring = ctx->ring_n;
-    a.pad1 = ctx->ring_gen;  // part of the graph cache key
+    a.ring_gen = ctx->ring_gen;
     for (int r = 0; r <= kMaxRings; ++r) a.W[r] = ctx->ring_W[r];
   }
   // Fused-step items are (volume, group of pt particles, tile).
@@ -571,7 +571,9 @@ LaunchArgs make_args(const pifcm_ctx* ctx, const VolDev* vols_dev, const PairDev
   int acc = 0;
   for (int b = 0; b < nvol; ++b) {
     a.item_begin[b] = acc;
-    acc += groups * (a.use_1d ? vh[b].tiles1d : vh[b].tiles);
+    const int slots = a.use_1d ? vh[b].tiles1d : vh[b].tiles;
+    a.max_slots = std::max(a.max_slots, slots);
+    acc += groups * slots;
   }
   a.item_begin[nvol] = acc;
   a.nitems = acc;

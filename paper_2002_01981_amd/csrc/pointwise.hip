@@ -99,7 +99,7 @@ __global__ __launch_bounds__(256) void k_fcm_x(const LaunchArgs a) {
         }
       }
     }
-    block_tile_store<NV, NT>(pr, tile, acc, s_red);
+    block_tile_store<NV, NT>(pr.partials, tile, vd.tiles1d, acc, s_red);
   }
 }
 
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(256) void k_fcm_last(const LaunchArgs a) {
         }
       }
     }
-    block_tile_store<1, NT>(pr, tile, acc, s_red);
+    block_tile_store<1, NT>(pr.partials, tile, vd.tiles1d, acc, s_red);
   }
 }
 
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(256) void k_fcm_point(const LaunchArgs a) {
         acc[0] += Jv;
       }
     }
-    block_tile_store<NV, NT>(pr, tile, acc, s_red);
+    block_tile_store<NV, NT>(pr.partials, tile, vd.tiles1d, acc, s_red);
   }
 }
 
@@ -604,11 +604,17 @@ static hipError_t launch_fcm_c(const LaunchArgs& a, int grid, bool m2, bool step
   return hipGetLastError();
 }
 
+template <int C, int NT>
+static hipError_t launch_finalize_ct(const LaunchArgs& a, int npairs, bool step, hipStream_t s) {
+  if (step) hipLaunchKernelGGL((k_finalize<C, true, NT>), dim3(npairs), dim3(NT), 0, s, a);
+  else hipLaunchKernelGGL((k_finalize<C, false, NT>), dim3(npairs), dim3(NT), 0, s, a);
+  return hipGetLastError();
+}
+
 template <int C>
 static hipError_t launch_finalize_c(const LaunchArgs& a, int npairs, bool step, hipStream_t s) {
-  if (step) hipLaunchKernelGGL((k_finalize<C, true>), dim3(npairs), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((k_finalize<C, false>), dim3(npairs), dim3(256), 0, s, a);
-  return hipGetLastError();
+  return a.max_slots <= 256 ? launch_finalize_ct<C, 256>(a, npairs, step, s)
+                            : launch_finalize_ct<C, 1024>(a, npairs, step, s);
 }
 
 template <int C>

@@ -132,7 +132,7 @@ __global__ __launch_bounds__(64 * kRingWaves) void k_ifcm_ring(const LaunchArgs 
         acc[0] += Jv;
       }
     }
-    wave_tile_store<NV>(pr, tile, acc);
+    wave_tile_store<NV>(pr.partials, tile, vd.tiles, acc);
   }
 }
 

@@ -410,7 +410,7 @@ __global__ __launch_bounds__(64 * kRing2Waves) void k_ifcm_ring2(const LaunchArg
       plane(p, I0{}, Gen{});
       shift();
     }
-    wave_tile_store<NV>(pr, tile, acc);
+    wave_tile_store<NV>(pr.partials, tile, vd.tiles, acc);
   }
 }
 
