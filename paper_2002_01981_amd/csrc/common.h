@@ -349,7 +349,7 @@ __global__ __launch_bounds__(NT) void k_finalize(const LaunchArgs a) {
   SolveState* st = pr.st;
   if (STEP && ld_const(&st->stop)) return;
   const VolDev* vd = a.vols + pair / a.P;
-  const int slots = a.use_1d ? ld_const(&vd->tiles1d) : ld_const(&vd->tiles);
+  const int slots = a.use_1d ? ld_const(&vd->tiles1d) : ld_const(&vd->slots);
   const int t = ld_const(&st->iter) + 1;
   const float c_old = st->c[(t & 1) ^ 1][lane & (kMaxC - 1)];
   const double J1 = st->J_prev1;

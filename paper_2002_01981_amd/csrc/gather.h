@@ -49,10 +49,12 @@
 //     formed from the column position and the plane index;
 //   * cells outside the volume are staged with u = 0, so they add nothing to
 //     any sum.
-// Sums over voxels are per-lane in fp32, reduced per tile in a fixed
-// butterfly order into the tile's own slot; k_finalize then adds the slots of
-// each pair in fp64 in tile order (no floating-point atomics: results are
-// bit-reproducible).
+// Sums over voxels are per-lane in fp32, reduced in a fixed tree over the wave
+// after every run of sc planes into that run's own slot; k_finalize then adds
+// the slots of each pair in fp64 in their order (no floating-point atomics:
+// results are bit-reproducible).  sc depends on the volume alone, and a tile
+// holds one run or several: a launch picks its tile depth by how many pairs
+// it carries without changing a bit of any result.
 #pragma once
 #include "common.h"
 
@@ -63,7 +65,10 @@ constexpr int kHX = kWX + 2, kHY = kWY + 2;    // staged plane with halo
 constexpr int kNCell = kHX * kHY;              // 108 cells
 constexpr int kNHalo = kNCell - 64;            // 44 halo cells, one per lane
 
-template <int C, bool M2, int NW, bool STEP, int PT>
+// RUNS: tiles may hold several runs of planes.  A launch without such tiles
+// takes the instance without the test after every plane (13.0 against 13.3 ms
+// on six ragged volumes x 64 particles).
+template <int C, bool M2, int NW, bool STEP, int PT, bool RUNS>
 __global__ __launch_bounds__(64 * NW) void k_ifcm_gather(const LaunchArgs a) {
   constexpr int CP = (C + 3) / 4 * 4;
   constexpr int CH = C - 1;  // clusters whose H is gathered
@@ -533,6 +538,21 @@ __global__ __launch_bounds__(64 * NW) void k_ifcm_gather(const LaunchArgs a) {
     // The interior's last prefetch reads plane p + 4 <= zhi, which is nz
     // when the tile ends at the volume's last plane: load_plane keeps its
     // plane-range test.  tests/test_plane_walk.py replays this walk.
+    // The sums of a finished run of sc planes go to its slot (slots are
+    // numbered like tiles of sc planes); without RUNS a tile is one run.
+    const int txy = vd.ntx * vd.nty;
+    int slot = RUNS ? tile + tzi * (vd.zc / vd.sc - 1) * txy : tile, left = vd.sc;
+    auto finished = [&](int z) __attribute__((always_inline)) {
+      if (RUNS && --left > 0 && z + 1 < zhi) return;
+#pragma unroll
+      for (int k = 0; k < PT; ++k) {
+        if (live[k]) wave_tile_store<NV>(pr[k].partials, slot, vd.slots, acc[k]);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) acc[k][v] = 0.f;
+      }
+      slot += txy;
+      left = vd.sc;
+    };
     int p = zlo - 1;
     for (; p <= zlo && p <= zhi; ++p) {
       plane(p, I0{}, I1{}, I2{}, Bdyn{}, Gen{});
@@ -542,17 +562,18 @@ __global__ __launch_bounds__(64 * NW) void k_ifcm_gather(const LaunchArgs a) {
     // buffer 2): every test is true, slots rotate by name.
     for (; p + 4 <= zhi; p += 3) {
       plane(p, I0{}, I1{}, I2{}, I2{}, Steady{});
+      if constexpr (RUNS) finished(p - 1);
       plane(p + 1, I1{}, I2{}, I0{}, I0{}, Steady{});
+      if constexpr (RUNS) finished(p);
       plane(p + 2, I2{}, I0{}, I1{}, I1{}, Steady{});
+      if constexpr (RUNS) finished(p + 1);
     }
     for (; p <= zhi; ++p) {
       plane(p, I0{}, I1{}, I2{}, Bdyn{}, Gen{});
       shift();
+      if constexpr (RUNS) finished(p - 1);
     }
-
-#pragma unroll
-    for (int k = 0; k < PT; ++k)
-      if (live[k]) wave_tile_store<NV>(pr[k].partials, tile, vd.tiles, acc[k]);
+    if constexpr (!RUNS) finished(zhi - 1);
   }
   if (handout && lane == 0) {
     __threadfence();
@@ -566,18 +587,24 @@ __global__ __launch_bounds__(64 * NW) void k_ifcm_gather(const LaunchArgs a) {
 // Launch / occupancy of one C with NW waves per work group and PT particles
 // per work item.  NW and PT variants exist only where ALL_NW is set (the
 // C = 4 fast path); elsewhere NW = 4 and PT = 1.
+template <int C, bool M2, int NW, int PT, bool RUNS>
+static hipError_t launch_gather_ctr(const LaunchArgs& a, int grid, bool step, hipStream_t s) {
+  if (step) hipLaunchKernelGGL((k_ifcm_gather<C, M2, NW, true, PT, RUNS>), dim3(grid), dim3(64 * NW), 0, s, a);
+  else hipLaunchKernelGGL((k_ifcm_gather<C, M2, NW, false, PT, RUNS>), dim3(grid), dim3(64 * NW), 0, s, a);
+  return hipGetLastError();
+}
+
 template <int C, bool M2, int NW, int PT>
 static hipError_t launch_gather_ct(const LaunchArgs& a, int grid, bool step, hipStream_t s) {
-  if (step) hipLaunchKernelGGL((k_ifcm_gather<C, M2, NW, true, PT>), dim3(grid), dim3(64 * NW), 0, s, a);
-  else hipLaunchKernelGGL((k_ifcm_gather<C, M2, NW, false, PT>), dim3(grid), dim3(64 * NW), 0, s, a);
-  return hipGetLastError();
+  return a.runs ? launch_gather_ctr<C, M2, NW, PT, true>(a, grid, step, s)
+                : launch_gather_ctr<C, M2, NW, PT, false>(a, grid, step, s);
 }
 
 template <int C, bool M2, int NW, int PT>
 static int occ_gather_ct(bool step) {
   int n = 0;
-  const void* f = step ? reinterpret_cast<const void*>(&k_ifcm_gather<C, M2, NW, true, PT>)
-                       : reinterpret_cast<const void*>(&k_ifcm_gather<C, M2, NW, false, PT>);
+  const void* f = step ? reinterpret_cast<const void*>(&k_ifcm_gather<C, M2, NW, true, PT, false>)
+                       : reinterpret_cast<const void*>(&k_ifcm_gather<C, M2, NW, false, PT, false>);
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 64 * NW, 0) != hipSuccess) n = 1;
   return std::max(n, 1);
 }

@@ -42,6 +42,9 @@ struct VolDev {
   int32_t zc;          // planes per tile
   int32_t ntx, nty, ntz;
   int32_t tiles;       // ntx * nty * ntz (gather kernels)
+  int32_t sc;          // planes per slot of sums: zc, or a divisor of it where
+                       // a tile holds several runs of planes
+  int32_t slots;       // slots of sums of a pair: ntx * nty * ceil(planes / sc)
   int32_t tiles1d;     // ceil(active voxels / (256 vpt)) (pointwise kernels)
   int32_t zbeg, zend;  // planes iterated; the others are fixed context
   int32_t vpt;         // voxels per thread of the pointwise kernels
@@ -93,6 +96,7 @@ struct LaunchArgs {
   int32_t nring;       // number of offsets
   int32_t ring_gen;    // which table `ring` holds (part of the graph cache key)
   int32_t max_slots;   // most tile slots of a pair of the launch
+  int32_t runs;        // 1: a volume's tiles hold several runs of planes
   int32_t pt;          // particles per work item of the fused step (1 or 2):
                        // its items are (volume, group of pt particles, tile)
   int32_t want_j;      // 1: J of an iteration's input state is needed (a stop

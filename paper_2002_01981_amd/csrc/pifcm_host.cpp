@@ -40,6 +40,7 @@ struct TileShape {
   int nw = 4;   // wavefronts per work group of the fused step
   int zc = 0;   // planes per tile (0: the volume's default, default_zc)
   int pt = 1;   // particles per work item of the batched fused step (C = 4: 1 or 2)
+  bool deep = false;  // zc is the default: a launch over many pairs may give a tile several runs of zc planes
 };
 
 constexpr int kChunk = 8;            // iterations between stop-flag reads
@@ -215,27 +216,75 @@ size_t nvox(const pifcm_volume& v) { return (size_t)v.nx * v.ny * v.nz; }
 
 // Largest plane count per tile such that the 32-bit in-tile offsets of the
 // fused step stay below 2^31 bytes: (zc + 2) * nx * ny * C * 4 < 2^31.
-int max_zc(const pifcm_volume& v, int C) {
+int deepest_zc(const pifcm_volume& v, int C) {
   const double per_plane = (double)v.nx * v.ny * C * 4.0;
-  const double z = std::floor((2147483647.0 / per_plane)) - 2.0;
-  return (int)std::max(0.0, std::min(z, (double)v.nz));
+  return (int)std::max(0.0, std::min(std::floor(2147483647.0 / per_plane) - 2.0, 1e9));
+}
+int max_zc(const pifcm_volume& v, int C) { return std::min(deepest_zc(v, C), v.nz); }
+
+// Which step kernel a launch uses.
+// kFcm: plain FCM without states in memory; kFcmStore: with them (adjoint).
+enum Kind { kGather = 0, kFcm = 1, kRing = 2, kRing2 = 3, kFcmStore = 4 };
+
+bool ring_params(const pifcm_params* p) { return p->V > 1 || (p->flags & PIFCM_SHELL_SQDIST); }
+// The two Chebyshev rings of the 5x5x5 cube with C <= 4 run the fused
+// two-ring kernel; other general neighbourhoods walk the offset table.
+bool ring2_params(const pifcm_params* p) {
+  return p->V == 2 && !(p->flags & PIFCM_SHELL_SQDIST) && p->C <= 4;
+}
+bool is_ring(int kind) { return kind == kRing || kind == kRing2; }
+
+// The cost, in plane passes, of `items` tiles (of mean depth `depth`) of the
+// fused step on `resident` waves.  A tile costs its planes and about four
+// more (its two halo planes and the start of its walk); a plane pass takes
+// 2 + k units of time on a SIMD that holds k waves (lone-wave latency and
+// VALU issue: 0.75 + 0.33 k us at C = 4, m = 2; 0.8 + 0.44 k at C = 3, m = 2.5;
+// 1.2 + 0.6 k at C = 8, fitted over depths of 8 to 181 planes within 5 %), and
+// the tiles run in rounds of `resident`, the last one with fewer waves.
+double tile_cost(double items, double depth, double resident, double simds) {
+  const double full = std::floor(items / resident), rest = items - full * resident;
+  return (depth + 4.0) * (full * (2.0 + resident / simds) + (rest > 0.0 ? 2.0 + rest / simds : 0.0));
 }
 
-// Planes per tile when no shape was chosen for the volume.  A solve of one
-// pair runs ceil(tiles / R) rounds of tiles on the R waves the fused step
-// keeps resident (4 waves per work group), and a tile costs about zc + 4
-// plane passes (its two halo planes and the start of its walk): among the
-// depths ceil(nz / k) and 32 that are at least min(nz, 32) deep, take the
-// one with the fewest rounds * (zc + 4), the deeper one on a tie.  Batched
-// swarm launches hold many pairs and want deep tiles (fewer tile starts and
-// halo planes), hence the floor; the depth does not depend on the launch, so
-// every launch mode gives the same bits.  On the 181-plane brain volume this
-// is 46 planes (four tiles per column, one round) rather than 32 (six per
-// column, 1.3 rounds).
-int default_zc(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v) {
+// Waves of the fused step the card keeps resident (4 waves per work group).
+double resident_waves(pifcm_ctx* ctx, int C, bool m2) {
   int& occ = ctx->occ_gather[std::max(0, std::min(C, kMaxC))][m2 ? 1 : 0];
   if (occ == 0) occ = std::max(1, gather_occupancy(C, 4, 1, m2, true));
-  const long R = (long)occ * ctx->num_cu * 4;
+  return 4.0 * occ * ctx->num_cu;
+}
+
+// Planes per tile of the fused step when no shape was chosen for the volume:
+// the depth ceil(nz / k) that costs one pair's tiles least (the deeper one on a
+// tie).  It depends on the volume alone: tile sums are kept per run of that
+// many planes in every launch (VolDev::sc), so all launch modes give the same
+// bits; a launch over many pairs gives its tiles several runs (tile_runs).
+// One step of a lone pair: 181x217x181, C = 4: 46 planes, 82 us (23: 88 us,
+// 61: 91 us, 181: 190 us); 162x181x75, C = 3, m = 2.5: 11 planes, 38 us (38
+// planes, the least with a floor of 32: 50 us); 32x32x8: 1 plane, 10 us (8
+// planes: 15 us).
+int default_zc(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v) {
+  const double R = resident_waves(ctx, C, m2), simds = 4.0 * ctx->num_cu;
+  const double txy = (double)((v.nx + kWaveTileX - 1) / kWaveTileX) * ((v.ny + kWaveTileY - 1) / kWaveTileY);
+  int best = v.nz;
+  double best_cost = -1.0;
+  for (int k = 1; k <= v.nz; ++k) {
+    const int zc = (v.nz + k - 1) / k;
+    if (k > 1 && zc == (v.nz + k - 2) / (k - 1)) continue;  // the depth of k - 1
+    const double cost = tile_cost(txy * ((v.nz + zc - 1) / zc), zc, R, simds);
+    if (best_cost < 0.0 || cost < best_cost) {
+      best_cost = cost;
+      best = zc;
+    }
+  }
+  return best;
+}
+
+// Planes per tile of the general-neighbourhood kernels: of the depths
+// ceil(nz / k) and 32 that are at least min(nz, 32) deep, the one with the
+// fewest rounds of one pair's tiles on the fused step's resident waves times
+// (depth + 4); the deeper one on a tie.
+int ring_zc(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v) {
+  const long R = (long)resident_waves(ctx, C, m2);
   const long txy = (long)((v.nx + kWaveTileX - 1) / kWaveTileX) * ((v.ny + kWaveTileY - 1) / kWaveTileY);
   const int floor_zc = std::min(v.nz, 32);
   int best = v.nz;
@@ -257,19 +306,22 @@ int default_zc(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v) {
   return best;
 }
 
-TileShape shape_for(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v) {
+TileShape shape_for(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v, int kind) {
   TileShape t;
   auto it = ctx->tuned.find(std::make_tuple(C, (int)m2, v.nx, v.ny, v.nz));
   if (it != ctx->tuned.end()) t = it->second;
-  if (t.zc <= 0) t.zc = default_zc(ctx, C, m2, v);
+  if (t.zc <= 0) {
+    t.deep = kind == kGather;
+    t.zc = is_ring(kind) ? ring_zc(ctx, C, m2, v) : default_zc(ctx, C, m2, v);
+  }
   t.zc = std::max(1, std::min(t.zc, max_zc(v, C)));
   return t;
 }
 
 // Launch descriptor of a volume whose planes [zbeg, zend) are iterated
-// (zend < 0: all planes).
+// (zend < 0: all planes), its tiles `runs` runs of ts.zc planes deep.
 VolDev make_vol(const pifcm_volume& v, const float* invg, TileShape ts, int zbeg = 0, int zend = -1,
-                const float* rinv = nullptr) {
+                const float* rinv = nullptr, int runs = 1) {
   if (zend < 0) zend = v.nz;
   VolDev d{};
   d.x = v.x;
@@ -281,11 +333,13 @@ VolDev make_vol(const pifcm_volume& v, const float* invg, TileShape ts, int zbeg
   d.zbeg = zbeg;
   d.zend = zend;
   const int nact = zend - zbeg;
-  d.zc = std::max(1, std::min(ts.zc, nact));
+  d.sc = std::max(1, std::min(ts.zc, nact));
+  d.zc = (int)std::min<long>((long)d.sc * runs, (nact + d.sc - 1) / d.sc * (long)d.sc);
   d.ntx = (v.nx + kWaveTileX - 1) / kWaveTileX;
   d.nty = (v.ny + kWaveTileY - 1) / kWaveTileY;
   d.ntz = (nact + d.zc - 1) / d.zc;
   d.tiles = d.ntx * d.nty * d.ntz;
+  d.slots = d.ntx * d.nty * ((nact + d.sc - 1) / d.sc);
   // Pointwise passes: at most kFcmTiles work groups of 256 threads (four waves
   // per SIMD of the card, and as few sums to add per iteration).
   const size_t n1 = (size_t)v.nx * v.ny * nact, most = (size_t)256 * kFcmTiles;
@@ -306,10 +360,6 @@ int grid_for(pifcm_ctx* ctx, int nitems, int occupancy, int per_group = 1) {
   else g = resident / 8 * 8;
   return (int)std::max<long>(8, g);
 }
-
-// Which step kernel a launch uses.
-// kFcm: plain FCM without states in memory; kFcmStore: with them (adjoint).
-enum Kind { kGather = 0, kFcm = 1, kRing = 2, kRing2 = 3, kFcmStore = 4 };
 
 // g_inv of `nv` volumes into invg (volume b at invg + invg_off[b]; invg NULL:
 // not needed), the intensity check, and the row check of caller U0 pointers
@@ -380,14 +430,6 @@ SolveState init_state(const float* c0, int C, float lam, float xi, const pifcm_p
   return s;
 }
 
-bool ring_params(const pifcm_params* p) { return p->V > 1 || (p->flags & PIFCM_SHELL_SQDIST); }
-// The two Chebyshev rings of the 5x5x5 cube with C <= 4 run the fused
-// two-ring kernel; other general neighbourhoods walk the offset table.
-bool ring2_params(const pifcm_params* p) {
-  return p->V == 2 && !(p->flags & PIFCM_SHELL_SQDIST) && p->C <= 4;
-}
-bool is_ring(int kind) { return kind == kRing || kind == kRing2; }
-
 // lambda = xi = 0 makes the attraction factor of eq (4) exactly 1 for every
 // neighbourhood: plain FCM.
 int kind_of(const pifcm_params* p, bool zero_weights) {
@@ -409,7 +451,35 @@ int pt_for(int kind, int C, int P, const TileShape& ts) {
   return (kind == kGather && C == 4 && P >= 2) ? std::max(1, std::min(ts.pt, 2)) : 1;
 }
 
-// Work items in flight per work group.
+// Runs of a volume's default planes that a tile of a batched launch takes
+// (the same number for each volume, as far as its planes go): the cheapest by
+// tile_cost over all tiles of the launch, for `groups` particle groups per
+// volume.  A single pair takes one; with many pairs every round is full and
+// whole columns win (fewer tile starts and halo planes: six ragged volumes x
+// 64 particles, 13.3 ms per launch; 13.8 ms with a lone pair's depths).
+int tile_runs(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume* vols, const std::vector<TileShape>& shapes,
+              long groups) {
+  const double R = resident_waves(ctx, C, m2), simds = 4.0 * ctx->num_cu;
+  int best = 1, most = 1;
+  for (size_t b = 0; b < shapes.size(); ++b)
+    if (shapes[b].deep) most = std::max(most, (vols[b].nz + shapes[b].zc - 1) / shapes[b].zc);
+  double best_cost = -1.0;
+  for (int k = 1; k <= most; ++k) {
+    double items = 0.0, planes = 0.0;
+    for (size_t b = 0; b < shapes.size(); ++b) {
+      const VolDev v = make_vol(vols[b], nullptr, shapes[b], 0, -1, nullptr, shapes[b].deep ? k : 1);
+      items += (double)groups * v.tiles;
+      planes += (double)groups * v.ntx * v.nty * vols[b].nz;
+    }
+    const double cost = tile_cost(items, planes / items, R, simds);
+    if (best_cost < 0.0 || cost < best_cost) {
+      best_cost = cost;
+      best = k;
+    }
+  }
+  return best;
+}
+
 // Work items a work group takes at a time: one per wave for the tiled
 // kernels, one for the pointwise kernels.
 int items_per_group(int kind, int nw) {
@@ -571,9 +641,9 @@ LaunchArgs make_args(const pifcm_ctx* ctx, const VolDev* vols_dev, const PairDev
   int acc = 0;
   for (int b = 0; b < nvol; ++b) {
     a.item_begin[b] = acc;
-    const int slots = a.use_1d ? vh[b].tiles1d : vh[b].tiles;
-    a.max_slots = std::max(a.max_slots, slots);
-    acc += groups * slots;
+    a.max_slots = std::max(a.max_slots, a.use_1d ? vh[b].tiles1d : vh[b].slots);
+    if (vh[b].zc > vh[b].sc) a.runs = 1;
+    acc += groups * (a.use_1d ? vh[b].tiles1d : vh[b].tiles);
   }
   a.item_begin[nvol] = acc;
   a.nitems = acc;
@@ -870,9 +940,9 @@ struct SolveWs {
 
 // Tile slots of a solve over planes [zbeg, zend) (the larger of the tiled and
 // pointwise decompositions).
-int solve_slots(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_params* p, int zbeg, int zend) {
-  const VolDev v = make_vol(*vol, nullptr, shape_for(ctx, p->C, p->m == 2.0f, *vol), zbeg, zend);
-  return std::max(v.tiles, v.tiles1d);
+int solve_slots(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_params* p, int kind, int zbeg, int zend) {
+  const VolDev v = make_vol(*vol, nullptr, shape_for(ctx, p->C, p->m == 2.0f, *vol, kind), zbeg, zend);
+  return std::max(v.slots, v.tiles1d);
 }
 
 // One IFCM solve on the context's stream in the workspace ws.  U_out
@@ -894,7 +964,7 @@ pifcm_status solve_run(pifcm_ctx* ctx, const SolveWs& ws, const pifcm_volume* vo
   const float* u0s[1] = {U_in};
   TRY(run_invariants(ctx, vol, 1, C, u0s, kind == kGather ? ws.invg : nullptr, &off0, ws.flags,
                      (int*)ws.stage));
-  const TileShape ts = shape_for(ctx, C, m2, *vol);
+  const TileShape ts = shape_for(ctx, C, m2, *vol, kind);
   const VolDev vh = make_vol(*vol, ws.invg, ts, zbeg, zend, kind == kRing2 ? ws.rinv : nullptr);
   PairDev pr{};
   pr.U0 = U_in || kind == kFcm ? U_in : ws.ubuf;
@@ -981,7 +1051,7 @@ pifcm_status solve_impl(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_par
   const size_t N = nvox(*vol);
   const size_t Np = (N + 63) / 64 * 64;
   if (is_ring(kind)) TRY(prepare_ring(ctx, p));
-  const int slots = solve_slots(ctx, vol, p, zbeg, zend);
+  const int slots = solve_slots(ctx, vol, p, kind, zbeg, zend);
   if (kind == kGather) TRY(ensure(ctx, ctx->invg, Np * sizeof(float), "iteration invariants"));
   if (kind == kRing2) TRY(ensure(ctx, ctx->rinv, Np * 4 * sizeof(float), "ring invariants"));
   TRY(ensure(ctx, ctx->flags, 64, "flags"));
@@ -1064,7 +1134,7 @@ pifcm_status ifcm_solve_noalloc(pifcm_ctx* ctx, const pifcm_volume* vol, const p
   const int C = p->C;
   const size_t N = nvox(*vol);
   const size_t Np = (N + 63) / 64 * 64;
-  const int slots = solve_slots(ctx, vol, p, 0, vol->nz);
+  const int slots = solve_slots(ctx, vol, p, kGather, 0, vol->nz);
   auto al = [](size_t b) { return (b + 255) / 256 * 256; };
   const size_t o_invg = 0;
   const size_t o_ubuf = o_invg + al(Np * sizeof(float));
@@ -1182,19 +1252,27 @@ pifcm_status swarm_core(pifcm_ctx* ctx, const pifcm_volume* vols, int32_t B, con
   std::vector<size_t> off;
   TRY(prepare_volumes(ctx, vols, B, C, U0_check, off, kind, p));
 
-  // Tile shape: one per launch (the batched kernel has one TY).
-  const TileShape ts0 = shape_for(ctx, C, m2, vols[0]);
+  // Tile shape (the waves per work group are those of the launch) and, in the
+  // batched launch, particles per work item and runs of planes per tile.
+  const TileShape ts0 = shape_for(ctx, C, m2, vols[0], kind);
+  const int pt = mode == PIFCM_SWARM_BATCHED ? pt_for(kind, C, P, ts0) : 1;
+  std::vector<TileShape> shapes(B);
+  for (int b = 0; b < B; ++b) {
+    shapes[b] = shape_for(ctx, C, m2, vols[b], kind);
+    shapes[b].nw = ts0.nw;
+  }
+  const int runs = mode == PIFCM_SWARM_BATCHED ? tile_runs(ctx, C, m2, vols, shapes, (P + pt - 1) / pt) : 1;
   std::vector<VolDev> vh(B);
   size_t ubytes = 0, slots = 0;
   std::vector<size_t> uoff(B), soff(B);
   for (int b = 0; b < B; ++b) {
-    TileShape ts = shape_for(ctx, C, m2, vols[b]);
-    ts.nw = ts0.nw;
-    vh[b] = make_vol(vols[b], nullptr, ts);
+    const TileShape& ts = shapes[b];
+    vh[b] = make_vol(vols[b], nullptr, ts, 0, -1, nullptr,
+                     ts.deep ? std::max(1, std::min(runs, deepest_zc(vols[b], C) / ts.zc)) : 1);
     uoff[b] = ubytes;
     ubytes += (size_t)P * 2 * ((nvox(vols[b]) * C + 63) / 64 * 64) * sizeof(float);
     soff[b] = slots;
-    slots += (size_t)P * std::max(vh[b].tiles, vh[b].tiles1d);
+    slots += (size_t)P * std::max(vh[b].slots, vh[b].tiles1d);
   }
   const size_t npairs = (size_t)B * P;
   // Work items are numbered in 32 bits (their memberships alone would
@@ -1222,7 +1300,7 @@ pifcm_status swarm_core(pifcm_ctx* ctx, const pifcm_volume* vols, int32_t B, con
     hv[b] = vh[b];
     const size_t Nb = nvox(vols[b]);
     const size_t ustride = (Nb * C + 63) / 64 * 64;
-    const int tb = std::max(vh[b].tiles, vh[b].tiles1d);
+    const int tb = std::max(vh[b].slots, vh[b].tiles1d);
     for (int q = 0; q < P; ++q) {
       const size_t k = (size_t)b * P + q;
       hs[k] = init_state(centres_pp + k * C, C, particles[2 * k], particles[2 * k + 1], p, nullptr);
@@ -1246,9 +1324,6 @@ pifcm_status swarm_core(pifcm_ctx* ctx, const pifcm_volume* vols, int32_t B, con
   if (is_ring(kind)) TRY(prepare_ring(ctx, p));
   const VolDev* vdev = (const VolDev*)ctx->tvol.p;
   const PairDev* pdev = (const PairDev*)ctx->tpair.p;
-  // Particles per work item of the batched launch (the per-pair launches of
-  // the plain mode hold one particle).
-  const int pt = mode == PIFCM_SWARM_BATCHED ? pt_for(kind, C, P, ts0) : 1;
   const int occ = occupancy_of(kind, C, ts0.nw, m2, true, pt);
   const int occe = occupancy_of(kind, C, ts0.nw, m2, false, pt);
   const int ipg = items_per_group(kind, ts0.nw);
@@ -1431,9 +1506,9 @@ pifcm_status ifcm_backward(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_
   std::vector<size_t> off;
   const float* u0s[1] = {U0};
   TRY(prepare_volumes(ctx, vol, 1, C, u0s, off, kind, p));
-  const TileShape ts = shape_for(ctx, C, m2, *vol);
+  const TileShape ts = shape_for(ctx, C, m2, *vol, kind);
   std::vector<VolDev> vh{make_vol(*vol, (const float*)ctx->invg.p, ts)};
-  const int slots = std::max(vh[0].tiles, vh[0].tiles1d);
+  const int slots = std::max(vh[0].slots, vh[0].tiles1d);
   // Workspace: forward ping-pong, checkpoints at t = S, 2S, ... <= K - 1,
   // the S - 1 recomputed states of a segment, two adjoint buffers, the
   // transpose sources, slots and small histories.
