@@ -68,7 +68,12 @@ constexpr int kNHalo = kNCell - 64;            // 44 halo cells, one per lane
 // RUNS: tiles may hold several runs of planes.  A launch without such tiles
 // takes the instance without the test after every plane (13.0 against 13.3 ms
 // on six ragged volumes x 64 particles).
-template <int C, bool M2, int NW, bool STEP, int PT, bool RUNS>
+// WJ: J of the input state is wanted (always by the objective-only pass; by a
+// step only under a stop rule or for a history: 27 of 730 VALU instructions
+// per three planes at C = 4, which the memory system hides; at C = 3, m = 2.5,
+// where u^m is two transcendentals, a step of 162x181x75 takes 35.5 instead of
+// 38.7 us).
+template <int C, bool M2, int NW, bool STEP, int PT, bool RUNS, bool WJ>
 __global__ __launch_bounds__(64 * NW) void k_ifcm_gather(const LaunchArgs a) {
   constexpr int CP = (C + 3) / 4 * 4;
   constexpr int CH = C - 1;  // clusters whose H is gathered
@@ -251,6 +256,8 @@ __global__ __launch_bounds__(64 * NW) void k_ifcm_gather(const LaunchArgs a) {
       if (pv && active) {
         rx = *at_lane(Xq, own_ofs);
         rg = *at_lane(Gq, own_ofs);
+        // The next plane waits for these two first: keep them in front.
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int k = 0; k < PT; ++k) {
           const gfloat* Uq = opaque_base(at_byte(Ub[k], pb * C));
@@ -319,27 +326,30 @@ __global__ __launch_bounds__(64 * NW) void k_ifcm_gather(const LaunchArgs a) {
       }
     }
 
+    // sum_j H_ij of a voxel: 1, or 0 in a volume of one voxel.
+    const float hsum = nx * ny * nz > 1 ? 1.f : 0.f;
     // Finalise voxel z of slot S; its own cell is in buffer bz:
     // eqs (5)/(7) ratios, (4), (1), (2), (3), per particle.
-    auto finalize = [&](int z, auto Sc, int bz) __attribute__((always_inline)) {
+    auto finalize = [&](int z, auto Sc, int bz, auto GENc) __attribute__((always_inline)) {
       constexpr int S = decltype(Sc)::value;
+      constexpr bool GEN = decltype(GENc)::value;
       // Computed by every lane (a lane outside the volume sees staged zeros
       // and finite distances); only its store and its sums are masked, so no
       // conditional block holds the arithmetic.
       const float xv = sx_at(bz, 0, 0);
-      const float iq = (z > 0 && z < nz - 1) ? invQ2 : ((z > 0 || z < nz - 1) ? invQ1 : invQ0);
+      // (an interior plane's voxel is never on the volume's last plane)
+      const float iq = z > 0 && (!GEN || z < nz - 1) ? invQ2 : (!GEN || z > 0 || z < nz - 1 ? invQ1 : invQ0);
       const float g = fabsf(gs[S]);
 #pragma unroll
       for (int k = 0; k < PT; ++k) {
         float uo[C];
-        su_at(bz, k, 0, 0, uo);
+        if constexpr (WJ) su_at(bz, k, 0, 0, uo);
         // a_j = 1 - lambda H_j - xi F_j with H_j = hn_j * g, F_j = fn_j * iq.
         const float lg = -lam[k] * g, xq = -xi[k] * iq;
         float sh = hn[S][k][0];
 #pragma unroll
         for (int j = 1; j < CH; ++j) sh += hn[S][k][j];
-        // Last cluster by sum_j H_ij = 1 (0 when the voxel has no neighbour).
-        const float hlast = g != 0.f ? fmaf(-g, sh, 1.f) : 0.f;
+        const float hlast = fmaf(-g, sh, hsum);  // last cluster by sum_j H_ij
         float d2[C];
         float Jv = 0.f;
 #pragma unroll
@@ -349,7 +359,7 @@ __global__ __launch_bounds__(64 * NW) void k_ifcm_gather(const LaunchArgs a) {
           const float av = fmaf(xq, fn[S][k][j], ah);  // eq (4) factor
           const float dd = xv - cj[k][j];
           d2[j] = fmaxf(dd * dd * av, kDFloor);
-          Jv = fmaf(pow_m<M2>(uo[j], a.m), d2[j], Jv);  // eq (1)
+          if constexpr (WJ) Jv = fmaf(pow_m<M2>(uo[j], a.m), d2[j], Jv);  // eq (1)
         }
         if constexpr (STEP) {
           // eq (2); a lane outside the volume gets zeros (scale 0), so its
@@ -366,7 +376,7 @@ __global__ __launch_bounds__(64 * NW) void k_ifcm_gather(const LaunchArgs a) {
             acc[k][j] = fmaf(w, xv, acc[k][j]);  // eq (3) numerator
             acc[k][C + j] += w;                   // eq (3) denominator
           }
-          acc[k][2 * C] += Jv;  // 0 for a lane outside: its staged memberships are 0
+          if constexpr (WJ) acc[k][2 * C] += Jv;  // 0 for a lane outside: its staged memberships are 0
         } else {
           acc[k][0] += Jv;
         }
@@ -497,7 +507,7 @@ __global__ __launch_bounds__(64 * NW) void k_ifcm_gather(const LaunchArgs a) {
         xs[SC] = xC;
         if (!GEN || p + 2 <= zhi) load_plane(p + 2, std::integral_constant<bool, !GEN>{});
       }
-      if (doA) finalize(p - 1, SAc, bprev);
+      if (doA) finalize(p - 1, SAc, bprev, GENc);
       // Keep the next plane's gathers after this plane's store.
       __builtin_amdgcn_sched_barrier(0);
     };
@@ -589,8 +599,10 @@ __global__ __launch_bounds__(64 * NW) void k_ifcm_gather(const LaunchArgs a) {
 // C = 4 fast path); elsewhere NW = 4 and PT = 1.
 template <int C, bool M2, int NW, int PT, bool RUNS>
 static hipError_t launch_gather_ctr(const LaunchArgs& a, int grid, bool step, hipStream_t s) {
-  if (step) hipLaunchKernelGGL((k_ifcm_gather<C, M2, NW, true, PT, RUNS>), dim3(grid), dim3(64 * NW), 0, s, a);
-  else hipLaunchKernelGGL((k_ifcm_gather<C, M2, NW, false, PT, RUNS>), dim3(grid), dim3(64 * NW), 0, s, a);
+  const dim3 g(grid), t(64 * NW);
+  if (!step) hipLaunchKernelGGL((k_ifcm_gather<C, M2, NW, false, PT, RUNS, true>), g, t, 0, s, a);
+  else if (a.want_j) hipLaunchKernelGGL((k_ifcm_gather<C, M2, NW, true, PT, RUNS, true>), g, t, 0, s, a);
+  else hipLaunchKernelGGL((k_ifcm_gather<C, M2, NW, true, PT, RUNS, false>), g, t, 0, s, a);
   return hipGetLastError();
 }
 
@@ -603,8 +615,8 @@ static hipError_t launch_gather_ct(const LaunchArgs& a, int grid, bool step, hip
 template <int C, bool M2, int NW, int PT>
 static int occ_gather_ct(bool step) {
   int n = 0;
-  const void* f = step ? reinterpret_cast<const void*>(&k_ifcm_gather<C, M2, NW, true, PT, false>)
-                       : reinterpret_cast<const void*>(&k_ifcm_gather<C, M2, NW, false, PT, false>);
+  const void* f = step ? reinterpret_cast<const void*>(&k_ifcm_gather<C, M2, NW, true, PT, false, true>)
+                       : reinterpret_cast<const void*>(&k_ifcm_gather<C, M2, NW, false, PT, false, true>);
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 64 * NW, 0) != hipSuccess) n = 1;
   return std::max(n, 1);
 }

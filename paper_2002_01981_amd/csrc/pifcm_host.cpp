@@ -1594,7 +1594,7 @@ pifcm_status ifcm_backward(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_
                         hipMemcpyHostToDevice, ctx->s));
   HIPCHK(hipMemcpyAsync(c_hist, pin + sizeof(SolveState) + sizeof(PairDev) + sizeof(VolDev),
                         C * sizeof(float), hipMemcpyHostToDevice, ctx->s));
-  LaunchArgs a = make_args(ctx, (const VolDev*)ctx->tvol.p, tp, vh, 1, 1, kind, p);
+  LaunchArgs a = make_args(ctx, (const VolDev*)ctx->tvol.p, tp, vh, 1, 1, kind, &pf);
   const int occ = occupancy_of(kind, C, ts.nw, m2, true);
   const int grid = grid_for(ctx, a.nitems, occ, items_per_group(kind, ts.nw));
   const int occe = occupancy_of(kind, C, ts.nw, m2, false);
@@ -1680,7 +1680,7 @@ pifcm_status ifcm_backward(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_
       for (int i = 1; i < len; ++i) {
         if (t0 != t0_last) {
           const LaunchArgs ar =
-              make_args(ctx, (const VolDev*)ctx->tvol.p, rs_pr + seg_r + (i - 1), vh, 1, 1, kind, p);
+              make_args(ctx, (const VolDev*)ctx->tvol.p, rs_pr + seg_r + (i - 1), vh, 1, 1, kind, &pf);
           HIPCHK(launch_step(C, ar, grid, ts.nw, m2, kind, true, ctx->s));
         }
         seg[i] = seg_state(i);
