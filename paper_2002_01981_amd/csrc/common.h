@@ -292,18 +292,22 @@ __device__ __forceinline__ void wave_sums(const T (&v)[NV], T (&out)[kSumRegs<NV
   }
 }
 
-// Wave owning a tile: its sums to slot `tile` of `slots`.
+// Wave owning a tile: its sums to slot `tile` of `slots`.  Lane r of a row
+// stores the row's sum of register r, so one store instruction writes them all.
+// The lane number is opaque: kept out of the loops this is called in, the
+// addresses derived from it would occupy registers there (170 -> 184 at C = 6).
 template <int NV>
 __device__ __forceinline__ void wave_tile_store(float* partials, int tile, int slots, const float (&acc)[NV]) {
   float sum[kSumRegs<NV>];
   wave_sums<float, NV>(acc, sum);
-  const int lane = threadIdx.x & 63;
-  gfloat* slot = as_global(partials) + tile;
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));
+  const int r = lane & 15;
+  float v = sum[0];
 #pragma unroll
-  for (int r = 0; r < kSumRegs<NV>; ++r) {
-    const int k = sum_index(r, lane >> 4);
-    if ((lane & 15) == 0 && k < NV) slot[(size_t)k * slots] = sum[r];
-  }
+  for (int q = 1; q < kSumRegs<NV>; ++q) v = r == q ? sum[q] : v;
+  const int k = sum_index(r, lane >> 4);
+  if (r < kSumRegs<NV> && k < NV) as_global(partials)[(size_t)(uint32_t)k * (uint32_t)slots + (uint32_t)tile] = v;
 }
 
 // Work group owning a tile: the sums of its waves, added in order through LDS.
@@ -353,6 +357,8 @@ __global__ __launch_bounds__(NT) void k_finalize(const LaunchArgs a) {
   const int t = ld_const(&st->iter) + 1;
   const float c_old = st->c[(t & 1) ^ 1][lane & (kMaxC - 1)];
   const double J1 = st->J_prev1;
+  // Without want_j a step leaves no J sums.
+  const int nv = STEP && !a.want_j ? 2 * C : NV;
   double d[NV];
 #pragma unroll
   for (int k = 0; k < NV; ++k) d[k] = 0.0;
@@ -366,7 +372,7 @@ __global__ __launch_bounds__(NT) void k_finalize(const LaunchArgs a) {
 #pragma unroll
     for (int u = 0; u < kU; ++u)
 #pragma unroll
-      for (int k = 0; k < NV; ++k) v[u][k] = parts[(size_t)k * slots + s + u * NT];
+      for (int k = 0; k < NV; ++k) v[u][k] = k < nv ? parts[(size_t)k * slots + s + u * NT] : 0.f;
 #pragma unroll
     for (int u = 0; u < kU; ++u)
 #pragma unroll
@@ -374,7 +380,7 @@ __global__ __launch_bounds__(NT) void k_finalize(const LaunchArgs a) {
   }
   for (; s < slots; s += NT) {
 #pragma unroll
-    for (int k = 0; k < NV; ++k) d[k] += (double)parts[(size_t)k * slots + s];
+    for (int k = 0; k < NV; ++k) d[k] += k < nv ? (double)parts[(size_t)k * slots + s] : 0.0;
   }
   double sum[kSumRegs<NV>];
   wave_sums<double, NV>(d, sum);

@@ -65,6 +65,14 @@ constexpr int kHX = kWX + 2, kHY = kWY + 2;    // staged plane with halo
 constexpr int kNCell = kHX * kHY;              // 108 cells
 constexpr int kNHalo = kNCell - 64;            // 44 halo cells, one per lane
 
+// The registers are held to what keeps gather_waves waves on a SIMD (some
+// instances come out a few above the step; C = 11: one wave 518 us, two, with
+// a few spilled registers, 387 us for 20 particles on 120x100x50).
+template <int C, int PT>
+constexpr int gather_waves() {
+  return PT > 1 ? 2 : C == 2 ? 5 : C == 3 ? 4 : C <= 6 ? 3 : C <= 12 ? 2 : 1;
+}
+
 // RUNS: tiles may hold several runs of planes.  A launch without such tiles
 // takes the instance without the test after every plane (13.0 against 13.3 ms
 // on six ragged volumes x 64 particles).
@@ -74,10 +82,10 @@ constexpr int kNHalo = kNCell - 64;            // 44 halo cells, one per lane
 // where u^m is two transcendentals, a step of 162x181x75 takes 35.5 instead of
 // 38.7 us).
 template <int C, bool M2, int NW, bool STEP, int PT, bool RUNS, bool WJ>
-__global__ __launch_bounds__(64 * NW) void k_ifcm_gather(const LaunchArgs a) {
+__global__ __launch_bounds__(64 * NW, (gather_waves<C, PT>())) void k_ifcm_gather(const LaunchArgs a) {
   constexpr int CP = (C + 3) / 4 * 4;
   constexpr int CH = C - 1;  // clusters whose H is gathered
-  constexpr int NV = STEP ? 2 * C + 1 : 1;
+  constexpr int NV = STEP ? 2 * C + (WJ ? 1 : 0) : 1;  // sums kept (without J its slot is not written)
 
   // Three plane buffers per wave: the plane being read, the one before it
   // (own cells of the voxel being finalised), and the one being staged; the
@@ -613,10 +621,12 @@ static hipError_t launch_gather_ct(const LaunchArgs& a, int grid, bool step, hip
 }
 
 template <int C, bool M2, int NW, int PT>
-static int occ_gather_ct(bool step) {
+static int occ_gather_ct(bool step, bool runs) {
   int n = 0;
-  const void* f = step ? reinterpret_cast<const void*>(&k_ifcm_gather<C, M2, NW, true, PT, false, true>)
-                       : reinterpret_cast<const void*>(&k_ifcm_gather<C, M2, NW, false, PT, false, true>);
+  const void* f = step ? (runs ? reinterpret_cast<const void*>(&k_ifcm_gather<C, M2, NW, true, PT, true, true>)
+                               : reinterpret_cast<const void*>(&k_ifcm_gather<C, M2, NW, true, PT, false, true>))
+                       : (runs ? reinterpret_cast<const void*>(&k_ifcm_gather<C, M2, NW, false, PT, true, true>)
+                               : reinterpret_cast<const void*>(&k_ifcm_gather<C, M2, NW, false, PT, false, true>));
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 64 * NW, 0) != hipSuccess) n = 1;
   return std::max(n, 1);
 }
@@ -627,8 +637,8 @@ static hipError_t launch_gather_m(const LaunchArgs& a, int grid, bool m2, bool s
 }
 
 template <int C, int NW, int PT>
-static int occ_gather_m(bool m2, bool step) {
-  return m2 ? occ_gather_ct<C, true, NW, PT>(step) : occ_gather_ct<C, false, NW, PT>(step);
+static int occ_gather_m(bool m2, bool step, bool runs) {
+  return m2 ? occ_gather_ct<C, true, NW, PT>(step, runs) : occ_gather_ct<C, false, NW, PT>(step, runs);
 }
 
 template <int C, bool ALL_NW>
@@ -657,24 +667,24 @@ static hipError_t launch_gather_one(const LaunchArgs& a, int grid, int nw, bool 
 }
 
 template <int C, bool ALL_NW>
-static int occ_gather_one(int nw, int pt, bool m2, bool step) {
+static int occ_gather_one(int nw, int pt, bool m2, bool step, bool runs) {
   if constexpr (ALL_NW) {
     if (pt == 2) {
       switch (nw) {
-        case 1: return occ_gather_m<C, 1, 2>(m2, step);
-        case 2: return occ_gather_m<C, 2, 2>(m2, step);
-        case 4: return occ_gather_m<C, 4, 2>(m2, step);
+        case 1: return occ_gather_m<C, 1, 2>(m2, step, runs);
+        case 2: return occ_gather_m<C, 2, 2>(m2, step, runs);
+        case 4: return occ_gather_m<C, 4, 2>(m2, step, runs);
         default: return 1;
       }
     }
     switch (nw) {
-      case 1: return occ_gather_m<C, 1, 1>(m2, step);
-      case 2: return occ_gather_m<C, 2, 1>(m2, step);
-      case 4: return occ_gather_m<C, 4, 1>(m2, step);
+      case 1: return occ_gather_m<C, 1, 1>(m2, step, runs);
+      case 2: return occ_gather_m<C, 2, 1>(m2, step, runs);
+      case 4: return occ_gather_m<C, 4, 1>(m2, step, runs);
       default: return 1;
     }
   } else {
-    return occ_gather_m<C, 4, 1>(m2, step);
+    return occ_gather_m<C, 4, 1>(m2, step, runs);
   }
 }
 
@@ -684,6 +694,8 @@ static int occ_gather_one(int nw, int pt, bool m2, bool step) {
                                 hipStream_t s) {                                           \
     return launch_gather_one<c, all_nw>(a, grid, nw, m2, step, s);                         \
   }                                                                                        \
-  int occ_gather_C##c(int nw, int pt, bool m2, bool step) { return occ_gather_one<c, all_nw>(nw, pt, m2, step); }
+  int occ_gather_C##c(int nw, int pt, bool m2, bool step, bool runs) {                     \
+    return occ_gather_one<c, all_nw>(nw, pt, m2, step, runs);                              \
+  }
 
 }  // namespace pifcm

@@ -39,7 +39,7 @@ struct GraphCache {
 struct TileShape {
   int nw = 4;   // wavefronts per work group of the fused step
   int zc = 0;   // planes per tile (0: the volume's default, default_zc)
-  int pt = 1;   // particles per work item of the batched fused step (C = 4: 1 or 2)
+  int pt = 0;   // particles per work item of the batched fused step (C = 4: 1 or 2; 0: particles_per_item)
   bool deep = false;  // zc is the default: a launch over many pairs may give a tile several runs of zc planes
 };
 
@@ -77,7 +77,7 @@ struct pifcm_ctx {
   double step_ms = 0.0;
   int64_t step_launches = 0;
   std::map<std::tuple<int, int, int, int, int>, TileShape> tuned;  // (C, m2, nx, ny, nz)
-  int occ_gather[kMaxC + 1][2] = {};  // resident work groups per CU of the fused step (4 waves)
+  int occ_gather[kMaxC + 1][2][2][2] = {};  // resident work groups per CU of the fused step (4 waves)
   char arch[64] = "unknown";  // device architecture (tuning cache key)
 };
 
@@ -234,22 +234,25 @@ bool ring2_params(const pifcm_params* p) {
 }
 bool is_ring(int kind) { return kind == kRing || kind == kRing2; }
 
-// The cost, in plane passes, of `items` tiles (of mean depth `depth`) of the
-// fused step on `resident` waves.  A tile costs its planes and about four
-// more (its two halo planes and the start of its walk); a plane pass takes
-// 2 + k units of time on a SIMD that holds k waves (lone-wave latency and
-// VALU issue: 0.75 + 0.33 k us at C = 4, m = 2; 0.8 + 0.44 k at C = 3, m = 2.5;
-// 1.2 + 0.6 k at C = 8, fitted over depths of 8 to 181 planes within 5 %), and
-// the tiles run in rounds of `resident`, the last one with fewer waves.
-double tile_cost(double items, double depth, double resident, double simds) {
-  const double full = std::floor(items / resident), rest = items - full * resident;
-  return (depth + 4.0) * (full * (2.0 + resident / simds) + (rest > 0.0 ? 2.0 + rest / simds : 0.0));
+// The cost of a launch of the fused step whose tiles hold `planes` planes in
+// all, the longest `longest`, on `resident` waves.  A tile costs its planes and
+// about four more (its two halo planes and the start of its walk).  A plane
+// pass takes 2 + k units of time on a SIMD that holds k waves: two for the
+// latency of a lone wave and one for VALU issue (0.75 + 0.33 k us at C = 4,
+// m = 2; 0.8 + 0.44 k at C = 3, m = 2.5; 1.2 + 0.6 k at C = 8, fitted over
+// depths of 8 to 181 planes within 5 %), so a launch costs its passes per SIMD
+// and twice the passes of its longest-working wave, where the tiles run in
+// rounds of `resident`.
+double launch_cost(double tiles, double planes, double longest, double resident, double simds) {
+  const double passes = planes + 4.0 * tiles, mean = passes / tiles;
+  return passes / simds + 2.0 * (std::ceil(tiles / resident) * mean + (longest + 4.0 - mean));
 }
 
-// Waves of the fused step the card keeps resident (4 waves per work group).
-double resident_waves(pifcm_ctx* ctx, int C, bool m2) {
-  int& occ = ctx->occ_gather[std::max(0, std::min(C, kMaxC))][m2 ? 1 : 0];
-  if (occ == 0) occ = std::max(1, gather_occupancy(C, 4, 1, m2, true));
+// Waves of the fused step the card keeps resident (4 waves per work group,
+// pt particles per item; runs: tiles of several runs of planes).
+double resident_waves(pifcm_ctx* ctx, int C, bool m2, int pt = 1, bool runs = false) {
+  int& occ = ctx->occ_gather[std::max(0, std::min(C, kMaxC))][m2 ? 1 : 0][pt - 1][runs ? 1 : 0];
+  if (occ == 0) occ = std::max(1, gather_occupancy(C, 4, pt, m2, true, runs));
   return 4.0 * occ * ctx->num_cu;
 }
 
@@ -257,7 +260,7 @@ double resident_waves(pifcm_ctx* ctx, int C, bool m2) {
 // the depth ceil(nz / k) that costs one pair's tiles least (the deeper one on a
 // tie).  It depends on the volume alone: tile sums are kept per run of that
 // many planes in every launch (VolDev::sc), so all launch modes give the same
-// bits; a launch over many pairs gives its tiles several runs (tile_runs).
+// bits; a launch over many pairs gives its tiles several runs (launch_depth).
 // One step of a lone pair: 181x217x181, C = 4: 46 planes, 82 us (23: 88 us,
 // 61: 91 us, 181: 190 us); 162x181x75, C = 3, m = 2.5: 11 planes, 38 us (38
 // planes, the least with a floor of 32: 50 us); 32x32x8: 1 plane, 10 us (8
@@ -270,7 +273,8 @@ int default_zc(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v) {
   for (int k = 1; k <= v.nz; ++k) {
     const int zc = (v.nz + k - 1) / k;
     if (k > 1 && zc == (v.nz + k - 2) / (k - 1)) continue;  // the depth of k - 1
-    const double cost = tile_cost(txy * ((v.nz + zc - 1) / zc), zc, R, simds);
+    const double nt = txy * ((v.nz + zc - 1) / zc);
+    const double cost = launch_cost(nt, nt * zc, zc, R, simds);
     if (best_cost < 0.0 || cost < best_cost) {
       best_cost = cost;
       best = zc;
@@ -437,47 +441,73 @@ int kind_of(const pifcm_params* p, bool zero_weights) {
   return ring_params(p) ? (ring2_params(p) ? kRing2 : kRing) : kGather;
 }
 
-int occupancy_of(int kind, int C, int nw, bool m2, bool step, int pt = 1) {
+int occupancy_of(int kind, int C, int nw, bool m2, bool step, int pt = 1, bool runs = false) {
   if (kind == kFcm) return fcm_x_occupancy(C, m2, step);
   if (kind == kFcmStore) return fcm_occupancy(C, m2, step);
   if (kind == kRing) return ring_occupancy(C, m2, step);
   if (kind == kRing2) return ring2_occupancy(C, m2, step);
-  return gather_occupancy(C, nw, pt, m2, step);
+  return gather_occupancy(C, nw, pt, m2, step, runs);
 }
 
-// Particles per work item a launch of `kind` over P particles uses: the
-// shape's pt for the fused step of a swarm at C = 4, else 1.
-int pt_for(int kind, int C, int P, const TileShape& ts) {
-  return (kind == kGather && C == 4 && P >= 2) ? std::max(1, std::min(ts.pt, 2)) : 1;
+// Runs of its default planes that a tile of volume b takes in a batched
+// launch whose tiles are to be about `depth` planes deep.
+int runs_at(const pifcm_volume& v, const TileShape& ts, int C, int depth) {
+  if (!ts.deep) return 1;
+  const int whole = (v.nz + ts.zc - 1) / ts.zc;
+  return std::max(1, std::min({(2 * depth + ts.zc) / (2 * ts.zc), whole, deepest_zc(v, C) / ts.zc}));
 }
 
-// Runs of a volume's default planes that a tile of a batched launch takes
-// (the same number for each volume, as far as its planes go): the cheapest by
-// tile_cost over all tiles of the launch, for `groups` particle groups per
-// volume.  A single pair takes one; with many pairs every round is full and
-// whole columns win (fewer tile starts and halo planes: six ragged volumes x
-// 64 particles, 13.3 ms per launch; 13.8 ms with a lone pair's depths).
-int tile_runs(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume* vols, const std::vector<TileShape>& shapes,
-              long groups) {
-  const double R = resident_waves(ctx, C, m2), simds = 4.0 * ctx->num_cu;
-  int best = 1, most = 1;
-  for (size_t b = 0; b < shapes.size(); ++b)
-    if (shapes[b].deep) most = std::max(most, (vols[b].nz + shapes[b].zc - 1) / shapes[b].zc);
+// Tile depth of a batched launch of P particles, pt per item, per volume: the
+// cheapest by launch_cost (each volume takes the nearest number of its default
+// runs, up to whole columns).  With many pairs every round is full and whole
+// columns win (fewer tile starts and halo planes: six ragged volumes x 64
+// particles, 13.3 ms per launch; 13.8 ms with a lone pair's depths).
+struct LaunchDepth {
+  int depth;
+  double rounds;  // of the launch's tiles on the resident waves
+};
+LaunchDepth launch_depth(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume* vols,
+                         const std::vector<TileShape>& shapes, int P, int pt) {
+  const double R = resident_waves(ctx, C, m2, pt, true), simds = 4.0 * ctx->num_cu;
+  const double groups = (P + pt - 1) / pt;
+  int deepest = 1;
+  for (size_t b = 0; b < shapes.size(); ++b) deepest = std::max(deepest, vols[b].nz);
+  LaunchDepth best{1, 0.0};
   double best_cost = -1.0;
-  for (int k = 1; k <= most; ++k) {
-    double items = 0.0, planes = 0.0;
+  for (int depth = 1;; depth = std::min(deepest, depth + std::max(1, depth / 16))) {
+    double tiles = 0.0, planes = 0.0, longest = 0.0;
     for (size_t b = 0; b < shapes.size(); ++b) {
-      const VolDev v = make_vol(vols[b], nullptr, shapes[b], 0, -1, nullptr, shapes[b].deep ? k : 1);
-      items += (double)groups * v.tiles;
-      planes += (double)groups * v.ntx * v.nty * vols[b].nz;
+      const pifcm_volume& v = vols[b];
+      const int zc = std::min(v.nz, shapes[b].zc * runs_at(v, shapes[b], C, depth));
+      const double n = groups * ((v.nx + kWaveTileX - 1) / kWaveTileX) * ((v.ny + kWaveTileY - 1) / kWaveTileY);
+      tiles += n * ((v.nz + zc - 1) / zc);
+      planes += n * v.nz;
+      longest = std::max(longest, (double)zc);
     }
-    const double cost = tile_cost(items, planes / items, R, simds);
+    const double cost = launch_cost(tiles, planes, longest, R, simds);
     if (best_cost < 0.0 || cost < best_cost) {
       best_cost = cost;
-      best = k;
+      best = LaunchDepth{depth, tiles / R};
     }
+    if (depth >= deepest) break;
   }
   return best;
+}
+
+// Particles per work item of a batched launch: what was chosen for its first
+// volume, else two where sharing the intensities pays.  That is at C = 4
+// without a stop rule (a stopped particle's partner would drag it along) from
+// four rounds of one-particle tiles on: such launches are HBM bound (181x217x181:
+// 20 particles 1517 us against 1368 us with two per item, six ragged volumes x
+// 64 13.2 against 12.2 ms); below, the memberships fit the last-level cache or
+// the two-particle tiles, half as many on two thirds of the wave slots, leave
+// waves idle (181x217x181: 4 particles 297 against 329 us, 60x128x128: 8
+// particles 75 against 92 us).
+int particles_per_item(pifcm_ctx* ctx, int kind, int C, bool m2, const pifcm_volume* vols,
+                       const std::vector<TileShape>& shapes, int P, float eps) {
+  if (kind != kGather || C != 4 || P < 2) return 1;
+  if (shapes[0].pt > 0) return std::min(shapes[0].pt, 2);
+  return eps == 0.f && launch_depth(ctx, C, m2, vols, shapes, P, 1).rounds >= 4.0 ? 2 : 1;
 }
 
 // Work items a work group takes at a time: one per wave for the tiled
@@ -1255,20 +1285,22 @@ pifcm_status swarm_core(pifcm_ctx* ctx, const pifcm_volume* vols, int32_t B, con
   // Tile shape (the waves per work group are those of the launch) and, in the
   // batched launch, particles per work item and runs of planes per tile.
   const TileShape ts0 = shape_for(ctx, C, m2, vols[0], kind);
-  const int pt = mode == PIFCM_SWARM_BATCHED ? pt_for(kind, C, P, ts0) : 1;
   std::vector<TileShape> shapes(B);
   for (int b = 0; b < B; ++b) {
     shapes[b] = shape_for(ctx, C, m2, vols[b], kind);
     shapes[b].nw = ts0.nw;
   }
-  const int runs = mode == PIFCM_SWARM_BATCHED ? tile_runs(ctx, C, m2, vols, shapes, (P + pt - 1) / pt) : 1;
+  int pt = 1, depth = 0;
+  if (mode == PIFCM_SWARM_BATCHED) {
+    pt = particles_per_item(ctx, kind, C, m2, vols, shapes, P, p->eps);
+    depth = launch_depth(ctx, C, m2, vols, shapes, P, pt).depth;
+  }
   std::vector<VolDev> vh(B);
   size_t ubytes = 0, slots = 0;
   std::vector<size_t> uoff(B), soff(B);
   for (int b = 0; b < B; ++b) {
     const TileShape& ts = shapes[b];
-    vh[b] = make_vol(vols[b], nullptr, ts, 0, -1, nullptr,
-                     ts.deep ? std::max(1, std::min(runs, deepest_zc(vols[b], C) / ts.zc)) : 1);
+    vh[b] = make_vol(vols[b], nullptr, ts, 0, -1, nullptr, depth > 0 ? runs_at(vols[b], ts, C, depth) : 1);
     uoff[b] = ubytes;
     ubytes += (size_t)P * 2 * ((nvox(vols[b]) * C + 63) / 64 * 64) * sizeof(float);
     soff[b] = slots;
@@ -1324,8 +1356,10 @@ pifcm_status swarm_core(pifcm_ctx* ctx, const pifcm_volume* vols, int32_t B, con
   if (is_ring(kind)) TRY(prepare_ring(ctx, p));
   const VolDev* vdev = (const VolDev*)ctx->tvol.p;
   const PairDev* pdev = (const PairDev*)ctx->tpair.p;
-  const int occ = occupancy_of(kind, C, ts0.nw, m2, true, pt);
-  const int occe = occupancy_of(kind, C, ts0.nw, m2, false, pt);
+  bool several = false;  // some tiles hold several runs of planes
+  for (int b = 0; b < B; ++b) several = several || vh[b].zc > vh[b].sc;
+  const int occ = occupancy_of(kind, C, ts0.nw, m2, true, pt, several);
+  const int occe = occupancy_of(kind, C, ts0.nw, m2, false, pt, several);
   const int ipg = items_per_group(kind, ts0.nw);
 
   int64_t launches = 0;

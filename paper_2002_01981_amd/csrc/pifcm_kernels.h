@@ -85,8 +85,9 @@ hipError_t launch_adjoint(int C, const AdjArgs& a, bool m2, bool eval, float* Ub
 // Slots of per-wave sums the adjoint's per-voxel kernel writes (upper bound).
 size_t adjoint_slots(int nx, int ny, int nz);
 
-// Resident work groups per CU of the gather / pointwise kernels.
-int gather_occupancy(int C, int ty, int pt, bool m2, bool step);
+// Resident work groups per CU of the gather / pointwise kernels (runs: the
+// instance whose tiles may hold several runs of planes).
+int gather_occupancy(int C, int ty, int pt, bool m2, bool step, bool runs);
 int fcm_occupancy(int C, bool m2, bool step);
 
 }  // namespace pifcm
