@@ -232,6 +232,13 @@ bool ring_params(const pifcm_params* p) { return p->V > 1 || (p->flags & PIFCM_S
 bool ring2_params(const pifcm_params* p) {
   return p->V == 2 && !(p->flags & PIFCM_SHELL_SQDIST) && p->C <= 4;
 }
+// Cells the neighbourhood of p reaches along an axis.
+int ring_reach(const pifcm_params* p) {
+  if (!(p->flags & PIFCM_SHELL_SQDIST)) return p->V;
+  int r = 0;
+  while ((r + 1) * (r + 1) <= p->V) ++r;
+  return r;
+}
 bool is_ring(int kind) { return kind == kRing || kind == kRing2; }
 
 // The cost of a launch of the fused step whose tiles hold `planes` planes in
@@ -365,6 +372,18 @@ int grid_for(pifcm_ctx* ctx, int nitems, int occupancy, int per_group = 1) {
   return (int)std::max<long>(8, g);
 }
 
+// Waits for the checks and reports what they found (flags: device, 2 ints;
+// stage: host, 2 ints).
+pifcm_status read_flags(pifcm_ctx* ctx, const int* flags, int* stage) {
+  HIPCHK(hipMemcpyAsync(stage, flags, 2 * sizeof(int), hipMemcpyDeviceToHost, ctx->s));
+  HIPCHK(hipStreamSynchronize(ctx->s));
+  if (stage[0]) return fail(ctx, PIFCM_E_NONFINITE, "a volume holds a NaN or Inf intensity");
+  if (stage[1])
+    return fail(ctx, PIFCM_E_INVALID,
+                "initial memberships must be finite, in [0, 1] and sum to 1 (+-1e-4) per voxel");
+  return PIFCM_OK;
+}
+
 // g_inv of `nv` volumes into invg (volume b at invg + invg_off[b]; invg NULL:
 // not needed), the intensity check, and the row check of caller U0 pointers
 // (optional), with flags (device, 2 ints) and stage (host, 2 ints) as
@@ -375,18 +394,24 @@ pifcm_status run_invariants(pifcm_ctx* ctx, const pifcm_volume* vols, int nv, in
   HIPCHK(hipMemsetAsync(flags, 0, 2 * sizeof(int), ctx->s));
   for (int b = 0; b < nv; ++b) {
     if (invg)
-      HIPCHK(launch_invariants(vols[b].x, invg + invg_off[b], vols[b].nx, vols[b].ny, vols[b].nz, flags,
-                               ctx->s));
+      HIPCHK(launch_invariants(vols[b].x, invg + invg_off[b], vols[b].nx, vols[b].ny, vols[b].nz, 0, vols[b].nz,
+                               flags, ctx->s));
     else HIPCHK(launch_check_finite(vols[b].x, nvox(vols[b]), flags, ctx->s));
     if (U0s && U0s[b]) HIPCHK(launch_check_rows(U0s[b], nvox(vols[b]), C, flags + 1, ctx->s));
   }
-  HIPCHK(hipMemcpyAsync(stage, flags, 2 * sizeof(int), hipMemcpyDeviceToHost, ctx->s));
-  HIPCHK(hipStreamSynchronize(ctx->s));
-  if (stage[0]) return fail(ctx, PIFCM_E_NONFINITE, "a volume holds a NaN or Inf intensity");
-  if (stage[1])
-    return fail(ctx, PIFCM_E_INVALID,
-                "initial memberships must be finite, in [0, 1] and sum to 1 (+-1e-4) per voxel");
-  return PIFCM_OK;
+  return read_flags(ctx, flags, stage);
+}
+
+// The same for a slab [zbeg, zend) of one volume: g_inv of its planes only
+// (the intensity check covers the volume), and the row check together with
+// the copy of U_in to U_out and its labels (optional).
+pifcm_status run_context(pifcm_ctx* ctx, const pifcm_volume* v, int zbeg, int zend, int C, const float* U_in,
+                         float* U_out, uint8_t* labels, float* invg, int* flags, int* stage) {
+  HIPCHK(hipMemsetAsync(flags, 0, 2 * sizeof(int), ctx->s));
+  HIPCHK(launch_check_finite(v->x, nvox(*v), flags, ctx->s));
+  if (invg) HIPCHK(launch_invariants(v->x, invg, v->nx, v->ny, v->nz, zbeg, zend, flags, ctx->s));
+  HIPCHK(launch_context(U_in, nvox(*v), C, U_out, labels, flags + 1, ctx->s));
+  return read_flags(ctx, flags, stage);
 }
 
 // Set up the invariants a launch of `kind` (or the adjoint) reads, of `nv`
@@ -527,11 +552,7 @@ pifcm_status prepare_ring(pifcm_ctx* ctx, const pifcm_params* p) {
   if (ctx->ring_tab.p && ctx->ring_key[0] == p->V && ctx->ring_key[1] == fl && ctx->ring_key[2] == hb)
     return PIFCM_OK;
   const bool sq = fl & PIFCM_SHELL_SQDIST;
-  int reach = p->V;
-  if (sq) {
-    reach = 0;
-    while ((reach + 1) * (reach + 1) <= p->V) ++reach;
-  }
+  const int reach = ring_reach(p);
   std::vector<RingOff> offs;
   for (int r = 1; r <= p->V; ++r)
     for (int dz = -reach; dz <= reach; ++dz)
@@ -992,8 +1013,9 @@ pifcm_status solve_run(pifcm_ctx* ctx, const SolveWs& ws, const pifcm_volume* vo
                                    (p->flags & PIFCM_Q2_SQDIST) ? 1 : 0, ctx->s));
   const size_t off0 = 0;
   const float* u0s[1] = {U_in};
-  TRY(run_invariants(ctx, vol, 1, C, u0s, kind == kGather ? ws.invg : nullptr, &off0, ws.flags,
-                     (int*)ws.stage));
+  float* const invg = kind == kGather ? ws.invg : nullptr;
+  if (slab) TRY(run_context(ctx, vol, zbeg, zend, C, U_in, U_out, labels_out, invg, ws.flags, (int*)ws.stage));
+  else TRY(run_invariants(ctx, vol, 1, C, u0s, invg, &off0, ws.flags, (int*)ws.stage));
   const TileShape ts = shape_for(ctx, C, m2, *vol, kind);
   const VolDev vh = make_vol(*vol, ws.invg, ts, zbeg, zend, kind == kRing2 ? ws.rinv : nullptr);
   PairDev pr{};
@@ -1018,11 +1040,14 @@ pifcm_status solve_run(pifcm_ctx* ctx, const SolveWs& ws, const pifcm_volume* vo
   HIPCHK(hipMemcpyAsync(ws.tvol, pin + sizeof(SolveState) + sizeof(PairDev), sizeof(VolDev),
                         hipMemcpyHostToDevice, ctx->s));
   if (!U_in && kind != kFcm) HIPCHK(launch_init_u(C, vol->x, N, ws.st, p->m, m2, ws.ubuf, ctx->s));
-  if (slab) {
-    // Planes outside the slab keep U_in in both iteration buffers.
-    HIPCHK(hipMemcpyAsync(U_out, U_in, N * C * sizeof(float), hipMemcpyDeviceToDevice, ctx->s));
-    if (kind != kFcm)
-      HIPCHK(hipMemcpyAsync(ws.ubuf, U_in, N * C * sizeof(float), hipMemcpyDeviceToDevice, ctx->s));
+  // Rows of the planes iterated.
+  const size_t plane = (size_t)vol->nx * vol->ny, row0 = (size_t)zbeg * plane, rows = (size_t)(zend - zbeg) * plane;
+  if (slab && kind != kFcm) {
+    // U_out holds U_in already; the other iteration buffer needs it as far as
+    // the neighbourhood reaches beyond the slab.
+    const int reach = ring_reach(p), z0 = std::max(0, zbeg - reach), z1 = std::min(vol->nz, zend + reach);
+    HIPCHK(hipMemcpyAsync(ws.ubuf + z0 * plane * C, U_in + z0 * plane * C, (z1 - z0) * plane * C * sizeof(float),
+                          hipMemcpyDeviceToDevice, ctx->s));
   }
 
   LaunchArgs a = make_args(ctx, ws.tvol, ws.tpair, &vh, 1, 1, kind, p);
@@ -1054,8 +1079,11 @@ pifcm_status solve_run(pifcm_ctx* ctx, const SolveWs& ws, const pifcm_volume* vo
   const int T = hst->iter;
   TRY(timing_collect(ctx, t));
   const float* Ufin = kind == kFcm ? U_out : u_state_of(pr, T);
-  if (labels_out) HIPCHK(launch_labels(Ufin, N, C, labels_out, ctx->s));
-  if (Ufin != U_out) HIPCHK(hipMemcpyAsync(U_out, Ufin, N * C * sizeof(float), hipMemcpyDeviceToDevice, ctx->s));
+  if (labels_out) HIPCHK(launch_labels(Ufin + row0 * C, rows, C, labels_out + row0, ctx->s));
+  // (a slab whose iteration count is 0 has its state in U_in)
+  if (Ufin != U_out)
+    HIPCHK(hipMemcpyAsync(U_out + row0 * C, Ufin + row0 * C, rows * C * sizeof(float), hipMemcpyDeviceToDevice,
+                          ctx->s));
   double* jh = ws.jh_stage ? ws.jh_stage : J_hist_out;
   if (J_hist_out && T > 0)
     HIPCHK(hipMemcpyAsync(jh, ws.jhist, (size_t)T * sizeof(double), hipMemcpyDeviceToHost, ctx->s));

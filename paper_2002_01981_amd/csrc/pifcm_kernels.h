@@ -45,10 +45,14 @@ hipError_t launch_ring(int C, const LaunchArgs& a, int grid, bool m2, bool step,
 int ring_occupancy(int C, bool m2, bool step);
 hipError_t launch_init_u(int C, const float* x, size_t N, const SolveState* st, float m, bool m2,
                          float* U, hipStream_t s);
-hipError_t launch_invariants(const float* x, float* invg, int nx, int ny, int nz, int* flag,
-                             hipStream_t s);
+// g_inv of the planes [zbeg, zend) and their intensity check.
+hipError_t launch_invariants(const float* x, float* invg, int nx, int ny, int nz, int zbeg, int zend,
+                             int* flag, hipStream_t s);
 hipError_t launch_check_finite(const float* x, size_t n, int* flag, hipStream_t s);
 hipError_t launch_check_rows(const float* U, size_t N, int C, int* flag, hipStream_t s);
+// Row check of U, its copy into out and (labels not NULL) its labels.
+hipError_t launch_context(const float* U, size_t N, int C, float* out, uint8_t* labels, int* flag,
+                          hipStream_t s);
 hipError_t launch_labels(const float* U, size_t N, int C, uint8_t* out, hipStream_t s);
 // counts (device, C * K + 1 entries, zeroed by the caller) += confusion of
 // labels against truth; the last entry counts out-of-range pairs.

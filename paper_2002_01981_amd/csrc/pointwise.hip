@@ -271,15 +271,15 @@ __device__ __forceinline__ float from_right_lane(float v) {
 }
 
 __global__ __launch_bounds__(256) void k_invariants(const float* __restrict__ x, float* __restrict__ invg,
-                                                    int nx, int ny, int nz, int zc, int nitems,
-                                                    int* __restrict__ flag) {
+                                                    int nx, int ny, int nz, int zbeg, int zend, int zc,
+                                                    int nitems, int* __restrict__ flag) {
   constexpr int R = kInvRows;
   const int lane = threadIdx.x & 63;
   const int item = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
   if (item >= nitems) return;
   const int ntx = (nx + kInvCols - 1) / kInvCols, nty = (ny + R - 1) / R;
   const int gx = (item % ntx) * kInvCols + lane - 1, y0 = (item / ntx) % nty * R;
-  const int zlo = item / ntx / nty * zc, zhi = min(zlo + zc, nz);
+  const int zlo = zbeg + item / ntx / nty * zc, zhi = min(zlo + zc, zend);
   const bool own = lane >= 1 && lane <= kInvCols && gx < nx;
   const int cx = min(max(gx, 0), nx - 1);
   // Weights (0 or 1) of the cells left of, at and right of the lane's column,
@@ -416,6 +416,32 @@ __global__ __launch_bounds__(256) void k_check_finite(const float* __restrict__ 
 }
 
 // Rows of a caller's U must be memberships: finite, in [0, 1], sum 1 +- 1e-4.
+template <int C>
+__device__ __forceinline__ bool row_ok(const float (&u)[C]) {
+  float s = 0.f;
+  bool ok = true;
+#pragma unroll
+  for (int j = 0; j < C; ++j) {
+    ok = ok && isfinite(u[j]) && u[j] >= 0.f && u[j] <= 1.f + 1e-6f;
+    s += u[j];
+  }
+  return ok && !(fabsf(s - 1.f) > 1e-4f);
+}
+// argmax_j u_j, ties to the lowest j.
+template <int C>
+__device__ __forceinline__ uint8_t row_label(const float (&u)[C]) {
+  int best = 0;
+  float bv = u[0];
+#pragma unroll
+  for (int j = 1; j < C; ++j) {
+    if (u[j] > bv) {
+      bv = u[j];
+      best = j;
+    }
+  }
+  return (uint8_t)best;
+}
+
 // One row per thread, read as wide as its alignment allows.  HBM bound: 7.1 M
 // rows of 4 in 19 us (5.9 TB/s), 4.1 M rows of 8 in 25 us; a loop over C
 // known at run time, a dword at a time, took 39 and 72 us.
@@ -428,20 +454,12 @@ __global__ __launch_bounds__(256) void k_check_rows(const float* __restrict__ U,
        i += (size_t)gridDim.x * blockDim.x) {
     float u[C];
     load_row<C>(as_global(U) + i * C, u);
-    float s = 0.f;
-    bool ok = true;
-#pragma unroll
-    for (int j = 0; j < C; ++j) {
-      ok = ok && isfinite(u[j]) && u[j] >= 0.f && u[j] <= 1.f + 1e-6f;
-      s += u[j];
-    }
-    bad = bad || !ok || fabsf(s - 1.f) > 1e-4f;
+    bad = bad || !row_ok<C>(u);
   }
   if (bad) atomicOr(flag, 1);
 }
 
-// Labels: argmax_j u_ij, ties to the lowest j (7.1 M rows of 4 in 30 us, 41 us
-// with a run-time C).
+// Labels (7.1 M rows of 4 in 30 us, 41 us with a run-time C).
 template <int C>
 __global__ __launch_bounds__(256) void k_labels(const float* __restrict__ U, size_t N,
                                                 uint8_t* __restrict__ out) {
@@ -450,17 +468,28 @@ __global__ __launch_bounds__(256) void k_labels(const float* __restrict__ U, siz
        i += (size_t)gridDim.x * blockDim.x) {
     float u[C];
     load_row<C>(as_global(U) + i * C, u);
-    int best = 0;
-    float bv = u[0];
-#pragma unroll
-    for (int j = 1; j < C; ++j) {
-      if (u[j] > bv) {
-        bv = u[j];
-        best = j;
-      }
-    }
-    out[i] = (uint8_t)best;
+    out[i] = row_label<C>(u);
   }
+}
+
+// The context of a slab solve in one pass over the caller's memberships: the
+// row check, the copy into the output and (labels not NULL) the labels; the
+// slab's own planes are written again by the solve.  7.1 M rows of 4: 35 us,
+// the bytes of the copy alone, instead of 19 + 45 + 30 us in three passes.
+template <int C>
+__global__ __launch_bounds__(256) void k_context(const float* __restrict__ U, size_t N, float* __restrict__ out,
+                                                 uint8_t* __restrict__ labels, int* __restrict__ flag) {
+  bool bad = false;
+#pragma unroll 2
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < N;
+       i += (size_t)gridDim.x * blockDim.x) {
+    float u[C];
+    load_row<C>(as_global(U) + i * C, u);
+    bad = bad || !row_ok<C>(u);
+    store_row<C>(as_global(out) + i * C, u);
+    if (labels) labels[i] = row_label<C>(u);
+  }
+  if (bad) atomicOr(flag, 1);
 }
 
 // Confusion counts of labels (0..C-1) against reference classes (0..K-1):
@@ -700,17 +729,18 @@ hipError_t launch_init_u(int C, const float* x, size_t N, const SolveState* st, 
 
 static int small_grid(size_t n) { return (int)std::max<size_t>(1, std::min<size_t>((n + 255) / 256, 65536)); }
 
-hipError_t launch_invariants(const float* x, float* invg, int nx, int ny, int nz, int* flag,
-                             hipStream_t s) {
+hipError_t launch_invariants(const float* x, float* invg, int nx, int ny, int nz, int zbeg, int zend,
+                             int* flag, hipStream_t s) {
   // Runs of 16 planes (two more are read for their ends), shorter while the
-  // volume gives fewer than 3000 waves: three per SIMD of the card.
+  // planes give fewer than 3000 waves: three per SIMD of the card.
   const long txy = (long)((nx + kInvCols - 1) / kInvCols) * ((ny + kInvRows - 1) / kInvRows);
+  const int np = zend - zbeg;
   int zc = 16;
-  while (zc > 2 && txy * ((nz + zc - 1) / zc) < 3000) zc /= 2;
-  const long items = txy * ((nz + zc - 1) / zc);
+  while (zc > 2 && txy * ((np + zc - 1) / zc) < 3000) zc /= 2;
+  const long items = txy * ((np + zc - 1) / zc);
   if (items > 0x7fffffffL - 4) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_invariants, dim3((unsigned)((items + 3) / 4)), dim3(256), 0, s, x, invg, nx, ny, nz, zc,
-                     (int)items, flag);
+  hipLaunchKernelGGL(k_invariants, dim3((unsigned)((items + 3) / 4)), dim3(256), 0, s, x, invg, nx, ny, nz, zbeg,
+                     zend, zc, (int)items, flag);
   return hipGetLastError();
 }
 
@@ -753,6 +783,24 @@ hipError_t launch_labels(const float* U, size_t N, int C, uint8_t* out, hipStrea
   switch (C) {
 #define CASE(c) \
   case c: return launch_labels_c<c>(U, N, out, s);
+    PIFCM_FOR_EACH_C(CASE)
+#undef CASE
+    default: return hipErrorInvalidValue;
+  }
+}
+
+template <int C>
+static hipError_t launch_context_c(const float* U, size_t N, float* out, uint8_t* labels, int* flag,
+                                   hipStream_t s) {
+  hipLaunchKernelGGL((k_context<C>), dim3(row_grid(N)), dim3(256), 0, s, U, N, out, labels, flag);
+  return hipGetLastError();
+}
+
+hipError_t launch_context(const float* U, size_t N, int C, float* out, uint8_t* labels, int* flag,
+                          hipStream_t s) {
+  switch (C) {
+#define CASE(c) \
+  case c: return launch_context_c<c>(U, N, out, labels, flag, s);
     PIFCM_FOR_EACH_C(CASE)
 #undef CASE
     default: return hipErrorInvalidValue;
