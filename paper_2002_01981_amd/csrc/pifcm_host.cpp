@@ -45,7 +45,7 @@ struct TileShape {
 
 constexpr int kChunk = 8;            // iterations between stop-flag reads
 // Host staging of one solve: its state, pair and volume records.
-constexpr size_t kStageBytes = (sizeof(SolveState) + sizeof(PairDev) + sizeof(VolDev) + 64 + 255) / 256 * 256;
+constexpr size_t kStageBytes = (64 + sizeof(SolveState) + sizeof(PairDev) + sizeof(VolDev) + 64 + 255) / 256 * 256;
 constexpr float kMaxWeight = 1000.f; // |lambda|, |xi| accepted
 constexpr int kMaxPairs = 65536;
 
@@ -55,7 +55,7 @@ struct pifcm_ctx {
   int device = 0;
   hipStream_t user = nullptr;
   hipStream_t s = nullptr;
-  hipEvent_t ev_in = nullptr, ev_out = nullptr;
+  hipEvent_t ev_in = nullptr, ev_out = nullptr, ev_norm = nullptr;
   std::string err;
   int num_cu = 256;
   DevBuf invg, rinv, ubuf, partials, states, jhist, tvol, tpair, flags;
@@ -65,6 +65,11 @@ struct pifcm_ctx {
   DevBuf conf;                                         // pifcm_confusion counts
   DevBuf pso_state;                                    // pifcm_pso_interleaved states
   DevBuf work;                                         // fused step's item counters (16 ints)
+  bool work_zero = true;                               // ... are zero (every launch leaves them so)
+  int norm_slot = 0;                                   // pifcm_normalize's slot of the next call
+  bool norm_clean = false;                             // ... has been preset
+  DevBuf norm;                                         // pifcm_normalize's two slots
+  int* norm_seen = nullptr;                            // pinned: a value was not finite
   int ring_n = 0;                                      // offsets in ring_tab
   int ring_gen = 0;                                    // rebuilds of ring_tab
   int ring_key[3] = {0, -1, 0};                        // (V, flags, bits of h) of ring_tab
@@ -89,7 +94,11 @@ pifcm_status fail(pifcm_ctx* ctx, pifcm_status st, const char* fmt, ...) {
   va_start(ap, fmt);
   vsnprintf(buf, sizeof buf, fmt, ap);
   va_end(ap);
-  if (ctx) ctx->err = buf;
+  if (ctx) {
+    ctx->err = buf;
+    // A call that a HIP error cut short may leave these in any state.
+    if (st == PIFCM_E_HIP) ctx->work_zero = ctx->norm_clean = false;
+  }
   return st;
 }
 
@@ -145,11 +154,15 @@ pifcm_status begin(pifcm_ctx* ctx) {
   HIPCHK(hipSetDevice(ctx->device));
   HIPCHK(hipEventRecord(ctx->ev_in, ctx->user));
   HIPCHK(hipStreamWaitEvent(ctx->s, ctx->ev_in, 0));
-  // The fused step's item counters start every call at zero (each launch
-  // also leaves them at zero).
-  HIPCHK(hipMemsetAsync(ctx->work.p, 0, 16 * sizeof(int32_t), ctx->s));
+  if (!ctx->work_zero) {
+    HIPCHK(hipMemsetAsync(ctx->work.p, 0, 16 * sizeof(int32_t), ctx->s));
+    ctx->work_zero = true;
+  }
   return PIFCM_OK;
 }
+
+// Order the user's stream after the work queued so far (a call that has waited
+// for its work needs none of it).
 
 pifcm_status finish(pifcm_ctx* ctx) {
   HIPCHK(hipEventRecord(ctx->ev_out, ctx->s));
@@ -372,26 +385,47 @@ int grid_for(pifcm_ctx* ctx, int nitems, int occupancy, int per_group = 1) {
   return (int)std::max<long>(8, g);
 }
 
-// Waits for the checks and reports what they found (flags: device, 2 ints;
-// stage: host, 2 ints).
-pifcm_status read_flags(pifcm_ctx* ctx, const int* flags, int* stage) {
-  HIPCHK(hipMemcpyAsync(stage, flags, 2 * sizeof(int), hipMemcpyDeviceToHost, ctx->s));
-  HIPCHK(hipStreamSynchronize(ctx->s));
-  if (stage[0]) return fail(ctx, PIFCM_E_NONFINITE, "a volume holds a NaN or Inf intensity");
-  if (stage[1])
+// Control block of a solve or swarm in device memory: the check flags, the
+// solve states, the pair records and the volume records, laid out together so
+// that one copy uploads them all and one reads flags and states back.
+constexpr size_t kFlagBytes = 64;  // two ints: non-finite intensity, bad membership row
+size_t control_bytes(size_t npairs, size_t nvol) {
+  return kFlagBytes + npairs * (sizeof(SolveState) + sizeof(PairDev)) + nvol * sizeof(VolDev);
+}
+struct Control {
+  char* p;
+  size_t npairs;
+  int* flags() const { return (int*)p; }
+  SolveState* st() const { return (SolveState*)(p + kFlagBytes); }
+  PairDev* pairs() const { return (PairDev*)(st() + npairs); }
+  VolDev* vols() const { return (VolDev*)(pairs() + npairs); }
+  size_t readback() const { return kFlagBytes + npairs * sizeof(SolveState); }
+};
+
+// What the checks left in the (host copy of the) flags.
+pifcm_status check_flags(pifcm_ctx* ctx, const int* flags) {
+  if (flags[0]) return fail(ctx, PIFCM_E_NONFINITE, "a volume holds a NaN or Inf intensity");
+  if (flags[1])
     return fail(ctx, PIFCM_E_INVALID,
                 "initial memberships must be finite, in [0, 1] and sum to 1 (+-1e-4) per voxel");
   return PIFCM_OK;
 }
+// The checks run on the device in front of the iterations, and a call reads
+// their flags with its results.  Only before a long run (in voxel iterations,
+// some milliseconds) does it wait for them, so that bad input is refused at
+// once; the wait costs a short call a tenth of its time.
+constexpr double kLongRun = 5e7;
+pifcm_status wait_flags(pifcm_ctx* ctx, const Control& dev, const Control& host) {
+  HIPCHK(hipMemcpyAsync(host.p, dev.p, kFlagBytes, hipMemcpyDeviceToHost, ctx->s));
+  HIPCHK(hipStreamSynchronize(ctx->s));
+  return check_flags(ctx, host.flags());
+}
 
 // g_inv of `nv` volumes into invg (volume b at invg + invg_off[b]; invg NULL:
 // not needed), the intensity check, and the row check of caller U0 pointers
-// (optional), with flags (device, 2 ints) and stage (host, 2 ints) as
-// workspace.
+// (optional), into flags (device, 2 zeroed ints).
 pifcm_status run_invariants(pifcm_ctx* ctx, const pifcm_volume* vols, int nv, int C,
-                            const float* const* U0s, float* invg, const size_t* invg_off, int* flags,
-                            int* stage) {
-  HIPCHK(hipMemsetAsync(flags, 0, 2 * sizeof(int), ctx->s));
+                            const float* const* U0s, float* invg, const size_t* invg_off, int* flags) {
   for (int b = 0; b < nv; ++b) {
     if (invg)
       HIPCHK(launch_invariants(vols[b].x, invg + invg_off[b], vols[b].nx, vols[b].ny, vols[b].nz, 0, vols[b].nz,
@@ -399,48 +433,49 @@ pifcm_status run_invariants(pifcm_ctx* ctx, const pifcm_volume* vols, int nv, in
     else HIPCHK(launch_check_finite(vols[b].x, nvox(vols[b]), flags, ctx->s));
     if (U0s && U0s[b]) HIPCHK(launch_check_rows(U0s[b], nvox(vols[b]), C, flags + 1, ctx->s));
   }
-  return read_flags(ctx, flags, stage);
+  return PIFCM_OK;
 }
 
 // The same for a slab [zbeg, zend) of one volume: g_inv of its planes only
 // (the intensity check covers the volume), and the row check together with
 // the copy of U_in to U_out and its labels (optional).
 pifcm_status run_context(pifcm_ctx* ctx, const pifcm_volume* v, int zbeg, int zend, int C, const float* U_in,
-                         float* U_out, uint8_t* labels, float* invg, int* flags, int* stage) {
-  HIPCHK(hipMemsetAsync(flags, 0, 2 * sizeof(int), ctx->s));
+                         float* U_out, uint8_t* labels, float* invg, int* flags) {
   HIPCHK(launch_check_finite(v->x, nvox(*v), flags, ctx->s));
   if (invg) HIPCHK(launch_invariants(v->x, invg, v->nx, v->ny, v->nz, zbeg, zend, flags, ctx->s));
   HIPCHK(launch_context(U_in, nvox(*v), C, U_out, labels, flags + 1, ctx->s));
-  return read_flags(ctx, flags, stage);
+  return PIFCM_OK;
 }
 
-// Set up the invariants a launch of `kind` (or the adjoint) reads, of `nv`
-// volumes concatenated in ctx->invg or ctx->rinv, and check intensities;
-// optionally check rows of caller U0 pointers.
-pifcm_status prepare_volumes(pifcm_ctx* ctx, const pifcm_volume* vols, int nv, int C,
-                             const float* const* U0s, std::vector<size_t>& invg_off, int kind,
-                             const pifcm_params* p) {
+// Space for the invariants a launch of `kind` (or the adjoint) reads, of `nv`
+// volumes concatenated in ctx->invg or ctx->rinv.
+bool needs_invg(int kind) { return kind == kGather || kind == kFcmStore; }
+pifcm_status ensure_invariants(pifcm_ctx* ctx, const pifcm_volume* vols, int nv, std::vector<size_t>& invg_off,
+                               int kind) {
   size_t total = 0;
   invg_off.resize(nv);
   for (int b = 0; b < nv; ++b) {
     invg_off[b] = total;
     total += (nvox(vols[b]) + 63) / 64 * 64;
   }
-  const bool need_g = kind == kGather || kind == kFcmStore;
-  if (need_g) TRY(ensure(ctx, ctx->invg, total * sizeof(float), "iteration invariants"));
-  if (kind == kRing2) {
-    // Per-ring invariants of the fused two-ring kernel (4 floats per voxel,
-    // at 4 x the offsets of g_inv).
-    TRY(ensure(ctx, ctx->rinv, total * 4 * sizeof(float), "ring invariants"));
+  if (needs_invg(kind)) TRY(ensure(ctx, ctx->invg, total * sizeof(float), "iteration invariants"));
+  // (4 floats per voxel, at 4 x the offsets of g_inv)
+  if (kind == kRing2) TRY(ensure(ctx, ctx->rinv, total * 4 * sizeof(float), "ring invariants"));
+  return PIFCM_OK;
+}
+
+// Those invariants, the intensity check and (optional) the row check of
+// caller U0 pointers, into flags (device, 2 zeroed ints).
+pifcm_status prepare_volumes(pifcm_ctx* ctx, const pifcm_volume* vols, int nv, int C,
+                             const float* const* U0s, const std::vector<size_t>& invg_off, int kind,
+                             const pifcm_params* p, int* flags) {
+  if (kind == kRing2)
     for (int b = 0; b < nv; ++b)
       HIPCHK(launch_ring2_invariants(vols[b].x, (float*)ctx->rinv.p + 4 * invg_off[b], vols[b].nx,
                                      vols[b].ny, vols[b].nz, (p->flags & PIFCM_Q2_SQDIST) ? 1 : 0,
                                      ctx->s));
-  }
-  TRY(ensure(ctx, ctx->flags, 64, "flags"));
-  TRY(ensure_pinned(ctx, 4096));
-  return run_invariants(ctx, vols, nv, C, U0s, need_g ? (float*)ctx->invg.p : nullptr, invg_off.data(),
-                        (int*)ctx->flags.p, (int*)ctx->pinned);
+  return run_invariants(ctx, vols, nv, C, U0s, needs_invg(kind) ? (float*)ctx->invg.p : nullptr,
+                        invg_off.data(), flags);
 }
 
 SolveState init_state(const float* c0, int C, float lam, float xi, const pifcm_params* p,
@@ -820,6 +855,7 @@ pifcm_status pifcm_create(int device, void* hip_stream, pifcm_ctx** out) {
       hipStreamCreateWithFlags(&ctx->s, hipStreamNonBlocking) != hipSuccess ||
       hipEventCreateWithFlags(&ctx->ev_in, hipEventDisableTiming) != hipSuccess ||
       hipEventCreateWithFlags(&ctx->ev_out, hipEventDisableTiming) != hipSuccess ||
+      hipEventCreateWithFlags(&ctx->ev_norm, hipEventDisableTiming) != hipSuccess ||
       hipEventCreate(&ctx->tm0) != hipSuccess || hipEventCreate(&ctx->tm1) != hipSuccess) {
     (void)hipGetLastError();
     pifcm_destroy(ctx);
@@ -838,7 +874,9 @@ pifcm_status pifcm_create(int device, void* hip_stream, pifcm_ctx** out) {
   }
   ensure(ctx, ctx->tvol, sizeof(VolDev) * kMaxBatchVols, "volume table");
   ensure(ctx, ctx->tpair, sizeof(PairDev) * kMaxPairs, "pair table");
-  if (ensure(ctx, ctx->work, 16 * sizeof(int32_t), "item counters") != PIFCM_OK ||
+  if (ensure(ctx, ctx->norm, 2 * sizeof(NormSlot), "normalisation") != PIFCM_OK ||
+      hipHostMalloc((void**)&ctx->norm_seen, sizeof(int), hipHostMallocDefault) != hipSuccess ||
+      ensure(ctx, ctx->work, 16 * sizeof(int32_t), "item counters") != PIFCM_OK ||
       hipMemset(ctx->work.p, 0, 16 * sizeof(int32_t)) != hipSuccess) {
     (void)hipGetLastError();
     pifcm_destroy(ctx);
@@ -866,9 +904,11 @@ void pifcm_destroy(pifcm_ctx* ctx) {
   for (DevBuf* b : {&ctx->invg, &ctx->rinv, &ctx->ubuf, &ctx->partials, &ctx->states, &ctx->jhist, &ctx->tvol,
                     &ctx->tpair, &ctx->flags, &ctx->adj_ck, &ctx->adj_seg, &ctx->adj_bar,
                     &ctx->adj_pq, &ctx->adj_misc, &ctx->adj_rs, &ctx->tune_u0, &ctx->tune_state, &ctx->tune_ref, &ctx->ring_tab,
-                    &ctx->conf, &ctx->pso_state, &ctx->work})
+                    &ctx->conf, &ctx->pso_state, &ctx->work, &ctx->norm})
     if (b->p) (void)hipFree(b->p);
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
+  if (ctx->norm_seen) (void)hipHostFree(ctx->norm_seen);
+  if (ctx->ev_norm) (void)hipEventDestroy(ctx->ev_norm);
   if (ctx->ev_in) (void)hipEventDestroy(ctx->ev_in);
   if (ctx->ev_out) (void)hipEventDestroy(ctx->ev_out);
   if (ctx->tm0) (void)hipEventDestroy(ctx->tm0);
@@ -914,7 +954,7 @@ pifcm_status pifcm_workspace_bytes(pifcm_ctx* ctx, int64_t* device_bytes, int64_
                           &ctx->tvol, &ctx->tpair, &ctx->flags, &ctx->adj_ck, &ctx->adj_seg,
                           &ctx->adj_bar, &ctx->adj_pq, &ctx->adj_misc, &ctx->adj_rs, &ctx->tune_u0,
                           &ctx->tune_state, &ctx->tune_ref, &ctx->ring_tab, &ctx->conf, &ctx->pso_state,
-                          &ctx->work})
+                          &ctx->work, &ctx->norm})
     d += (int64_t)b->cap;
   if (device_bytes) *device_bytes = d;
   if (pinned_bytes) *pinned_bytes = (int64_t)ctx->pinned_cap;
@@ -950,22 +990,27 @@ pifcm_status pifcm_normalize(pifcm_ctx* ctx, const float* raw, int64_t n, float*
   if (!raw || !x_out) return fail(ctx, PIFCM_E_INVALID, "raw and x_out must be non-NULL");
   if (n < 1) return fail(ctx, PIFCM_E_INVALID, "n = %lld must be >= 1", (long long)n);
   TRY(begin(ctx));
-  TRY(ensure(ctx, ctx->flags, 64, "flags"));
-  uint32_t* mm = (uint32_t*)ctx->flags.p + 4;
-  int* flag = (int*)ctx->flags.p;
-  const uint32_t init[2] = {0xffffffffu, 0u};
-  TRY(ensure_pinned(ctx, 4096));
-  std::memcpy(ctx->pinned, init, sizeof init);
-  HIPCHK(hipMemsetAsync(flag, 0, sizeof(int), ctx->s));
-  HIPCHK(hipMemcpyAsync(mm, ctx->pinned, sizeof init, hipMemcpyHostToDevice, ctx->s));
-  // The flag is checked before x_out is written so an error leaves it alone.
-  HIPCHK(launch_minmax(raw, (size_t)n, mm, flag, ctx->s));
-  HIPCHK(hipMemcpyAsync((char*)ctx->pinned + 64, flag, sizeof(int), hipMemcpyDeviceToHost, ctx->s));
-  HIPCHK(hipStreamSynchronize(ctx->s));
-  if (*(int*)((char*)ctx->pinned + 64))
-    return fail(ctx, PIFCM_E_NONFINITE, "the raw volume holds a NaN or Inf");
-  HIPCHK(launch_scale(raw, (size_t)n, mm, x_out, ctx->s));
+  // Two slots in turn: this call's scaling pass presets the next call's slot.
+  // A call that did not get that far leaves norm_clean unset.
+  NormSlot* const slots = (NormSlot*)ctx->norm.p;
+  if (!ctx->norm_clean) {
+    const NormSlot init[2] = {{0xffffffffu, 0u, 0, 0}, {0xffffffffu, 0u, 0, 0}};
+    HIPCHK(hipMemcpyAsync(slots, init, sizeof init, hipMemcpyHostToDevice, ctx->s));
+    HIPCHK(hipStreamSynchronize(ctx->s));
+  }
+  ctx->norm_clean = false;
+  NormSlot* const slot = slots + ctx->norm_slot;
+  NormSlot* const next = slots + (ctx->norm_slot ^= 1);
+  *ctx->norm_seen = 0;
+  HIPCHK(launch_minmax(raw, (size_t)n, slot, ctx->norm_seen, ctx->s));
+  HIPCHK(hipEventRecord(ctx->ev_norm, ctx->s));
+  // The scaling pass finds the flag on the device and leaves x_out alone if
+  // it is set, so it need not wait for this thread to have seen it.
+  HIPCHK(launch_scale(raw, (size_t)n, slot, next, x_out, ctx->s));
+  ctx->norm_clean = true;
   TRY(finish(ctx));
+  HIPCHK(hipEventSynchronize(ctx->ev_norm));
+  if (*(volatile int*)ctx->norm_seen) return fail(ctx, PIFCM_E_NONFINITE, "the raw volume holds a NaN or Inf");
   return PIFCM_OK;
 }
 
@@ -979,11 +1024,8 @@ struct SolveWs {
   float* rinv = nullptr;       // device [N][4] ring invariants (two-ring kernel only)
   float* ubuf = nullptr;       // device [N][C] second membership buffer
   float* partials = nullptr;   // device [tiles][2C + 1] tile sums
-  SolveState* st = nullptr;    // device, one
-  PairDev* tpair = nullptr;    // device, one
-  VolDev* tvol = nullptr;      // device, one
+  char* control = nullptr;     // device, control block of one pair and one volume
   double* jhist = nullptr;     // device [max(1, max_iter)]
-  int* flags = nullptr;        // device, 2 ints
   char* stage = nullptr;       // host, kStageBytes (pinned or pageable)
   double* jh_stage = nullptr;  // host [max_iter] staging of the J history, or NULL to copy
                                // it straight into the caller's array
@@ -1008,14 +1050,7 @@ pifcm_status solve_run(pifcm_ctx* ctx, const SolveWs& ws, const pifcm_volume* vo
   const bool m2 = p->m == 2.0f;
   const int kind = kind_of(p, lambda == 0.0f && xi == 0.0f);
   const size_t N = nvox(*vol);
-  if (kind == kRing2)
-    HIPCHK(launch_ring2_invariants(vol->x, ws.rinv, vol->nx, vol->ny, vol->nz,
-                                   (p->flags & PIFCM_Q2_SQDIST) ? 1 : 0, ctx->s));
-  const size_t off0 = 0;
-  const float* u0s[1] = {U_in};
-  float* const invg = kind == kGather ? ws.invg : nullptr;
-  if (slab) TRY(run_context(ctx, vol, zbeg, zend, C, U_in, U_out, labels_out, invg, ws.flags, (int*)ws.stage));
-  else TRY(run_invariants(ctx, vol, 1, C, u0s, invg, &off0, ws.flags, (int*)ws.stage));
+  const Control dev{ws.control, 1}, host{ws.stage, 1};
   const TileShape ts = shape_for(ctx, C, m2, *vol, kind);
   const VolDev vh = make_vol(*vol, ws.invg, ts, zbeg, zend, kind == kRing2 ? ws.rinv : nullptr);
   PairDev pr{};
@@ -1027,19 +1062,24 @@ pifcm_status solve_run(pifcm_ctx* ctx, const SolveWs& ws, const pifcm_volume* vo
   // at the start (U_in given), the buffers swap so the last state lands in
   // U_out without a copy.
   if (kind != kFcm && U_in && p->eps == 0.f && (p->max_iter & 1) == 0) std::swap(pr.Ua, pr.Ub);
-  pr.st = ws.st;
+  pr.st = dev.st();
   pr.partials = ws.partials;
 
-  char* pin = ws.stage;
-  SolveState hs = init_state(centres_in, C, lambda, xi, p, ws.jhist);
-  std::memcpy(pin, &hs, sizeof hs);
-  std::memcpy(pin + sizeof(SolveState), &pr, sizeof pr);
-  std::memcpy(pin + sizeof(SolveState) + sizeof(PairDev), &vh, sizeof(VolDev));
-  HIPCHK(hipMemcpyAsync(ws.st, pin, sizeof hs, hipMemcpyHostToDevice, ctx->s));
-  HIPCHK(hipMemcpyAsync(ws.tpair, pin + sizeof(SolveState), sizeof pr, hipMemcpyHostToDevice, ctx->s));
-  HIPCHK(hipMemcpyAsync(ws.tvol, pin + sizeof(SolveState) + sizeof(PairDev), sizeof(VolDev),
-                        hipMemcpyHostToDevice, ctx->s));
-  if (!U_in && kind != kFcm) HIPCHK(launch_init_u(C, vol->x, N, ws.st, p->m, m2, ws.ubuf, ctx->s));
+  std::memset(host.p, 0, kFlagBytes);
+  *host.st() = init_state(centres_in, C, lambda, xi, p, ws.jhist);
+  *host.pairs() = pr;
+  *host.vols() = vh;
+  HIPCHK(hipMemcpyAsync(dev.p, host.p, control_bytes(1, 1), hipMemcpyHostToDevice, ctx->s));
+  if (kind == kRing2)
+    HIPCHK(launch_ring2_invariants(vol->x, ws.rinv, vol->nx, vol->ny, vol->nz,
+                                   (p->flags & PIFCM_Q2_SQDIST) ? 1 : 0, ctx->s));
+  const size_t off0 = 0;
+  const float* u0s[1] = {U_in};
+  float* const invg = kind == kGather ? ws.invg : nullptr;
+  if (slab) TRY(run_context(ctx, vol, zbeg, zend, C, U_in, U_out, labels_out, invg, dev.flags()));
+  else TRY(run_invariants(ctx, vol, 1, C, u0s, invg, &off0, dev.flags()));
+  if ((double)N * p->max_iter >= kLongRun) TRY(wait_flags(ctx, dev, host));
+  if (!U_in && kind != kFcm) HIPCHK(launch_init_u(C, vol->x, N, dev.st(), p->m, m2, ws.ubuf, ctx->s));
   // Rows of the planes iterated.
   const size_t plane = (size_t)vol->nx * vol->ny, row0 = (size_t)zbeg * plane, rows = (size_t)(zend - zbeg) * plane;
   if (slab && kind != kFcm) {
@@ -1050,21 +1090,25 @@ pifcm_status solve_run(pifcm_ctx* ctx, const SolveWs& ws, const pifcm_volume* vo
                           hipMemcpyDeviceToDevice, ctx->s));
   }
 
-  LaunchArgs a = make_args(ctx, ws.tvol, ws.tpair, &vh, 1, 1, kind, p);
+  LaunchArgs a = make_args(ctx, dev.vols(), dev.pairs(), &vh, 1, 1, kind, p);
   a.want_j = p->eps > 0.f || J_hist_out ? 1 : 0;
   a.fcm_sorted = fcm_sorted ? 1 : 0;
   const int occ = occupancy_of(kind, C, ts.nw, m2, true);
   const int grid = grid_for(ctx, a.nitems, occ, items_per_group(kind, ts.nw));
   int t = 0;
-  SolveState* hst = (SolveState*)pin;
+  const SolveState* hst = host.st();
+  auto read_back = [&]() -> pifcm_status {
+    HIPCHK(hipMemcpyAsync(host.p, dev.p, dev.readback(), hipMemcpyDeviceToHost, ctx->s));
+    HIPCHK(hipStreamSynchronize(ctx->s));
+    return check_flags(ctx, host.flags());
+  };
   TRY(timing_begin(ctx));
   while (t < p->max_iter) {
     const int k = p->eps > 0.f ? std::min(kChunk, p->max_iter - t) : p->max_iter - t;
     for (int i = 0; i < k; ++i) HIPCHK(launch_step(C, a, grid, ts.nw, m2, kind, true, ctx->s));
     t += k;
     if (p->eps > 0.f && t < p->max_iter) {
-      HIPCHK(hipMemcpyAsync(hst, ws.st, sizeof(SolveState), hipMemcpyDeviceToHost, ctx->s));
-      HIPCHK(hipStreamSynchronize(ctx->s));
+      TRY(read_back());
       if (hst->stop) break;
     }
   }
@@ -1074,20 +1118,30 @@ pifcm_status solve_run(pifcm_ctx* ctx, const SolveWs& ws, const pifcm_volume* vo
   const int occe = occupancy_of(kind, C, ts.nw, m2, false);
   HIPCHK(launch_step(C, ae, grid_for(ctx, a.nitems, occe, items_per_group(kind, ts.nw)), ts.nw, m2,
                      kind, false, ctx->s));
-  HIPCHK(hipMemcpyAsync(hst, ws.st, sizeof(SolveState), hipMemcpyDeviceToHost, ctx->s));
-  HIPCHK(hipStreamSynchronize(ctx->s));
+  double* jh = ws.jh_stage ? ws.jh_stage : J_hist_out;
+  // Labels, memberships and history of the final state, T iterations in.
+  auto outputs = [&](int T) -> pifcm_status {
+    const float* Ufin = kind == kFcm ? U_out : u_state_of(pr, T);
+    if (labels_out) HIPCHK(launch_labels(Ufin + row0 * C, rows, C, labels_out + row0, ctx->s));
+    // (a slab whose iteration count is 0 has its state in U_in)
+    if (Ufin != U_out)
+      HIPCHK(hipMemcpyAsync(U_out + row0 * C, Ufin + row0 * C, rows * C * sizeof(float), hipMemcpyDeviceToDevice,
+                            ctx->s));
+    if (J_hist_out && T > 0)
+      HIPCHK(hipMemcpyAsync(jh, ws.jhist, (size_t)T * sizeof(double), hipMemcpyDeviceToHost, ctx->s));
+    return PIFCM_OK;
+  };
+  // Without a stop rule T is max_iter, and one wait covers everything (but a
+  // history copied straight to the caller, who must not see it on an error).
+  const bool known = p->eps == 0.f && (!J_hist_out || ws.jh_stage);
+  if (known) TRY(outputs(p->max_iter));
+  TRY(read_back());
   const int T = hst->iter;
   TRY(timing_collect(ctx, t));
-  const float* Ufin = kind == kFcm ? U_out : u_state_of(pr, T);
-  if (labels_out) HIPCHK(launch_labels(Ufin + row0 * C, rows, C, labels_out + row0, ctx->s));
-  // (a slab whose iteration count is 0 has its state in U_in)
-  if (Ufin != U_out)
-    HIPCHK(hipMemcpyAsync(U_out + row0 * C, Ufin + row0 * C, rows * C * sizeof(float), hipMemcpyDeviceToDevice,
-                          ctx->s));
-  double* jh = ws.jh_stage ? ws.jh_stage : J_hist_out;
-  if (J_hist_out && T > 0)
-    HIPCHK(hipMemcpyAsync(jh, ws.jhist, (size_t)T * sizeof(double), hipMemcpyDeviceToHost, ctx->s));
-  HIPCHK(hipStreamSynchronize(ctx->s));
+  if (!known) {
+    TRY(outputs(T));
+    HIPCHK(hipStreamSynchronize(ctx->s));
+  }
   if (centres_out)
     for (int j = 0; j < C; ++j) centres_out[j] = hst->c[T & 1][j];
   if (J_out) *J_out = hst->J_eval;
@@ -1112,10 +1166,9 @@ pifcm_status solve_impl(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_par
   const int slots = solve_slots(ctx, vol, p, kind, zbeg, zend);
   if (kind == kGather) TRY(ensure(ctx, ctx->invg, Np * sizeof(float), "iteration invariants"));
   if (kind == kRing2) TRY(ensure(ctx, ctx->rinv, Np * 4 * sizeof(float), "ring invariants"));
-  TRY(ensure(ctx, ctx->flags, 64, "flags"));
   if (kind != kFcm) TRY(ensure(ctx, ctx->ubuf, N * C * sizeof(float), "memberships"));
   TRY(ensure(ctx, ctx->partials, (size_t)slots * (2 * C + 1) * sizeof(float), "tile sums"));
-  TRY(ensure(ctx, ctx->states, sizeof(SolveState), "solve state"));
+  TRY(ensure(ctx, ctx->states, control_bytes(1, 1), "solve state"));
   TRY(ensure(ctx, ctx->jhist, (size_t)std::max(1, p->max_iter) * sizeof(double), "objective history"));
   TRY(ensure_pinned(ctx, kStageBytes + (size_t)std::max(1, p->max_iter) * sizeof(double) + 4096));
   SolveWs ws;
@@ -1123,11 +1176,8 @@ pifcm_status solve_impl(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_par
   ws.rinv = kind == kRing2 ? (float*)ctx->rinv.p : nullptr;
   ws.ubuf = (float*)ctx->ubuf.p;
   ws.partials = (float*)ctx->partials.p;
-  ws.st = (SolveState*)ctx->states.p;
-  ws.tpair = (PairDev*)ctx->tpair.p;
-  ws.tvol = (VolDev*)ctx->tvol.p;
+  ws.control = (char*)ctx->states.p;
   ws.jhist = (double*)ctx->jhist.p;
-  ws.flags = (int*)ctx->flags.p;
   ws.stage = (char*)ctx->pinned;
   ws.jh_stage = (double*)((char*)ctx->pinned + kStageBytes);
   return solve_run(ctx, ws, vol, p, lambda, xi, centres_in, U_in, U_out, centres_out, labels_out, J_out,
@@ -1171,7 +1221,6 @@ pifcm_status ifcm_solve(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_par
   std::vector<double> jh((size_t)std::max(1, p->max_iter));
   TRY(solve_impl(ctx, vol, p, lambda, xi, centres_in, U_in, U_out, c_tmp, labels_out, &J, &T,
                  J_hist_out ? jh.data() : nullptr));
-  TRY(finish(ctx));
   if (centres_out) std::memcpy(centres_out, c_tmp, sizeof(float) * p->C);
   if (J_out) *J_out = J;
   if (iters_out) *iters_out = T;
@@ -1198,11 +1247,8 @@ pifcm_status ifcm_solve_noalloc(pifcm_ctx* ctx, const pifcm_volume* vol, const p
   const size_t o_ubuf = o_invg + al(Np * sizeof(float));
   const size_t o_part = o_ubuf + al(N * C * sizeof(float));
   const size_t o_st = o_part + al((size_t)slots * (2 * C + 1) * sizeof(float));
-  const size_t o_pair = o_st + al(sizeof(SolveState));
-  const size_t o_vol = o_pair + al(sizeof(PairDev));
-  const size_t o_jh = o_vol + al(sizeof(VolDev));
-  const size_t o_flags = o_jh + al((size_t)std::max(1, p->max_iter) * sizeof(double));
-  const size_t need = o_flags + al(2 * sizeof(int));
+  const size_t o_jh = o_st + al(control_bytes(1, 1));
+  const size_t need = o_jh + al((size_t)std::max(1, p->max_iter) * sizeof(double));
   if (need > kScratchBytes)
     return fail(ctx, PIFCM_E_INVALID,
                 "ifcm_solve_noalloc: this solve needs %zu bytes of scratch (N = %zu, C = %d, max_iter = %d), "
@@ -1219,11 +1265,8 @@ pifcm_status ifcm_solve_noalloc(pifcm_ctx* ctx, const pifcm_volume* vol, const p
   ws.invg = (float*)(sc + o_invg);
   ws.ubuf = (float*)(sc + o_ubuf);
   ws.partials = (float*)(sc + o_part);
-  ws.st = (SolveState*)(sc + o_st);
-  ws.tpair = (PairDev*)(sc + o_pair);
-  ws.tvol = (VolDev*)(sc + o_vol);
+  ws.control = sc + o_st;
   ws.jhist = (double*)(sc + o_jh);
-  ws.flags = (int*)(sc + o_flags);
   ws.stage = (char*)ctx->pinned;  // allocated at pifcm_create, at least kStageBytes
   ws.jh_stage = nullptr;          // the J history goes straight to J_hist_out
   float c_tmp[kMaxC];
@@ -1231,7 +1274,6 @@ pifcm_status ifcm_solve_noalloc(pifcm_ctx* ctx, const pifcm_volume* vol, const p
   int32_t T = 0;
   TRY(solve_run(ctx, ws, vol, p, lambda, xi, centres_in, U_in, U_out, c_tmp, labels_out, &J, &T,
                 J_hist_out, 0, vol->nz));
-  TRY(finish(ctx));
   if (centres_out) std::memcpy(centres_out, c_tmp, sizeof(float) * C);
   if (J_out) *J_out = J;
   if (iters_out) *iters_out = T;
@@ -1256,7 +1298,6 @@ pifcm_status ifcm_solve_slab(pifcm_ctx* ctx, const pifcm_volume* vol, int32_t zb
   std::vector<double> jh((size_t)std::max(1, p->max_iter));
   TRY(solve_impl(ctx, vol, p, lambda, xi, centres_in, U_in, U_out, c_tmp, labels_out, &J, &T,
                  J_hist_out ? jh.data() : nullptr, zbeg, zend));
-  TRY(finish(ctx));
   if (centres_out) std::memcpy(centres_out, c_tmp, sizeof(float) * p->C);
   if (J_out) *J_out = J;
   if (iters_out) *iters_out = T;
@@ -1281,7 +1322,6 @@ pifcm_status pifcm_fcm_init(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm
   int32_t perm[kMaxC];
   for (int j = 0; j < C; ++j) perm[j] = j;
   std::stable_sort(perm, perm + C, [&](int a, int b) { return c1[a] < c1[b]; });
-  TRY(finish(ctx));
   for (int j = 0; j < C; ++j) centres_out[j] = c1[perm[j]];
   if (iters_out) *iters_out = T;
   return PIFCM_OK;
@@ -1308,7 +1348,7 @@ pifcm_status swarm_core(pifcm_ctx* ctx, const pifcm_volume* vols, int32_t B, con
   for (long k = 0; k < 2L * B * P; ++k) zero = zero && particles[k] == 0.0f;
   const int kind = kind_of(p, zero);
   std::vector<size_t> off;
-  TRY(prepare_volumes(ctx, vols, B, C, U0_check, off, kind, p));
+  TRY(ensure_invariants(ctx, vols, B, off, kind));
 
   // Tile shape (the waves per work group are those of the launch) and, in the
   // batched launch, particles per work item and runs of planes per tile.
@@ -1343,21 +1383,20 @@ pifcm_status swarm_core(pifcm_ctx* ctx, const pifcm_volume* vols, int32_t B, con
     return fail(ctx, PIFCM_E_UNSUPPORTED, "%zu tiles in one launch: more than 2^31 - 2^20", slots);
   if (kind != kFcm) TRY(ensure(ctx, ctx->ubuf, ubytes, "swarm memberships"));
   TRY(ensure(ctx, ctx->partials, slots * (2 * C + 1) * sizeof(float), "tile sums"));
-  TRY(ensure(ctx, ctx->states, npairs * sizeof(SolveState), "solve states"));
-  const size_t pin_bytes = npairs * (sizeof(SolveState) + sizeof(PairDev)) + sizeof(VolDev) * B + 4096;
-  TRY(ensure_pinned(ctx, pin_bytes));
+  TRY(ensure(ctx, ctx->states, control_bytes(npairs, B), "solve states"));
+  TRY(ensure_pinned(ctx, control_bytes(npairs, B) + 4096));
   for (int b = 0; b < B; ++b) {
     vh[b].invg = kind == kGather ? (const float*)ctx->invg.p + off[b] : nullptr;
     vh[b].rinv = kind == kRing2 ? (const float*)ctx->rinv.p + 4 * off[b] : nullptr;
   }
 
-  char* pin = (char*)ctx->pinned;
-  SolveState* hs = (SolveState*)pin;
-  PairDev* hp = (PairDev*)(pin + npairs * sizeof(SolveState));
-  VolDev* hv = (VolDev*)(pin + npairs * (sizeof(SolveState) + sizeof(PairDev)));
-  SolveState* st_dev = (SolveState*)ctx->states.p;
+  const Control dev{(char*)ctx->states.p, npairs}, host{(char*)ctx->pinned, npairs};
+  SolveState* const hs = host.st();
+  PairDev* const hp = host.pairs();
+  SolveState* const st_dev = dev.st();
+  std::memset(host.p, 0, kFlagBytes);
   for (int b = 0; b < B; ++b) {
-    hv[b] = vh[b];
+    host.vols()[b] = vh[b];
     const size_t Nb = nvox(vols[b]);
     const size_t ustride = (Nb * C + 63) / 64 * 64;
     const int tb = std::max(vh[b].slots, vh[b].tiles1d);
@@ -1377,13 +1416,15 @@ pifcm_status swarm_core(pifcm_ctx* ctx, const pifcm_volume* vols, int32_t B, con
       pr.partials = (float*)ctx->partials.p + (soff[b] + (size_t)q * tb) * (2 * C + 1);
     }
   }
-  HIPCHK(hipMemcpyAsync(st_dev, hs, npairs * sizeof(SolveState), hipMemcpyHostToDevice, ctx->s));
-  HIPCHK(hipMemcpyAsync(ctx->tpair.p, hp, npairs * sizeof(PairDev), hipMemcpyHostToDevice, ctx->s));
-  HIPCHK(hipMemcpyAsync(ctx->tvol.p, hv, B * sizeof(VolDev), hipMemcpyHostToDevice, ctx->s));
+  HIPCHK(hipMemcpyAsync(dev.p, host.p, control_bytes(npairs, B), hipMemcpyHostToDevice, ctx->s));
+  TRY(prepare_volumes(ctx, vols, B, C, U0_check, off, kind, p, dev.flags()));
+  double passes = 0.0;
+  for (int b = 0; b < B; ++b) passes += (double)nvox(vols[b]) * P * p->max_iter;
+  if (passes >= kLongRun) TRY(wait_flags(ctx, dev, host));
 
   if (is_ring(kind)) TRY(prepare_ring(ctx, p));
-  const VolDev* vdev = (const VolDev*)ctx->tvol.p;
-  const PairDev* pdev = (const PairDev*)ctx->tpair.p;
+  const VolDev* vdev = dev.vols();
+  const PairDev* pdev = dev.pairs();
   bool several = false;  // some tiles hold several runs of planes
   for (int b = 0; b < B; ++b) several = several || vh[b].zc > vh[b].sc;
   const int occ = occupancy_of(kind, C, ts0.nw, m2, true, pt, several);
@@ -1391,9 +1432,13 @@ pifcm_status swarm_core(pifcm_ctx* ctx, const pifcm_volume* vols, int32_t B, con
   const int ipg = items_per_group(kind, ts0.nw);
 
   int64_t launches = 0;
-  auto all_stopped = [&](bool& done) -> pifcm_status {
-    HIPCHK(hipMemcpyAsync(hs, st_dev, npairs * sizeof(SolveState), hipMemcpyDeviceToHost, ctx->s));
+  auto read_back = [&]() -> pifcm_status {
+    HIPCHK(hipMemcpyAsync(host.p, dev.p, dev.readback(), hipMemcpyDeviceToHost, ctx->s));
     HIPCHK(hipStreamSynchronize(ctx->s));
+    return check_flags(ctx, host.flags());
+  };
+  auto all_stopped = [&](bool& done) -> pifcm_status {
+    TRY(read_back());
     done = true;
     for (size_t k = 0; k < npairs; ++k) done = done && hs[k].stop;
     return PIFCM_OK;
@@ -1474,8 +1519,7 @@ pifcm_status swarm_core(pifcm_ctx* ctx, const pifcm_volume* vols, int32_t B, con
     for (size_t q = 0; q < npairs; ++q)
       HIPCHK(launch_step(C, args[q], gride[q], ts0.nw, m2, kind, false, ctx->s));
   }
-  HIPCHK(hipMemcpyAsync(hs, st_dev, npairs * sizeof(SolveState), hipMemcpyDeviceToHost, ctx->s));
-  HIPCHK(hipStreamSynchronize(ctx->s));
+  TRY(read_back());
   TRY(timing_collect(ctx, launches));
   if (state_out && kind != kFcm) {
     for (int b = 0; b < B; ++b)
@@ -1488,7 +1532,6 @@ pifcm_status swarm_core(pifcm_ctx* ctx, const pifcm_volume* vols, int32_t B, con
       }
     HIPCHK(hipStreamSynchronize(ctx->s));
   }
-  TRY(finish(ctx));
   for (size_t k = 0; k < npairs; ++k) {
     const int T = hs[k].iter;
     fitness_out[k] = hs[k].J_eval;
@@ -1567,7 +1610,12 @@ pifcm_status ifcm_backward(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_
   TRY(begin(ctx));
   std::vector<size_t> off;
   const float* u0s[1] = {U0};
-  TRY(prepare_volumes(ctx, vol, 1, C, u0s, off, kind, p));
+  TRY(ensure_invariants(ctx, vol, 1, off, kind));
+  TRY(ensure(ctx, ctx->flags, kFlagBytes, "flags"));
+  TRY(ensure_pinned(ctx, 4096));
+  HIPCHK(hipMemsetAsync(ctx->flags.p, 0, kFlagBytes, ctx->s));
+  TRY(prepare_volumes(ctx, vol, 1, C, u0s, off, kind, p, (int*)ctx->flags.p));
+  TRY(wait_flags(ctx, Control{(char*)ctx->flags.p, 0}, Control{(char*)ctx->pinned, 0}));
   const TileShape ts = shape_for(ctx, C, m2, *vol, kind);
   std::vector<VolDev> vh{make_vol(*vol, (const float*)ctx->invg.p, ts)};
   const int slots = std::max(vh[0].slots, vh[0].tiles1d);

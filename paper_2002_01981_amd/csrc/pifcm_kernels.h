@@ -58,10 +58,17 @@ hipError_t launch_labels(const float* U, size_t N, int C, uint8_t* out, hipStrea
 // labels against truth; the last entry counts out-of-range pairs.
 hipError_t launch_confusion(const uint8_t* labels, const uint8_t* truth, size_t N, int C, int K,
                             unsigned long long* counts, hipStream_t s);
-// Min-max normalisation: exact min/max keys into mm[0..1] (mm preset to
-// {0xffffffff, 0}) and a non-finite flag, then the scaling pass.
-hipError_t launch_minmax(const float* raw, size_t n, uint32_t* mm, int* flag, hipStream_t s);
-hipError_t launch_scale(const float* raw, size_t n, const uint32_t* mm, float* out, hipStream_t s);
+// Min-max normalisation: exact min/max keys and a non-finite flag in one of
+// two slots (preset to {0xffffffff, 0, 0}), then the scaling pass, which
+// presets the other slot for the call after.  *seen (host memory the device
+// can write, 0 before) is set if a value is not finite.
+struct NormSlot {
+  uint32_t lo, hi;
+  int32_t bad, pad;
+};
+hipError_t launch_minmax(const float* raw, size_t n, NormSlot* slot, int* seen, hipStream_t s);
+hipError_t launch_scale(const float* raw, size_t n, const NormSlot* slot, NormSlot* next, float* out,
+                        hipStream_t s);
 // Arguments of the reverse pass of one iteration (adjoint.hip).
 struct AdjArgs {
   const float* x;          // [N] normalised intensities

@@ -527,7 +527,7 @@ __device__ __forceinline__ float kinv(uint32_t k) {
 // 1024 work groups of 256 threads and dword loads).
 constexpr int kMinmaxThreads = 1024;
 __global__ __launch_bounds__(kMinmaxThreads) void k_minmax(const float* __restrict__ raw, size_t n,
-                                                           uint32_t* __restrict__ mm, int* __restrict__ flag) {
+                                                           NormSlot* __restrict__ slot, int* __restrict__ seen) {
   uint32_t lo = 0xffffffffu, hi = 0u;
   bool bad = false;
   auto take = [&](float v) {
@@ -574,18 +574,25 @@ __global__ __launch_bounds__(kMinmaxThreads) void k_minmax(const float* __restri
       lo = min(lo, s_lo[w]);
       hi = max(hi, s_hi[w]);
     }
-    atomicMin(&mm[0], lo);
-    atomicMax(&mm[1], hi);
-    if (any_bad) atomicOr(flag, 1);
+    atomicMin(&slot->lo, lo);
+    atomicMax(&slot->hi, hi);
+    if (any_bad) {
+      atomicOr(&slot->bad, 1);
+      __hip_atomic_store(seen, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
   }
 }
 
 // One thread scales four elements (float4s where raw and out sit alike on
 // 16-byte boundaries); raw and out may be the same array.  HBM bound: 7.1 M
-// values in 11 us (5.1 TB/s; 15 us with dwords).
+// values in 11 us (5.1 TB/s; 15 us with dwords).  Leaves out alone if a value is
+// not finite, and presets the slot of the next call.
 __global__ __launch_bounds__(256) void k_normalize(const float* raw, size_t n,
-                                                   const uint32_t* __restrict__ mm, float* out) {
-  const double mn = (double)kinv(mm[0]), mx = (double)kinv(mm[1]);
+                                                   const NormSlot* __restrict__ slot, NormSlot* __restrict__ next,
+                                                   float* out) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *next = NormSlot{0xffffffffu, 0u, 0, 0};
+  if (slot->bad) return;
+  const double mn = (double)kinv(slot->lo), mx = (double)kinv(slot->hi);
   const bool flat = mx == mn;
   auto scale = [&](float v) { return flat ? 0.f : (float)(((double)v - mn) / (mx - mn)); };
   const size_t tid = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
@@ -813,17 +820,18 @@ hipError_t launch_confusion(const uint8_t* labels, const uint8_t* truth, size_t 
   return hipGetLastError();
 }
 
-hipError_t launch_minmax(const float* raw, size_t n, uint32_t* mm, int* flag, hipStream_t s) {
+hipError_t launch_minmax(const float* raw, size_t n, NormSlot* slot, int* seen, hipStream_t s) {
   // At most one work group per CU (256 on the card), each thread four float4s
   // or more.
   const size_t per = (size_t)kMinmaxThreads * 16;
   const int g = (int)std::max<size_t>(1, std::min<size_t>((n + per - 1) / per, 256));
-  hipLaunchKernelGGL(k_minmax, dim3(g), dim3(kMinmaxThreads), 0, s, raw, n, mm, flag);
+  hipLaunchKernelGGL(k_minmax, dim3(g), dim3(kMinmaxThreads), 0, s, raw, n, slot, seen);
   return hipGetLastError();
 }
 
-hipError_t launch_scale(const float* raw, size_t n, const uint32_t* mm, float* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_normalize, dim3(small_grid((n + 3) / 4)), dim3(256), 0, s, raw, n, mm, out);
+hipError_t launch_scale(const float* raw, size_t n, const NormSlot* slot, NormSlot* next, float* out,
+                        hipStream_t s) {
+  hipLaunchKernelGGL(k_normalize, dim3(small_grid((n + 3) / 4)), dim3(256), 0, s, raw, n, slot, next, out);
   return hipGetLastError();
 }
 
