@@ -303,11 +303,14 @@ int default_zc(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v) {
   return best;
 }
 
-// Planes per tile of the general-neighbourhood kernels: of the depths
-// ceil(nz / k) and 32 that are at least min(nz, 32) deep, the one with the
-// fewest rounds of one pair's tiles on the fused step's resident waves times
-// (depth + 4); the deeper one on a tie.
-int ring_zc(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v) {
+// Planes per tile of the general-neighbourhood kernels and of the adjoint's
+// forward pass: of the depths ceil(nz / k) and 32 that are at least min(nz, 32)
+// deep, the one with the fewest rounds of one pair's tiles on the fused step's
+// resident waves times (depth + 4); the deeper one on a tie.  The adjoint keeps
+// it although other depths are faster on small volumes: the gradient at the
+// initial centres is what is left of sums that cancel to 1e-5 of their terms,
+// and the order of the forward pass's sums shows in it.
+int floored_zc(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v) {
   const long R = (long)resident_waves(ctx, C, m2);
   const long txy = (long)((v.nx + kWaveTileX - 1) / kWaveTileX) * ((v.ny + kWaveTileY - 1) / kWaveTileY);
   const int floor_zc = std::min(v.nz, 32);
@@ -330,13 +333,14 @@ int ring_zc(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v) {
   return best;
 }
 
-TileShape shape_for(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v, int kind) {
+TileShape shape_for(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v, int kind, bool adjoint = false) {
   TileShape t;
   auto it = ctx->tuned.find(std::make_tuple(C, (int)m2, v.nx, v.ny, v.nz));
   if (it != ctx->tuned.end()) t = it->second;
   if (t.zc <= 0) {
-    t.deep = kind == kGather;
-    t.zc = is_ring(kind) ? ring_zc(ctx, C, m2, v) : default_zc(ctx, C, m2, v);
+    const bool floored = adjoint || is_ring(kind);
+    t.deep = kind == kGather && !floored;
+    t.zc = floored ? floored_zc(ctx, C, m2, v) : default_zc(ctx, C, m2, v);
   }
   t.zc = std::max(1, std::min(t.zc, max_zc(v, C)));
   return t;
@@ -621,25 +625,30 @@ pifcm_status prepare_ring(pifcm_ctx* ctx, const pifcm_params* p) {
   return PIFCM_OK;
 }
 
-// One iteration (step) or the objective-only pass: the tile kernel, then the
-// per-pair finalise that adds the tile sums and advances the state.
+// The tile kernel of one iteration (step) or of the objective-only pass.
 // A grid with a wave slot for every item of an even split by count (each XCD
 // runs its range in one pass) keeps that split: ranges balanced by work
 // would hand some XCD more items than it has waves.  A persistent grid,
 // whose waves walk several items each, takes the balanced ranges.
-hipError_t launch_step(int C, const LaunchArgs& a, int grid, int nw, bool m2, int kind, bool step,
-                       hipStream_t s) {
+hipError_t launch_tiles(int C, const LaunchArgs& a, int grid, int nw, bool m2, int kind, bool step,
+                        hipStream_t s) {
   LaunchArgs b = a;
   const long per = ((long)a.nitems + 7) / 8;
   if ((long)(grid / 8) * items_per_group(kind, nw) >= per)
     for (int k = 0; k <= 8; ++k) b.xcd_begin[k] = (int32_t)std::min<long>(a.nitems, per * k);
-  hipError_t e = kind == kFcm        ? launch_fcm_x(C, b, grid, m2, step, s)
-                 : kind == kFcmStore ? launch_fcm(C, b, grid, m2, step, s)
-                 : kind == kRing     ? launch_ring(C, b, grid, m2, step, s)
-                 : kind == kRing2    ? launch_ring2(C, b, grid, m2, step, s)
-                                     : launch_gather(C, b, grid, nw, m2, step, s);
-  if (e != hipSuccess) return e;
-  return launch_finalize(C, b, b.nvol * b.P, step, s);
+  return kind == kFcm        ? launch_fcm_x(C, b, grid, m2, step, s)
+         : kind == kFcmStore ? launch_fcm(C, b, grid, m2, step, s)
+         : kind == kRing     ? launch_ring(C, b, grid, m2, step, s)
+         : kind == kRing2    ? launch_ring2(C, b, grid, m2, step, s)
+                             : launch_gather(C, b, grid, nw, m2, step, s);
+}
+
+// The same, then the per-pair finalise that adds the tile sums and advances
+// the state.
+hipError_t launch_step(int C, const LaunchArgs& a, int grid, int nw, bool m2, int kind, bool step,
+                       hipStream_t s) {
+  const hipError_t e = launch_tiles(C, a, grid, nw, m2, kind, step, s);
+  return e != hipSuccess ? e : launch_finalize(C, a, a.nvol * a.P, step, s);
 }
 
 // The 8 XCD ranges of a launch's items (LaunchArgs::xcd_begin): contiguous,
@@ -1616,9 +1625,12 @@ pifcm_status ifcm_backward(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_
   HIPCHK(hipMemsetAsync(ctx->flags.p, 0, kFlagBytes, ctx->s));
   TRY(prepare_volumes(ctx, vol, 1, C, u0s, off, kind, p, (int*)ctx->flags.p));
   TRY(wait_flags(ctx, Control{(char*)ctx->flags.p, 0}, Control{(char*)ctx->pinned, 0}));
-  const TileShape ts = shape_for(ctx, C, m2, *vol, kind);
+  const TileShape ts = shape_for(ctx, C, m2, *vol, kind, true);
   std::vector<VolDev> vh{make_vol(*vol, (const float*)ctx->invg.p, ts)};
-  const int slots = std::max(vh[0].slots, vh[0].tiles1d);
+  // Recomputed steps need no sums, and take the depth of a lone solve.
+  const TileShape tr = shape_for(ctx, C, m2, *vol, kind);
+  std::vector<VolDev> vr{make_vol(*vol, (const float*)ctx->invg.p, tr)};
+  const int slots = std::max({vh[0].slots, vr[0].slots, vh[0].tiles1d});
   // Workspace: forward ping-pong, checkpoints at t = S, 2S, ... <= K - 1,
   // the S - 1 recomputed states of a segment, two adjoint buffers, the
   // transpose sources, slots and small histories.
@@ -1643,7 +1655,7 @@ pifcm_status ifcm_backward(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_
   const size_t rs_bytes = rs_states + (size_t)std::max(R, 1) * sizeof(PairDev);
   TRY(ensure(ctx, ctx->adj_rs, rs_bytes, "recompute states"));
   TRY(ensure(ctx, ctx->tpair, (size_t)K * sizeof(PairDev), "pair records"));
-  const size_t pin_fixed = (size_t)(S + 2) * (sizeof(SolveState) + sizeof(PairDev)) + sizeof(VolDev) +
+  const size_t pin_fixed = (size_t)(S + 2) * (sizeof(SolveState) + sizeof(PairDev)) + 2 * sizeof(VolDev) +
                            (size_t)(K + 1) * C * sizeof(float) + 64 * sizeof(double) + 4096;
   const size_t pin_rs = (pin_fixed + 255) / 256 * 256;  // pinned copy of the recompute records
   const size_t pin_fwd = (pin_rs + rs_bytes + 255) / 256 * 256;  // ... and of the forward's
@@ -1696,19 +1708,21 @@ pifcm_status ifcm_backward(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_
     hrec[t - 1] = q;
   }
   std::memcpy(pin, &hs, sizeof hs);
-  std::memcpy(pin + sizeof(SolveState) + sizeof(PairDev), &vh[0], sizeof(VolDev));
-  std::memcpy(pin + sizeof(SolveState) + sizeof(PairDev) + sizeof(VolDev), centres0, C * sizeof(float));
+  VolDev* const hvol = (VolDev*)(pin + sizeof(SolveState) + sizeof(PairDev));
+  hvol[0] = vh[0];
+  hvol[1] = vr[0];
+  std::memcpy(hvol + 2, centres0, C * sizeof(float));
   HIPCHK(hipMemcpyAsync(st_dev, pin, sizeof hs, hipMemcpyHostToDevice, ctx->s));
   HIPCHK(hipMemcpyAsync(tp, hrec, (size_t)K * sizeof(PairDev), hipMemcpyHostToDevice, ctx->s));
-  HIPCHK(hipMemcpyAsync(ctx->tvol.p, pin + sizeof(SolveState) + sizeof(PairDev), sizeof(VolDev),
-                        hipMemcpyHostToDevice, ctx->s));
-  HIPCHK(hipMemcpyAsync(c_hist, pin + sizeof(SolveState) + sizeof(PairDev) + sizeof(VolDev),
-                        C * sizeof(float), hipMemcpyHostToDevice, ctx->s));
+  HIPCHK(hipMemcpyAsync(ctx->tvol.p, hvol, 2 * sizeof(VolDev), hipMemcpyHostToDevice, ctx->s));
+  HIPCHK(hipMemcpyAsync(c_hist, hvol + 2, C * sizeof(float), hipMemcpyHostToDevice, ctx->s));
   LaunchArgs a = make_args(ctx, (const VolDev*)ctx->tvol.p, tp, vh, 1, 1, kind, &pf);
   const int occ = occupancy_of(kind, C, ts.nw, m2, true);
   const int grid = grid_for(ctx, a.nitems, occ, items_per_group(kind, ts.nw));
   const int occe = occupancy_of(kind, C, ts.nw, m2, false);
   const int gride = grid_for(ctx, a.nitems, occe, items_per_group(kind, ts.nw));
+  const int gridr = grid_for(ctx, kind == kGather ? vr[0].tiles : vr[0].tiles1d,
+                             occupancy_of(kind, C, tr.nw, m2, true), items_per_group(kind, tr.nw));
   for (int t = 1; t <= K; ++t) {
     a.pairs = tp + (t - 1);
     HIPCHK(launch_step(C, a, grid, ts.nw, m2, kind, true, ctx->s));
@@ -1790,8 +1804,8 @@ pifcm_status ifcm_backward(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_
       for (int i = 1; i < len; ++i) {
         if (t0 != t0_last) {
           const LaunchArgs ar =
-              make_args(ctx, (const VolDev*)ctx->tvol.p, rs_pr + seg_r + (i - 1), vh, 1, 1, kind, &pf);
-          HIPCHK(launch_step(C, ar, grid, ts.nw, m2, kind, true, ctx->s));
+              make_args(ctx, (const VolDev*)ctx->tvol.p + 1, rs_pr + seg_r + (i - 1), vr, 1, 1, kind, &pf);
+          HIPCHK(launch_tiles(C, ar, gridr, tr.nw, m2, kind, true, ctx->s));
         }
         seg[i] = seg_state(i);
       }
