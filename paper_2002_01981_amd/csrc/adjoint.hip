@@ -51,8 +51,10 @@ constexpr int kAdjPW = 4;                    // waves per work group of k_adj_po
 // (by the number of existing off-planes: 0, 1, 2) once per tile and picks
 // one per plane (adj_qinv_column, adj_qinv_at); the transpose, which needs
 // them for its halo cells too, forms each cell's one value as it stages it
-// (adj_qinv_cell; measured faster there than carrying six values).  The
-// expressions are the same, so the transpose rebuilds Q bit for bit.
+// (adj_qinv_cell; measured faster there than carrying six values), and on the
+// planes of a tile where every cell has all its neighbours takes the one
+// value they share.  The expressions are the same, so the transpose rebuilds
+// Q bit for bit.
 struct AdjQinv {
   float v[3];
 };
@@ -89,7 +91,12 @@ __device__ __forceinline__ float adj_qinv_cell(int gx, int gy, int gz, int nx, i
 // planes are done is finalised: it recomputes the forward values of eqs (4),
 // (2) from (U^t, c^t) and applies the adjoint formulas above, writing its
 // transpose source da (the transpose forms P and Q from it) and adding its
-// dJ/dc, dJ/dlambda, dJ/dxi terms to the lane's sums.  Each wave leaves its sums in its own slot.
+// dJ/dc, dJ/dlambda, dJ/dxi terms to the lane's sums.  Each wave leaves its
+// sums in its own slot.
+// Bound by VALU issue at two waves per SIMD (217 registers).  Plane bases in
+// scalar registers with 32-bit lane offsets, and centre values kept in the
+// column's slots instead of read back from LDS: 126.7 -> 124.7 us on
+// 77 x 256 x 256, C = 4.
 template <int C, bool M2, bool EVAL>
 __global__ __launch_bounds__(64 * kAdjPW) void k_adj_point(const AdjArgs a) {
   constexpr int CP = (C + 3) / 4 * 4;
@@ -150,8 +157,11 @@ __global__ __launch_bounds__(64 * kAdjPW) void k_adj_point(const AdjArgs a) {
     const bool active = gx < nx && gy < ny;
     const int hx = x0 - 1 + hcx, hy = y0 - 1 + hcy;
     const bool hvalid = hlane && hx >= 0 && hx < nx && hy >= 0 && hy < ny;
-    const size_t own_xy = active ? (size_t)gy * nx + gx : 0;
-    const size_t halo_xy = hvalid ? (size_t)hy * nx + hx : 0;
+    // Lane byte offsets within a plane of x (4 B per voxel; rows of C floats
+    // are C times that); the plane's base moves in scalar registers.
+    uint32_t own_ofs = active ? ((uint32_t)gy * nx + gx) * 4u : 0u;
+    uint32_t halo_ofs = hvalid ? ((uint32_t)hy * nx + hx) * 4u : 0u;
+    uint32_t own_ofs_u = own_ofs * C, halo_ofs_u = halo_ofs * C;
     float* const sc = &s_c[wave][0][0];
     const AdjQinv qcol = adj_qinv_column(gx, gy, nx, ny, wCa, wEb, wCb);
 
@@ -161,12 +171,14 @@ __global__ __launch_bounds__(64 * kAdjPW) void k_adj_point(const AdjArgs a) {
     float rx, rg, ru[C], rgn[C], hxv, hu[C];
     auto load_plane = [&](int q) __attribute__((always_inline)) {
       const bool pv = q >= 0 && q < nz;
+      const size_t pofs = pv ? (size_t)q * psz : 0;
+      const gfloat* Xq = opaque_base(as_global(a.x) + pofs);
+      const gfloat* Uq = opaque_base(as_global(a.U) + pofs * C);
       if (pv && active) {
-        const size_t i = (size_t)q * psz + own_xy;
-        rx = a.x[i];
-        rg = a.invg[i];
-        load_row<C>(as_global(a.U) + i * C, ru);
-        if constexpr (!EVAL) load_row<C>(as_global(a.Ubar_next) + i * C, rgn);
+        rx = *at_lane(Xq, own_ofs);
+        rg = *at_lane(opaque_base(as_global(a.invg) + pofs), own_ofs);
+        load_row<C>(at_lane(Uq, own_ofs_u), ru);
+        if constexpr (!EVAL) load_row<C>(at_lane(opaque_base(as_global(a.Ubar_next) + pofs * C), own_ofs_u), rgn);
       } else {
         rx = 0.f;
         rg = 1.f;
@@ -174,9 +186,8 @@ __global__ __launch_bounds__(64 * kAdjPW) void k_adj_point(const AdjArgs a) {
         for (int j = 0; j < C; ++j) ru[j] = rgn[j] = 0.f;
       }
       if (pv && hvalid) {
-        const size_t i = (size_t)q * psz + halo_xy;
-        hxv = a.x[i];
-        load_row<C>(as_global(a.U) + i * C, hu);
+        hxv = *at_lane(Xq, halo_ofs);
+        load_row<C>(at_lane(Uq, halo_ofs_u), hu);
       } else {
         hxv = 0.f;
 #pragma unroll
@@ -198,13 +209,15 @@ __global__ __launch_bounds__(64 * kAdjPW) void k_adj_point(const AdjArgs a) {
 
     // Slots of the voxels p-1, p, p+1 of the lane's column: H numerators of
     // the first C - 1 clusters (the last H is 1 minus their sum, as in the
-    // forward step), F numerators, the stored g_inv and (iteration pass)
+    // forward step), F numerators, the stored g_inv, the centre value that
+    // forms g (shifted by -1 for a flat neighbourhood) and (iteration pass)
     // dJ/dU^(t+1).
     constexpr int CH = C - 1;
-    float hn[3][C], fn[3][C], gs[3], gns[3][C];
+    float hn[3][C], fn[3][C], gs[3], xs[3], gns[3][C];
 #pragma unroll
     for (int s2 = 0; s2 < 3; ++s2) {
       gs[s2] = 1.f;
+      xs[s2] = 0.f;
 #pragma unroll
       for (int j = 0; j < C; ++j) hn[s2][j] = fn[s2][j] = gns[s2][j] = 0.f;
     }
@@ -230,7 +243,7 @@ __global__ __launch_bounds__(64 * kAdjPW) void k_adj_point(const AdjArgs a) {
         e[j] = dd[j] * dd[j] * av[j];
         d[j] = fmaxf(e[j], kDFloor);
       }
-      const size_t i = (size_t)z * psz + own_xy;
+      const size_t zofs = (size_t)z * psz * C;
       float dbar[C];
       if constexpr (EVAL) {
         float u[C];
@@ -242,7 +255,7 @@ __global__ __launch_bounds__(64 * kAdjPW) void k_adj_point(const AdjArgs a) {
           direct[j] = m * um1 * d[j];
           dbar[j] = pow_m<M2>(u[j], m);
         }
-        if (active) store_row<C>(as_global(a.Ubar_direct) + i * C, direct);
+        if (active) store_row<C>(at_lane(opaque_base(as_global(a.Ubar_direct) + zofs), own_ofs_u), direct);
       } else {
         float w[C], up[C];
         float sw = 0.f;
@@ -297,7 +310,7 @@ __global__ __launch_bounds__(64 * kAdjPW) void k_adj_point(const AdjArgs a) {
         acc[C] += -da[j] * H[j];             // dJ/dlambda
         acc[C + 1] += -da[j] * F[j];         // dJ/dxi
       }
-      if (active) store_row<C>(as_global(a.PQ) + i * C, da);
+      if (active) store_row<C>(at_lane(opaque_base(as_global(a.PQ) + zofs), own_ofs_u), da);
     };
 
     auto plane = [&](int p, int SA, int SB, int SC) __attribute__((always_inline)) {
@@ -307,16 +320,13 @@ __global__ __launch_bounds__(64 * kAdjPW) void k_adj_point(const AdjArgs a) {
       const bool pv = p >= 0 && p < nz;
       const bool doA = p - 1 >= zlo, doB = p >= zlo && p < zhi, doC = p + 1 < zhi;
       __builtin_amdgcn_wave_barrier();
-      // Centre values for g (shifted by -1 for a flat neighbourhood).
-      const float xA = doA ? cell_at(bprev, 0, 0)[0] : 0.f;
-      const float xcA = gs[SA] < 0.f ? xA - 1.f : xA;
-      const float xC = rg < 0.f ? rx - 1.f : rx;  // voxel p+1, prefetched
+      // Centre values for g: voxels p-1 and p from their slots, p+1 prefetched.
+      const float xcA = xs[SA], xcB = xs[SB];
+      const float xC = rg < 0.f ? rx - 1.f : rx;
       float hC[C], E[C], Co[C], Pc[C];
 #pragma unroll
       for (int j = 0; j < C; ++j) hC[j] = E[j] = Co[j] = Pc[j] = 0.f;
       if (pv) {
-        const float xB = cell_at(bp, 0, 0)[0];
-        const float xcB = gs[SB] < 0.f ? xB - 1.f : xB;
 #pragma unroll
         for (int dy = -1; dy <= 1; ++dy) {
 #pragma unroll
@@ -359,6 +369,7 @@ __global__ __launch_bounds__(64 * kAdjPW) void k_adj_point(const AdjArgs a) {
       if (p + 1 <= zhi) {
         store_plane(bnext);
         gs[SC] = rg;
+        xs[SC] = xC;
 #pragma unroll
         for (int j = 0; j < C; ++j) gns[SC][j] = rgn[j];
         if (p + 2 <= zhi) load_plane(p + 2);
@@ -393,6 +404,8 @@ __global__ __launch_bounds__(64 * kAdjPW) void k_adj_point(const AdjArgs a) {
         }
         gs[0] = gs[1];
         gs[1] = gs[2];
+        xs[0] = xs[1];
+        xs[1] = xs[2];
         p += 1;
       }
     }
@@ -409,6 +422,11 @@ __global__ __launch_bounds__(64 * kAdjPW) void k_adj_point(const AdjArgs a) {
 // its 3 x 3 in-plane cells to the three voxels of its column they touch.
 // For the Q part the in-plane cells are summed per offset class first (the
 // weights of eq (7) depend only on the class).
+// Bound by VALU issue.  A cell's eq (7) normalisation costs two IEEE divisions;
+// on the planes of a tile whose cells (halo included) lie off every face it is
+// one constant, which covers all but the boundary tiles.  With that and scalar
+// plane bases: 127.9 -> 106.5 us on 77 x 256 x 256, C = 4 (objective pass 165
+// -> 124 us).
 template <int C>
 constexpr int adj_waves() { return C <= 12 ? 4 : 3; }
 
@@ -440,6 +458,7 @@ __global__ __launch_bounds__(64 * adj_waves<C>()) void k_adj_transpose_tiled(con
   const int ntz = (nz + zc - 1) / zc;
   const int nitems = ntx * nty * ntz;
   const uint32_t psz = (uint32_t)nx * (uint32_t)ny;
+  const float q_inner = adj_qinv_cell(1, 1, 1, 3, 3, 3, wCa, wEb, wCb);
 
   const int per = (nitems + 7) >> 3;
   const int xcd = blockIdx.x & 7;
@@ -456,47 +475,54 @@ __global__ __launch_bounds__(64 * adj_waves<C>()) void k_adj_transpose_tiled(con
     const bool active = gx < nx && gy < ny;
     const int hx = x0 - 1 + hcx, hy = y0 - 1 + hcy;
     const bool hvalid = hlane && hx >= 0 && hx < nx && hy >= 0 && hy < ny;
-    const size_t own_xy = active ? (size_t)gy * nx + gx : 0;
-    const size_t halo_xy = hvalid ? (size_t)hy * nx + hx : 0;
+    uint32_t own_ofs = active ? ((uint32_t)gy * nx + gx) * 4u : 0u;
+    uint32_t halo_ofs = hvalid ? ((uint32_t)hy * nx + hx) * 4u : 0u;
+    uint32_t own_ofs_u = own_ofs * C, halo_ofs_u = halo_ofs * C;
+    // Every cell of the tile and its halo lies off the volume's x and y faces:
+    // on planes off its z faces they all have the same q_inv.
+    const bool inner = x0 >= 2 && x0 + kAdjTX + 1 < nx && y0 >= 2 && y0 + kAdjTY + 1 < ny;
     float* const sc = &s_c[wave][0][0];
 
-    // Prefetch registers of one plane: own and halo cell (intensity as the
-    // cell uses it in eq (5), its |g_inv| and q_inv, and da).
+    // Prefetch registers of one plane: own and halo cell (intensity,
+    // g_inv, q_inv and da).
     // The own cell also brings the voxel's U (and in the objective pass its
     // direct term), which only the voxel's own finalisation reads, three
     // planes later.
-    float rxc, rx, rgi, rqi, rd[C], ru[C], rdir[C], hxc, hgi, hqi, hd[C];
+    float rx, rg, rqi, rd[C], ru[C], rdir[C], hx0, hg, hqi, hd[C];
     auto load_plane = [&](int q) __attribute__((always_inline)) {
       const bool pv = q >= 0 && q < nz;
-      rx = rxc = rgi = rqi = hxc = hgi = hqi = 0.f;
+      rx = rg = rqi = hx0 = hg = hqi = 0.f;
 #pragma unroll
       for (int j = 0; j < C; ++j) rd[j] = hd[j] = ru[j] = rdir[j] = 0.f;
+      const size_t pofs = pv ? (size_t)q * psz : 0;
+      const gfloat* Xq = opaque_base(as_global(a.x) + pofs);
+      const gfloat* Gq = opaque_base(as_global(a.invg) + pofs);
+      const gfloat* Dq = opaque_base(as_global(a.PQ) + pofs * C);
       if (pv && active) {
-        const size_t i = (size_t)q * psz + own_xy;
-        rx = a.x[i];
-        const float g = a.invg[i];
-        rxc = g < 0.f ? rx - 1.f : rx;
-        rgi = fabsf(g);
-        rqi = adj_qinv_cell(gx, gy, q, nx, ny, nz, wCa, wEb, wCb);
-        load_row<C>(as_global(a.PQ) + i * C, rd);
-        load_row<C>(as_global(a.U) + i * C, ru);
-        if constexpr (EVAL) load_row<C>(as_global(a.Ubar_direct) + i * C, rdir);
+        rx = *at_lane(Xq, own_ofs);
+        rg = *at_lane(Gq, own_ofs);
+        load_row<C>(at_lane(Dq, own_ofs_u), rd);
+        load_row<C>(at_lane(opaque_base(as_global(a.U) + pofs * C), own_ofs_u), ru);
+        if constexpr (EVAL) load_row<C>(at_lane(opaque_base(as_global(a.Ubar_direct) + pofs * C), own_ofs_u), rdir);
       }
       if (pv && hvalid) {
-        const size_t i = (size_t)q * psz + halo_xy;
-        const float xh = a.x[i];
-        const float g = a.invg[i];
-        hxc = g < 0.f ? xh - 1.f : xh;
-        hgi = fabsf(g);
-        hqi = adj_qinv_cell(hx, hy, q, nx, ny, nz, wCa, wEb, wCb);
-        load_row<C>(as_global(a.PQ) + i * C, hd);
+        hx0 = *at_lane(Xq, halo_ofs);
+        hg = *at_lane(Gq, halo_ofs);
+        load_row<C>(at_lane(Dq, halo_ofs_u), hd);
+      }
+      if (inner && q > 0 && q < nz - 1) {
+        rqi = hqi = q_inner;
+      } else if (pv) {
+        if (active) rqi = adj_qinv_cell(gx, gy, q, nx, ny, nz, wCa, wEb, wCb);
+        if (hvalid) hqi = adj_qinv_cell(hx, hy, q, nx, ny, nz, wCa, wEb, wCb);
       }
     };
     // P = -lambda da g_inv and Q = -xi da q_inv of the cell (the products the
     // per-voxel kernel would have formed).
-    auto store_cell = [&](float* cell, float* xcell, float xc, float gi, float qi, const float (&dav)[C])
+    auto store_cell = [&](float* cell, float* xcell, float xv, float g, float qi, const float (&dav)[C])
         __attribute__((always_inline)) {
-      *xcell = xc;
+      *xcell = g < 0.f ? xv - 1.f : xv;
+      const float gi = fabsf(g);
       float P[C], Q[C];
 #pragma unroll
       for (int j = 0; j < C; ++j) {
@@ -510,8 +536,8 @@ __global__ __launch_bounds__(64 * adj_waves<C>()) void k_adj_transpose_tiled(con
     auto store_plane = [&](int buf) __attribute__((always_inline)) {
       float* base = sc + buf * kAdjCells * CW;
       float* xb = sxw + buf * kAdjCells;
-      store_cell(base + own_cell * CW, xb + own_cell, rxc, rgi, rqi, rd);
-      if (hlane) store_cell(base + halo_cell * CW, xb + halo_cell, hxc, hgi, hqi, hd);
+      store_cell(base + own_cell * CW, xb + own_cell, rx, rg, rqi, rd);
+      if (hlane) store_cell(base + halo_cell * CW, xb + halo_cell, hx0, hg, hqi, hd);
     };
 
     // Target slots (voxels p-1, p, p+1 of the lane's column): P-part and
@@ -525,14 +551,13 @@ __global__ __launch_bounds__(64 * adj_waves<C>()) void k_adj_transpose_tiled(con
     }
     auto finalize = [&](int z, int S) __attribute__((always_inline)) {
       if (!active) return;
-      const size_t k = (size_t)z * psz + own_xy;
       float out[C];
 #pragma unroll
       for (int j = 0; j < C; ++j) {
         const float t = hP[S][j] + 2.f * us[S][j] * fQ[S][j];
         out[j] = EVAL ? ds[S][j] + t : t;
       }
-      store_row<C>(as_global(Ubar_out) + k * C, out);
+      store_row<C>(at_lane(opaque_base(as_global(Ubar_out) + (size_t)z * psz * C), own_ofs_u), out);
     };
 
     auto cell_at = [&](int buf, int dy, int dx) -> const float* {
