@@ -15,58 +15,215 @@
 // two-voxel halo (20 x 8 cells of x and U) is staged once in the wave's LDS
 // (four plane buffers), and every lane reads its 5 x 5 in-plane cells once:
 // they contribute to the five voxels of its column at planes p-2 .. p+2, kept
-// in five register slots that move down by one after each plane (a version
-// that renames the slots over five unrolled planes needs more than 512
-// registers).  For F the squared memberships of the 25
+// in five register slots that move down by one after each plane (mostly
+// in the destination of the last sum).  For F the squared memberships of the 25
 // cells are summed per in-plane offset class once per plane and weighted per
-// slot.  The last cluster's H comes from sum_j H_ij = sum_r W_r (rows of U
-// sum to 1).  Voxel p-2 is complete after plane p and is finalised: eqs (4),
-// (1), (2), (3) as in the fused step.
+// plane distance, which two slots share.  The last cluster's H comes from
+// sum_j H_ij = sum_r W_r (rows of U sum to 1).  Voxel p-2 is complete after
+// plane p and is finalised: eqs (4), (1), (2), (3) as in the fused step.
+//
+// Bound by VALU issue: 124 differences, 372 + 100 + 84 multiply-adds for H, the
+// squares and F at C = 4, 829 instructions per voxel in all (939 before).  Two
+// waves per SIMD: the ring invariants wait in LDS for their voxel instead of in
+// the slots, ring 1 has no slot p+2, cells beside the volume are zeroed once per
+// tile and their lanes store to a spare cell, so loads need no test and plane
+// bases are scalar.  A step of 8 particles on 204 x 251 x 104, C = 4: 1659 ->
+// 1065 us.
 #include "common.h"
 #include "pifcm_kernels.h"
 
 namespace pifcm {
 
-__global__ __launch_bounds__(256) void k_ring2_invariants(const float* __restrict__ x,
-                                                          float* __restrict__ rinv, int nx, int ny,
-                                                          int nz, int q2_sqdist) {
-  const size_t N = (size_t)nx * ny * nz;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < N;
-       i += (size_t)gridDim.x * blockDim.x) {
-    const int gx = (int)(i % nx);
-    const size_t rr = i / nx;
-    const int gy = (int)(rr % ny);
-    const int gz = (int)(rr / ny);
-    const float xi = x[i];
-    float gs[2] = {0.f, 0.f}, qs[2] = {0.f, 0.f};
-    int cnt[2] = {0, 0};
-    for (int dz = -2; dz <= 2; ++dz)
-      for (int dy = -2; dy <= 2; ++dy)
-        for (int dx = -2; dx <= 2; ++dx) {
-          const int X2 = gx + dx, Y2 = gy + dy, Z2 = gz + dz;
-          if ((dx | dy | dz) == 0 || X2 < 0 || X2 >= nx || Y2 < 0 || Y2 >= ny || Z2 < 0 || Z2 >= nz)
-            continue;
-          const int r = max(abs(dx), max(abs(dy), abs(dz))) - 1;
-          const int s2 = dx * dx + dy * dy + dz * dz;
-          gs[r] += fabsf(xi - x[((size_t)Z2 * ny + Y2) * nx + X2]);
-          qs[r] += q2_sqdist ? (float)s2 : (float)(s2 * s2);
-          ++cnt[r];
-        }
-    float o[4];
+// Ring invariants of one volume: per voxel and ring g_inv (or -1 / n_r, see
+// above; 0 for a ring without cells) and q_inv.
+//
+// A wave owns kInv2Cols x kInv2Rows columns of a run of zc planes and walks it
+// along z.  Lane l holds column x0 - 2 + l (the two outer lanes on each side are
+// halo), the columns beside it come from the lanes beside it (DPP wave shifts),
+// the rows from its own registers, and each plane serves the voxels of five
+// planes.  Cells outside the volume are loaded from a clamped address and
+// weighted 0.  The eq (7) denominators depend on the position only: products of
+// per-axis sums of 1, d^2 and d^4 over the offsets inside the volume (whole
+// numbers, exact), formed again only for planes next to a z face.
+// Bound by VALU issue (124 differences and sums per voxel): 85 us for 204 x 251 x
+// 104 voxels, where one thread per voxel reading its 124 neighbours through the
+// caches with a test each took 328 us.
+constexpr int kInv2Cols = 60, kInv2Rows = 2;
+
+namespace {
+__device__ __forceinline__ float lane_before(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x138, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float lane_after(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x130, 0xf, 0xf, true));
+}
+// Sums of 1, d^2 and d^4 over the offsets |d| <= r of one axis that stay inside
+// the volume (r = 1, 2).
+struct Axis {
+  float n[2], a[2], b[2];
+};
+__device__ __forceinline__ Axis axis_sums(int g, int n) {
+  const int e1 = (g > 0) + (g < n - 1), e2 = (g > 1) + (g < n - 2);
+  Axis s;
+  s.n[0] = (float)(1 + e1);
+  s.a[0] = s.b[0] = (float)e1;
+  s.n[1] = (float)(1 + e1 + e2);
+  s.a[1] = (float)(e1 + 4 * e2);
+  s.b[1] = (float)(e1 + 16 * e2);
+  return s;
+}
+// Cells of ring r (0, 1) and the inverse of their eq (7) weights' sum.
+__device__ __forceinline__ void ring_sums(const Axis& x, const Axis& y, const Axis& z, int q2_sqdist,
+                                          float (&cnt)[2], float (&qinv)[2]) {
+  float q[2];
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      o[r] = gs[r] > 0.f ? 1.f / gs[r] : (cnt[r] > 0 ? -1.f / (float)cnt[r] : 0.f);
-      o[2 + r] = cnt[r] > 0 ? 1.f / qs[r] : 0.f;
+  for (int r = 0; r < 2; ++r) {
+    const float xy = x.n[r] * y.n[r], a = x.a[r] * y.n[r] + y.a[r] * x.n[r];
+    cnt[r] = xy * z.n[r] - 1.f;
+    if (q2_sqdist)
+      q[r] = a * z.n[r] + z.a[r] * xy;
+    else
+      q[r] = (x.b[r] * y.n[r] + y.b[r] * x.n[r] + 2.f * (x.a[r] * y.a[r])) * z.n[r] + z.b[r] * xy + 2.f * (z.a[r] * a);
+  }
+  cnt[1] -= cnt[0];
+  q[1] -= q[0];
+#pragma unroll
+  for (int r = 0; r < 2; ++r) qinv[r] = cnt[r] > 0.f ? 1.f / q[r] : 0.f;
+}
+}  // namespace
+
+__global__ __launch_bounds__(256) void k_ring2_invariants(const float* __restrict__ x, float* __restrict__ rinv,
+                                                          int nx, int ny, int nz, int zc, int nitems,
+                                                          int q2_sqdist) {
+  constexpr int R = kInv2Rows;
+  const int lane = threadIdx.x & 63;
+  const int item = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+  if (item >= nitems) return;
+  const int ntx = (nx + kInv2Cols - 1) / kInv2Cols, nty = (ny + R - 1) / R;
+  const int gx = (item % ntx) * kInv2Cols + lane - 2, y0 = (item / ntx) % nty * R;
+  const int zlo = item / ntx / nty * zc, zhi = min(zlo + zc, nz);
+  const bool own = lane >= 2 && lane < 2 + kInv2Cols && gx < nx;
+  const int cx = min(max(gx, 0), nx - 1);
+  // Weights (0 or 1) of the cells two left of the lane's column to two right of
+  // it, by row: rows y0 - 2 .. y0 + R + 1.
+  float w[R + 4][5];
+  uint32_t ofs[R + 4];
+#pragma unroll
+  for (int r = 0; r < R + 4; ++r) {
+    const int gy = y0 - 2 + r;
+#pragma unroll
+    for (int d = 0; d < 5; ++d)
+      w[r][d] = gy >= 0 && gy < ny && gx + d - 2 >= 0 && gx + d - 2 < nx ? 1.f : 0.f;
+    ofs[r] = ((uint32_t)min(max(gy, 0), ny - 1) * (uint32_t)nx + (uint32_t)cx) * 4u;
+  }
+  const size_t psz = (size_t)nx * ny;
+  auto load = [&](int p, float (&v)[R + 4]) __attribute__((always_inline)) {
+    const gfloat* base = opaque_base(as_global(x) + (size_t)min(max(p, 0), nz - 1) * psz);
+#pragma unroll
+    for (int r = 0; r < R + 4; ++r) v[r] = *at_lane(base, ofs[r]);
+  };
+  const Axis ax = axis_sums(gx, nx);
+  float cnt[R][2], qinv[R][2];
+  bool full = false;  // cnt and qinv are those of a plane off the z faces
+  // x of the planes p - 2 .. p + 2 (xs[4] and the rows beside the lane's own
+  // only as the next planes' cells), and the ring sums of their voxels: ring 1
+  // starts a plane later.
+  float xs[5][R + 4], ahead[R + 4], s1[R][4], s2[R][5];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) s1[r][k] = 0.f;
+#pragma unroll
+    for (int k = 0; k < 5; ++k) s2[r][k] = 0.f;
+  }
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+#pragma unroll
+    for (int r = 0; r < R + 4; ++r) xs[k][r] = 0.f;
+  load(zlo - 2, xs[2]);
+  load(zlo - 1, xs[3]);
+  load(zlo, xs[4]);
+  for (int p = zlo - 2; p <= zhi + 1; ++p) {
+    load(p + 3, ahead);
+    if (p >= 0 && p < nz) {
+      float c[R + 4][5];
+#pragma unroll
+      for (int r = 0; r < R + 4; ++r) {
+        c[r][2] = xs[2][r];
+        c[r][1] = lane_before(c[r][2]);
+        c[r][0] = lane_before(c[r][1]);
+        c[r][3] = lane_after(c[r][2]);
+        c[r][4] = lane_after(c[r][3]);
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int dy = 0; dy < 5; ++dy)
+#pragma unroll
+          for (int dx = 0; dx < 5; ++dx)
+#pragma unroll
+            for (int k = 0; k < 5; ++k) {  // voxel of plane p - 2 + k
+              if (dy == 2 && dx == 2 && k == 2) continue;
+              const bool in1 = dy >= 1 && dy <= 3 && dx >= 1 && dx <= 3 && k >= 1 && k <= 3;
+              float& s = in1 ? s1[r][k] : s2[r][k];
+              s = fmaf(fabsf(xs[k][r + 2] - c[r + dy][dx]), w[r + dy][dx], s);
+            }
     }
-    store_row<4>(as_global(rinv) + i * 4, o);
+    const int z = p - 2;
+    if (z >= zlo) {
+      gfloat* out = opaque_base(as_global(rinv) + (size_t)z * psz * 4);
+      const bool inner = z > 1 && z < nz - 2;
+      if (!inner || !full) {
+        const Axis az = axis_sums(z, nz);
+#pragma unroll
+        for (int r = 0; r < R; ++r) ring_sums(ax, axis_sums(y0 + r, ny), az, q2_sqdist, cnt[r], qinv[r]);
+        full = inner;
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if (own && y0 + r < ny) {
+          float o[4];
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const float g = q == 0 ? s1[r][0] : s2[r][0];
+            const float d = (g > 0.f ? 1.f : -1.f) / (g > 0.f ? g : cnt[r][q]);
+            o[q] = g > 0.f || cnt[r][q] > 0.f ? d : 0.f;
+            o[2 + q] = qinv[r][q];
+          }
+          uint32_t at = ofs[r + 2] * 4u;
+          store_row<4>(at_lane(out, at), o);
+        }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int r = 0; r < R + 4; ++r) xs[k][r] = xs[k + 1][r];
+#pragma unroll
+    for (int r = 0; r < R + 4; ++r) xs[4][r] = ahead[r];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) s1[r][k] = s1[r][k + 1];
+      s1[r][3] = 0.f;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) s2[r][k] = s2[r][k + 1];
+      s2[r][4] = 0.f;
+    }
   }
 }
 
 hipError_t launch_ring2_invariants(const float* x, float* rinv, int nx, int ny, int nz, int q2_sqdist,
                                    hipStream_t s) {
-  const size_t N = (size_t)nx * ny * nz;
-  const int grid = (int)std::min<size_t>((N + 255) / 256, 65536);
-  hipLaunchKernelGGL(k_ring2_invariants, dim3(grid), dim3(256), 0, s, x, rinv, nx, ny, nz, q2_sqdist);
+  // Runs of 32 planes (four more are read for their ends), shorter while the
+  // planes give fewer than 3000 waves: three per SIMD of the card.
+  const long txy = (long)((nx + kInv2Cols - 1) / kInv2Cols) * ((ny + kInv2Rows - 1) / kInv2Rows);
+  int zc = 32;
+  while (zc > 4 && txy * ((nz + zc - 1) / zc) < 3000) zc /= 2;
+  const long items = txy * ((nz + zc - 1) / zc);
+  if (items > 0x7fffffffL - 4) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_ring2_invariants, dim3((unsigned)((items + 3) / 4)), dim3(256), 0, s, x, rinv, nx, ny, nz, zc,
+                     (int)items, q2_sqdist);
   return hipGetLastError();
 }
 
@@ -113,14 +270,16 @@ __device__ __forceinline__ void static_for(F&& f) {
 }  // namespace r2
 
 template <int C, bool M2, bool STEP>
-__global__ __launch_bounds__(64 * kRing2Waves) void k_ifcm_ring2(const LaunchArgs a) {
+__global__ __launch_bounds__(64 * kRing2Waves, 2) void k_ifcm_ring2(const LaunchArgs a) {
   static_assert(C >= 2 && C <= 4, "the fused two-ring step holds C <= 4 clusters");
   using namespace r2;
   constexpr int CP = 4, CH = C - 1, NW = kRing2Waves;
   constexpr int NV = STEP ? 2 * C + 1 : 1;
-  // One spare cell takes the second halo load of lanes that have none.
+  // One spare cell takes the stores of lanes that have no cell in the volume.
   __shared__ float s_x[NW][NBUF][NCELL + 1];
   __shared__ __align__(16) float s_u[NW][NBUF][(NCELL + 1) * CP];
+  // Ring invariants of the lane's voxels p-2 .. p+1.
+  __shared__ __align__(16) float s_r[NW][NBUF][64 * 4];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -130,8 +289,6 @@ __global__ __launch_bounds__(64 * kRing2Waves) void k_ifcm_ring2(const LaunchArg
   halo_cell(lane, h0x, h0y);
   const bool has_h1 = lane + 64 < NHALO;
   if (has_h1) halo_cell(lane + 64, h1x, h1y);
-  const int h0_cell = h0y * HX + h0x;
-  const int h1_dst = has_h1 ? h1y * HX + h1x : NCELL;
   const float W1 = a.W[1], W2 = a.W[2];
   auto qw = [&](int s2) { return a.q2_sqdist ? (float)s2 : (float)(s2 * s2); };
 
@@ -148,10 +305,10 @@ __global__ __launch_bounds__(64 * kRing2Waves) void k_ifcm_ring2(const LaunchArg
     const SolveState* st = pr.st;
     if (STEP && ld_const(&st->stop)) continue;
     const int t = STEP ? ld_const(&st->iter) + 1 : ld_const(&st->iter);
-    const gfloat* Uin = as_global(STEP ? u_in_of(pr, t) : u_state_of(pr, t));
-    gfloat* Uout = STEP ? as_global(u_out_of(pr, t)) : nullptr;
-    const gfloat* X = as_global(vd.x);
-    const gfloat* RI = as_global(vd.rinv);
+    const gfloat* Uin = as_global(uniform_ptr(STEP ? u_in_of(pr, t) : u_state_of(pr, t)));
+    gfloat* Uout = STEP ? as_global(uniform_ptr(u_out_of(pr, t))) : nullptr;
+    const gfloat* X = as_global(uniform_ptr(vd.x));
+    const gfloat* RI = as_global(uniform_ptr(vd.rinv));
     float cj[C];
 #pragma unroll
     for (int j = 0; j < C; ++j) cj[j] = ld_const(&st->c[(STEP ? t - 1 : t) & 1][j]);
@@ -171,98 +328,100 @@ __global__ __launch_bounds__(64 * kRing2Waves) void k_ifcm_ring2(const LaunchArg
     };
     const bool v0 = in_xy(h0x, h0y), v1 = has_h1 && in_xy(h1x, h1y);
     const size_t psz = (size_t)nx * ny;
-    const size_t own_xy = active ? (size_t)gy * nx + gx : 0;
-    const size_t h0_xy = v0 ? (size_t)(y0 - 2 + h0y) * nx + (x0 - 2 + h0x) : 0;
-    const size_t h1_xy = v1 ? (size_t)(y0 - 2 + h1y) * nx + (x0 - 2 + h1x) : 0;
+    // Lane byte offsets of the three cells within a plane of x (rows of C
+    // floats are C times that); the plane's base moves in scalar registers.
+    uint32_t own_ofs = active ? ((uint32_t)gy * nx + gx) * 4u : 0u;
+    uint32_t h0_ofs = v0 ? ((uint32_t)(y0 - 2 + h0y) * nx + (x0 - 2 + h0x)) * 4u : 0u;
+    uint32_t h1_ofs = v1 ? ((uint32_t)(y0 - 2 + h1y) * nx + (x0 - 2 + h1x)) * 4u : 0u;
+    uint32_t own_ofs_u = own_ofs * C, h0_ofs_u = h0_ofs * C, h1_ofs_u = h1_ofs * C, own_ofs_r = own_ofs * 4u;
+    // A cell beside the volume is 0 in every buffer from here on: its lane
+    // loads the plane's first voxel and stores it in the spare cell.
+    auto cell_of = [&](int cx, int cy, bool valid) __attribute__((always_inline)) {
+      const int cell = cy * HX + cx;
+      if (valid) return cell;
+      const float zero[CP] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int q = 0; q < NBUF; ++q) {
+        s_x[wave][q][cell] = 0.f;
+        lds_cell_store<CP, CP>(&s_u[wave][q][cell * CP], zero);
+      }
+      return NCELL;
+    };
+    __builtin_amdgcn_wave_barrier();
+    const int own_dst = cell_of(tx + 2, ty + 2, active);
+    const int h0_dst = cell_of(h0x, h0y, v0);
+    const int h1_dst = has_h1 ? cell_of(h1x, h1y, v1) : NCELL;
+    __builtin_amdgcn_wave_barrier();
     auto bufof = [&](int q) { return (q - zlo + 2) & (NBUF - 1); };
 
     // Prefetch registers of the next staged plane (own cell, two halo cells)
     // and of the lane's own intensity and ring invariants two planes ahead.
+    // Planes outside the volume are read from plane 0 and not used.
     float px, pu[C], qx0, qu0[C], qx1, qu1[C];
     float ox, ri[4];
     auto load_cells = [&](int q) __attribute__((always_inline)) {
-      const bool pv = q >= 0 && q < nz;
-      const size_t pofs = pv ? (size_t)q * psz : 0;
-      px = qx0 = qx1 = 0.f;
-#pragma unroll
-      for (int j = 0; j < C; ++j) pu[j] = qu0[j] = qu1[j] = 0.f;
-      if (pv && active) {
-        px = X[pofs + own_xy];
-        load_row<C>(Uin + (pofs + own_xy) * C, pu);
-      }
-      if (pv && v0) {
-        qx0 = X[pofs + h0_xy];
-        load_row<C>(Uin + (pofs + h0_xy) * C, qu0);
-      }
-      if (pv && v1) {
-        qx1 = X[pofs + h1_xy];
-        load_row<C>(Uin + (pofs + h1_xy) * C, qu1);
-      }
+      const size_t pofs = q >= 0 && q < nz ? (size_t)q * psz : 0;
+      const gfloat* Xq = opaque_base(X + pofs);
+      const gfloat* Uq = opaque_base(Uin + pofs * C);
+      px = *at_lane(Xq, own_ofs);
+      qx0 = *at_lane(Xq, h0_ofs);
+      qx1 = *at_lane(Xq, h1_ofs);
+      load_row<C>(at_lane(Uq, own_ofs_u), pu);
+      load_row<C>(at_lane(Uq, h0_ofs_u), qu0);
+      load_row<C>(at_lane(Uq, h1_ofs_u), qu1);
     };
     auto load_own = [&](int q) __attribute__((always_inline)) {
-      const bool pv = q >= 0 && q < nz;
-      ox = 0.f;
-      ri[0] = ri[1] = ri[2] = ri[3] = 0.f;
-      if (pv && active) {
-        const size_t i = (size_t)q * psz + own_xy;
-        ox = X[i];
-        load_row<4>(RI + i * 4, ri);
-      }
+      const size_t pofs = q >= 0 && q < nz ? (size_t)q * psz : 0;
+      ox = *at_lane(opaque_base(X + pofs), own_ofs);
+      load_row<4>(at_lane(opaque_base(RI + pofs * 4), own_ofs_r), ri);
     };
     auto store_cells = [&](int buf) __attribute__((always_inline)) {
       float* sx = &s_x[wave][buf][0];
       float* su = &s_u[wave][buf][0];
-      sx[own_cell] = px;
-      lds_cell_store<C, CP>(su + own_cell * CP, pu);
-      sx[h0_cell] = qx0;
-      lds_cell_store<C, CP>(su + h0_cell * CP, qu0);
+      sx[own_dst] = px;
+      lds_cell_store<C, CP>(su + own_dst * CP, pu);
+      sx[h0_dst] = qx0;
+      lds_cell_store<C, CP>(su + h0_dst * CP, qu0);
       sx[h1_dst] = qx1;
       lds_cell_store<C, CP>(su + h1_dst * CP, qu1);
     };
 
-    // Slots of the voxels p-2 .. p+2 of the lane's column, per ring: H
-    // numerators (first C - 1 clusters), F numerators, and the centre value,
-    // g_inv and q_inv of the slot's voxel.
-    float hn[5][2][CH], fn[5][2][C], xcs[5][2], gis[5][2], qis[5][2];
+    // Slots of the voxels p-2 .. p+2 of the lane's column: H numerators (first
+    // C - 1 clusters) and F numerators of ring 1 (h1, f1; they start with slot
+    // 3) and of ring 2 (h2, f2), and the centre value by ring.
+    float h1[4][CH], h2[5][CH], f1[4][C], f2[5][C], xcs[5][2];
     float acc[NV];
 #pragma unroll
     for (int k = 0; k < NV; ++k) acc[k] = 0.f;
 #pragma unroll
-    for (int s5 = 0; s5 < 5; ++s5)
+    for (int k = 0; k < 5; ++k) {
+      xcs[k][0] = xcs[k][1] = 0.f;
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        xcs[s5][q] = gis[s5][q] = qis[s5][q] = 0.f;
-#pragma unroll
-        for (int j = 0; j < CH; ++j) hn[s5][q][j] = 0.f;
-#pragma unroll
-        for (int j = 0; j < C; ++j) fn[s5][q][j] = 0.f;
+      for (int j = 0; j < C; ++j) {
+        if (j < CH) h2[k][j] = 0.f;
+        f2[k][j] = 0.f;
+        if (k < 4 && j < CH) h1[k][j] = 0.f;
+        if (k < 4) f1[k][j] = 0.f;
       }
+    }
 
-    auto finalize = [&](int z, auto Sc, int bz) __attribute__((always_inline)) {
-      constexpr int S = decltype(Sc)::value;
+    auto finalize = [&](int z, int bz, const float (&inv)[4]) __attribute__((always_inline)) {
       const float xv = s_x[wave][bz][own_cell];
       float uo[C];
       lds_cell_load<C, CP>(&s_u[wave][bz][own_cell * CP], uo);
+      const float g1 = W1 * fabsf(inv[0]), g2 = W2 * fabsf(inv[1]);
+      const float q1 = W1 * inv[2], q2 = W2 * inv[3];
       float H[C], F[C];
+      // A ring's ratios sum to 1 over the clusters (0 for a ring without cells).
+      float rest_h = (inv[0] != 0.f ? W1 : 0.f) + (inv[1] != 0.f ? W2 : 0.f);
 #pragma unroll
-      for (int j = 0; j < C; ++j) H[j] = F[j] = 0.f;
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const float w = q == 0 ? W1 : W2;
-        const float gi = gis[S][q];
-        float sh = 0.f;
-#pragma unroll
-        for (int j = 0; j < CH; ++j) {
-          const float h = hn[S][q][j] * gi;
-          H[j] = fmaf(w, h, H[j]);
-          sh += h;
-        }
-        // The ring's ratios sum to 1 over the clusters (0 for a ring without cells).
-        H[C - 1] = fmaf(gi != 0.f ? w : 0.f, 1.f - sh, H[C - 1]);
-        const float wq = w * qis[S][q];
-#pragma unroll
-        for (int j = 0; j < C; ++j) F[j] = fmaf(wq, fn[S][q][j], F[j]);
+      for (int j = 0; j < CH; ++j) {
+        H[j] = fmaf(g2, h2[0][j], g1 * h1[0][j]);
+        rest_h -= H[j];
       }
+      H[C - 1] = rest_h;
+#pragma unroll
+      for (int j = 0; j < C; ++j) F[j] = fmaf(q2, f2[0][j], q1 * f1[0][j]);
       float d2[C];
       float Jv = 0.f;
 #pragma unroll
@@ -272,52 +431,46 @@ __global__ __launch_bounds__(64 * kRing2Waves) void k_ifcm_ring2(const LaunchArg
         d2[j] = fmaxf(dd * dd * av, kDFloor);
         Jv = fmaf(pow_m<M2>(uo[j], a.m), d2[j], Jv);  // eq (1)
       }
+      Jv = active ? Jv : 0.f;
       if constexpr (STEP) {
         float un[C];
         memberships<C, M2>(d2, a.m, un);  // eq (2)
-        if (active) store_row<C>(Uout + ((size_t)z * psz + own_xy) * C, un);
+        if (active) store_row<C>(at_lane(opaque_base(Uout + (size_t)z * psz * C), own_ofs_u), un);
 #pragma unroll
         for (int j = 0; j < C; ++j) {
           const float w = active ? pow_m<M2>(un[j], a.m) : 0.f;
           acc[j] = fmaf(w, xv, acc[j]);  // eq (3)
           acc[C + j] += w;
         }
-        acc[2 * C] += Jv;  // 0 for a lane outside: its staged memberships are 0
+        acc[2 * C] += Jv;
       } else {
         acc[0] += Jv;
       }
     };
 
-    // One plane p: its 5 x 5 cells added to the voxels p-2 .. p+2 (slots
-    // rotated by ROT), the slot of p+2 started, plane p+1 staged, p+2 and the own
-    // values of p+3 prefetched, voxel p-2 finalised.  GEN: the tile's first
-    // and last planes, with the validity tests.
-    auto plane = [&](int p, auto ROTc, auto GENc) __attribute__((always_inline)) {
-      constexpr int ROT = decltype(ROTc)::value;
+    // One plane p: its 5 x 5 cells added to the voxels p-2 .. p+2, the slot of
+    // p+2 started, plane p+1 staged, p+2 and the own values of p+3 prefetched,
+    // voxel p-2 finalised, the slots moved down.  GEN: the tile's first and last
+    // planes, with the validity tests.
+    auto plane = [&](int p, auto GENc) __attribute__((always_inline)) {
       constexpr bool GEN = decltype(GENc)::value;
-      // Slots of voxels p - 2 (finalised) and p + 2 (started).
-      constexpr int S0 = ROT % 5, S4 = (4 + ROT) % 5;
       const bool pv = !GEN || (p >= 0 && p < nz);
-      // Start voxel p+2 (its own values were prefetched).
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        xcs[S4][q] = ri[q] < 0.f ? ox - 1.f : ox;
-        gis[S4][q] = fabsf(ri[q]);
-        qis[S4][q] = ri[2 + q];
-#pragma unroll
-        for (int j = 0; j < CH; ++j) hn[S4][q][j] = 0.f;
-#pragma unroll
-        for (int j = 0; j < C; ++j) fn[S4][q][j] = 0.f;
-      }
+      // Voxel p+2 starts from its prefetched values; its invariants take the
+      // place of those of voxel p-2.
+      float inv[4];
+      float* const sr = &s_r[wave][bufof(p + 2)][lane * 4];
+      lds_cell_load<4, 4>(sr, inv);
+      __builtin_amdgcn_wave_barrier();
+      lds_cell_store<4, 4>(sr, ri);
+      xcs[4][0] = ri[0] < 0.f ? ox - 1.f : ox;
+      xcs[4][1] = ri[1] < 0.f ? ox - 1.f : ox;
+      if (!GEN || p + 3 <= zhi + 1) load_own(p + 3);
+      __builtin_amdgcn_sched_barrier(0);
       if (pv) {
         const int bp = bufof(p);
         const float* sx = &s_x[wave][bp][own_cell];
         const float* su = &s_u[wave][bp][own_cell * CP];
         float cs[6][C];
-#pragma unroll
-        for (int c = 0; c < 6; ++c)
-#pragma unroll
-          for (int j = 0; j < C; ++j) cs[c][j] = 0.f;
         static_for<0, 5>([&](auto yc) {
           constexpr int dy = decltype(yc)::value - 2;
           static_for<0, 5>([&](auto xc) {
@@ -326,18 +479,24 @@ __global__ __launch_bounds__(64 * kRing2Waves) void k_ifcm_ring2(const LaunchArg
             const float xk = sx[dy * HX + dx];
             float u[C];
             lds_cell_load<C, CP>(su + (dy * HX + dx) * CP, u);
+            // The first cell of a class, and of a slot, starts its sum.
             constexpr int c = cls(ad, bd);
+            constexpr bool first = dy == -(ad > bd ? ad : bd) && dx == -(ad < bd ? ad : bd);
 #pragma unroll
-            for (int j = 0; j < C; ++j) cs[c][j] = fmaf(u[j], u[j], cs[c][j]);
+            for (int j = 0; j < C; ++j) cs[c][j] = first ? u[j] * u[j] : fmaf(u[j], u[j], cs[c][j]);
             static_for<0, 5>([&](auto kc) {
               constexpr int k = decltype(kc)::value;
               constexpr int dz = 2 - k, ed = dz < 0 ? -dz : dz;
               if constexpr (!(dx == 0 && dy == 0 && dz == 0)) {
-                constexpr int q = (ad > bd ? (ad > ed ? ad : ed) : (bd > ed ? bd : ed)) - 1;
-                constexpr int sk = (k + ROT) % 5;
-                const float g = fabsf(xcs[sk][q] - xk);  // eq (6)
+                constexpr bool ring1 = ad <= 1 && bd <= 1 && ed <= 1;
+                const float g = fabsf(xcs[k][ring1 ? 0 : 1] - xk);  // eq (6)
 #pragma unroll
-                for (int j = 0; j < CH; ++j) hn[sk][q][j] = fmaf(u[j], g, hn[sk][q][j]);
+                for (int j = 0; j < CH; ++j) {
+                  if constexpr (ring1)
+                    h1[k][j] = k == 3 && dy == -1 && dx == -1 ? u[j] * g : fmaf(u[j], g, h1[k][j]);
+                  else
+                    h2[k][j] = k == 4 && dy == -2 && dx == -2 ? u[j] * g : fmaf(u[j], g, h2[k][j]);
+                }
               }
             });
           });
@@ -345,47 +504,54 @@ __global__ __launch_bounds__(64 * kRing2Waves) void k_ifcm_ring2(const LaunchArg
           // whole window's, in registers.
           __builtin_amdgcn_sched_barrier(0);
         });
-        // eq (7): the class sums, weighted per slot.
-        static_for<0, 5>([&](auto kc) {
-          constexpr int k = decltype(kc)::value;
-          constexpr int ed = k < 2 ? 2 - k : k - 2, sk = (k + ROT) % 5;
-          static_for<0, 6>([&](auto cc) {
-            constexpr int c = decltype(cc)::value;
-            constexpr int ad = cls_a(c), bd = cls_b(c);
-            if constexpr (!(ad == 0 && bd == 0 && ed == 0)) {
-              constexpr int q = (ad > bd ? (ad > ed ? ad : ed) : (bd > ed ? bd : ed)) - 1;
-              const float wgt = qw(ad * ad + bd * bd + ed * ed);
+        // eq (7): the class sums, weighted by the distance of the slot's plane
+        // (the slots on both sides of the plane share theirs).
 #pragma unroll
-              for (int j = 0; j < C; ++j) fn[sk][q][j] = fmaf(wgt, cs[c][j], fn[sk][q][j]);
-            }
-          });
-        });
+        for (int j = 0; j < C; ++j) {
+          f1[2][j] = fmaf(qw(1), cs[1][j], f1[2][j]);
+          f1[2][j] = fmaf(qw(2), cs[2][j], f1[2][j]);
+          f2[2][j] = fmaf(qw(4), cs[3][j], f2[2][j]);
+          f2[2][j] = fmaf(qw(5), cs[4][j], f2[2][j]);
+          f2[2][j] = fmaf(qw(8), cs[5][j], f2[2][j]);
+          const float n1 = fmaf(qw(3), cs[2][j], fmaf(qw(2), cs[1][j], cs[0][j]));
+          const float n2 = fmaf(qw(9), cs[5][j], fmaf(qw(6), cs[4][j], qw(5) * cs[3][j]));
+          f1[1][j] += n1;
+          f1[3][j] = n1;
+          f2[1][j] += n2;
+          f2[3][j] += n2;
+          float n3 = fmaf(qw(6), cs[2][j], fmaf(qw(5), cs[1][j], qw(4) * cs[0][j]));
+          n3 = fmaf(qw(12), cs[5][j], fmaf(qw(9), cs[4][j], fmaf(qw(8), cs[3][j], n3)));
+          f2[0][j] += n3;
+          f2[4][j] = n3;
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+          if (j < CH) h1[3][j] = h2[4][j] = 0.f;
+          f1[3][j] = f2[4][j] = 0.f;
+        }
       }
       __builtin_amdgcn_sched_barrier(0);
       if (!GEN || p + 1 <= zhi + 1) {
         store_cells(bufof(p + 1));
         if (!GEN || p + 2 <= zhi + 1) load_cells(p + 2);
       }
-      if (!GEN || p + 3 <= zhi + 1) load_own(p + 3);
-      if (!GEN || (p - 2 >= zlo && p - 2 < zhi)) finalize(p - 2, std::integral_constant<int, S0>{}, bufof(p - 2));
+      if (!GEN || (p - 2 >= zlo && p - 2 < zhi)) finalize(p - 2, bufof(p - 2), inv);
       __builtin_amdgcn_sched_barrier(0);
-    };
-    auto shift = [&]() __attribute__((always_inline)) {
 #pragma unroll
-      for (int s5 = 0; s5 < 4; ++s5)
+      for (int k = 0; k < 4; ++k) {
+        xcs[k][0] = xcs[k + 1][0];
+        xcs[k][1] = xcs[k + 1][1];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          xcs[s5][q] = xcs[s5 + 1][q];
-          gis[s5][q] = gis[s5 + 1][q];
-          qis[s5][q] = qis[s5 + 1][q];
-#pragma unroll
-          for (int j = 0; j < CH; ++j) hn[s5][q][j] = hn[s5 + 1][q][j];
-#pragma unroll
-          for (int j = 0; j < C; ++j) fn[s5][q][j] = fn[s5 + 1][q][j];
+        for (int j = 0; j < C; ++j) {
+          if (j < CH) h2[k][j] = h2[k + 1][j];
+          f2[k][j] = f2[k + 1][j];
+          if (k < 3 && j < CH) h1[k][j] = h1[k + 1][j];
+          if (k < 3) f1[k][j] = f1[k + 1][j];
         }
+      }
     };
 
-    using I0 = std::integral_constant<int, 0>;
     using Gen = std::integral_constant<bool, true>;
     using Steady = std::integral_constant<bool, false>;
 
@@ -396,20 +562,11 @@ __global__ __launch_bounds__(64 * kRing2Waves) void k_ifcm_ring2(const LaunchArg
     load_cells(zlo - 1);
     load_own(zlo);
     int p = zlo - 2;
-    for (; p < zlo + 2; ++p) {
-      plane(p, I0{}, Gen{});
-      shift();
-    }
-    // Interior planes: every per-plane test is true (the loads still test
-    // the plane range).  tests/test_plane_walk.py replays this walk.
-    for (; p + 4 <= zhi; ++p) {
-      plane(p, I0{}, Steady{});
-      shift();
-    }
-    for (; p <= zhi + 1; ++p) {
-      plane(p, I0{}, Gen{});
-      shift();
-    }
+    for (; p < zlo + 2; ++p) plane(p, Gen{});
+    // Interior planes: every per-plane test is true (the loads still clamp
+    // the plane).  tests/test_plane_walk.py replays this walk.
+    for (; p + 4 <= zhi; ++p) plane(p, Steady{});
+    for (; p <= zhi + 1; ++p) plane(p, Gen{});
     wave_tile_store<NV>(pr.partials, tile, vd.tiles, acc);
   }
 }
