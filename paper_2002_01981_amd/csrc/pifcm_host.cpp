@@ -82,7 +82,10 @@ struct pifcm_ctx {
   double step_ms = 0.0;
   int64_t step_launches = 0;
   std::map<std::tuple<int, int, int, int, int>, TileShape> tuned;  // (C, m2, nx, ny, nz)
-  int occ_gather[kMaxC + 1][2][2][2] = {};  // resident work groups per CU of the fused step (4 waves)
+  // Resident work groups (4 waves) per CU: of the fused step by particles per
+  // item and runs, of the general-neighbourhood kernels by runs.
+  int occ_gather[kMaxC + 1][2][2][2] = {};
+  int occ_ring[kMaxC + 1][2][2][2] = {};  // [C][m2][two rings][runs]
   char arch[64] = "unknown";  // device architecture (tuning cache key)
 };
 
@@ -268,11 +271,15 @@ double launch_cost(double tiles, double planes, double longest, double resident,
   return passes / simds + 2.0 * (std::ceil(tiles / resident) * mean + (longest + 4.0 - mean));
 }
 
-// Waves of the fused step the card keeps resident (4 waves per work group,
+// Waves of the step of `kind` the card keeps resident (4 waves per work group,
 // pt particles per item; runs: tiles of several runs of planes).
-double resident_waves(pifcm_ctx* ctx, int C, bool m2, int pt = 1, bool runs = false) {
-  int& occ = ctx->occ_gather[std::max(0, std::min(C, kMaxC))][m2 ? 1 : 0][pt - 1][runs ? 1 : 0];
-  if (occ == 0) occ = std::max(1, gather_occupancy(C, 4, pt, m2, true, runs));
+double resident_waves(pifcm_ctx* ctx, int kind, int C, bool m2, int pt = 1, bool runs = false) {
+  const int c = std::max(0, std::min(C, kMaxC)), im = m2 ? 1 : 0, ir = runs ? 1 : 0;
+  int& occ = is_ring(kind) ? ctx->occ_ring[c][im][kind == kRing2 ? 1 : 0][ir] : ctx->occ_gather[c][im][pt - 1][ir];
+  if (occ == 0)
+    occ = std::max(1, kind == kRing    ? ring_occupancy(C, m2, true)
+                      : kind == kRing2 ? ring2_occupancy(C, m2, true, runs)
+                                       : gather_occupancy(C, 4, pt, m2, true, runs));
   return 4.0 * occ * ctx->num_cu;
 }
 
@@ -284,34 +291,59 @@ double resident_waves(pifcm_ctx* ctx, int C, bool m2, int pt = 1, bool runs = fa
 // One step of a lone pair: 181x217x181, C = 4: 46 planes, 82 us (23: 88 us,
 // 61: 91 us, 181: 190 us); 162x181x75, C = 3, m = 2.5: 11 planes, 38 us (38
 // planes, the least with a floor of 32: 50 us); 32x32x8: 1 plane, 10 us (8
-// planes: 15 us).
-int default_zc(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v) {
-  const double R = resident_waves(ctx, C, m2), simds = 4.0 * ctx->num_cu;
+// planes: 15 us).  The two-ring kernel follows the same costs (one solve of 20
+// iterations, per iteration: 181x217x181: 61 planes, 193 us, 32: 213 us;
+// 95x21x63: 3 planes, 27 us, 32: 84 us).
+int default_zc(pifcm_ctx* ctx, int kind, int C, bool m2, const pifcm_volume& v) {
+  const double R = resident_waves(ctx, kind, C, m2), simds = 4.0 * ctx->num_cu;
   const double txy = (double)((v.nx + kWaveTileX - 1) / kWaveTileX) * ((v.ny + kWaveTileY - 1) / kWaveTileY);
-  int best = v.nz;
-  double best_cost = -1.0;
-  for (int k = 1; k <= v.nz; ++k) {
-    const int zc = (v.nz + k - 1) / k;
-    if (k > 1 && zc == (v.nz + k - 2) / (k - 1)) continue;  // the depth of k - 1
+  auto cost_of = [&](int zc) {
     const double nt = txy * ((v.nz + zc - 1) / zc);
-    const double cost = launch_cost(nt, nt * zc, zc, R, simds);
-    if (best_cost < 0.0 || cost < best_cost) {
+    return launch_cost(nt, nt * zc, zc, R, simds);
+  };
+  int best = v.nz;
+  double best_cost = cost_of(v.nz);
+  for (int k = 2; k <= v.nz; ++k) {
+    const int zc = (v.nz + k - 1) / k;
+    const double cost = cost_of(zc);
+    if (cost < best_cost) {
       best_cost = cost;
       best = zc;
     }
   }
+  // A batched launch stores its sums once per run: of shallow runs, the deepest
+  // (up to eight planes) that costs a lone pair at most a twentieth more.
+  for (int k = 1; (v.nz + k - 1) / k > best; ++k) {
+    const int zc = (v.nz + k - 1) / k;
+    if (zc <= 8 && cost_of(zc) <= 1.05 * best_cost) return zc;
+  }
   return best;
 }
 
-// Planes per tile of the general-neighbourhood kernels and of the adjoint's
-// forward pass: of the depths ceil(nz / k) and 32 that are at least min(nz, 32)
-// deep, the one with the fewest rounds of one pair's tiles on the fused step's
-// resident waves times (depth + 4); the deeper one on a tie.  The adjoint keeps
-// it although other depths are faster on small volumes: the gradient at the
+// Planes per tile of the table walk (kRing) in a launch whose tiles hold
+// `planes` planes in all: as few as leave four rounds of tiles (a walk is long and
+// bound by latency, so every wave that can be resident must be, and evenly), at
+// most eight (from there on nothing is gained by walking next to cells that the
+// caches still hold).  V = 3, C = 4, us per iteration of a solve: 95x21x63: 1
+// plane 152, 32 planes 3717; 100x120x130: 1 plane 653, 2 719, 8 1178, 32 4025; of
+// a swarm: 37x56x49 x 64: 1 plane 3494, 4 2929, 8 3545, 32 4917; 117x202x89 x 8: 1
+// plane 8641, 8 7381, 32 9068.
+int ring_depth(pifcm_ctx* ctx, int C, bool m2, double planes) {
+  return (int)std::max(1.0, std::min(8.0, planes / (4.0 * resident_waves(ctx, kRing, C, m2))));
+}
+int ring_zc(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v) {
+  const double txy = (double)((v.nx + kWaveTileX - 1) / kWaveTileX) * ((v.ny + kWaveTileY - 1) / kWaveTileY);
+  return std::min(v.nz, ring_depth(ctx, C, m2, txy * v.nz));
+}
+
+// Planes per tile of the adjoint's forward pass: of the depths ceil(nz / k) and
+// 32 that are at least min(nz, 32) deep, the one with the fewest rounds of one
+// pair's tiles on the fused step's resident waves times (depth + 4); the deeper
+// one on a tie.  The adjoint keeps it although other depths are faster on small volumes: the gradient at the
 // initial centres is what is left of sums that cancel to 1e-5 of their terms,
 // and the order of the forward pass's sums shows in it.
 int floored_zc(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v) {
-  const long R = (long)resident_waves(ctx, C, m2);
+  const long R = (long)resident_waves(ctx, kGather, C, m2);
   const long txy = (long)((v.nx + kWaveTileX - 1) / kWaveTileX) * ((v.ny + kWaveTileY - 1) / kWaveTileY);
   const int floor_zc = std::min(v.nz, 32);
   int best = v.nz;
@@ -338,9 +370,10 @@ TileShape shape_for(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v, int k
   auto it = ctx->tuned.find(std::make_tuple(C, (int)m2, v.nx, v.ny, v.nz));
   if (it != ctx->tuned.end()) t = it->second;
   if (t.zc <= 0) {
-    const bool floored = adjoint || is_ring(kind);
-    t.deep = kind == kGather && !floored;
-    t.zc = floored ? floored_zc(ctx, C, m2, v) : default_zc(ctx, C, m2, v);
+    t.deep = !adjoint && kind != kFcm && kind != kFcmStore;
+    t.zc = adjoint         ? floored_zc(ctx, C, m2, v)
+           : kind == kRing ? ring_zc(ctx, C, m2, v)
+                           : default_zc(ctx, kind == kRing2 ? kRing2 : kGather, C, m2, v);
   }
   t.zc = std::max(1, std::min(t.zc, max_zc(v, C)));
   return t;
@@ -509,7 +542,7 @@ int occupancy_of(int kind, int C, int nw, bool m2, bool step, int pt = 1, bool r
   if (kind == kFcm) return fcm_x_occupancy(C, m2, step);
   if (kind == kFcmStore) return fcm_occupancy(C, m2, step);
   if (kind == kRing) return ring_occupancy(C, m2, step);
-  if (kind == kRing2) return ring2_occupancy(C, m2, step);
+  if (kind == kRing2) return ring2_occupancy(C, m2, step, runs);
   return gather_occupancy(C, nw, pt, m2, step, runs);
 }
 
@@ -518,26 +551,35 @@ int occupancy_of(int kind, int C, int nw, bool m2, bool step, int pt = 1, bool r
 int runs_at(const pifcm_volume& v, const TileShape& ts, int C, int depth) {
   if (!ts.deep) return 1;
   const int whole = (v.nz + ts.zc - 1) / ts.zc;
-  return std::max(1, std::min({(2 * depth + ts.zc) / (2 * ts.zc), whole, deepest_zc(v, C) / ts.zc}));
+  const int tiles = std::max(1, (2 * v.nz + depth) / (2 * depth));  // per column, as even as runs allow
+  return std::max(1, std::min((whole + tiles - 1) / tiles, deepest_zc(v, C) / ts.zc));
 }
 
 // Tile depth of a batched launch of P particles, pt per item, per volume: the
-// cheapest by launch_cost (each volume takes the nearest number of its default
-// runs, up to whole columns).  With many pairs every round is full and whole
+// cheapest by launch_cost (each volume's columns are cut into as many tiles of
+// whole runs as come nearest to it).  With many pairs every round is full and whole
 // columns win (fewer tile starts and halo planes: six ragged volumes x 64
 // particles, 13.3 ms per launch; 13.8 ms with a lone pair's depths).
 struct LaunchDepth {
   int depth;
   double rounds;  // of the launch's tiles on the resident waves
 };
-LaunchDepth launch_depth(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume* vols,
+LaunchDepth launch_depth(pifcm_ctx* ctx, int kind, int C, bool m2, const pifcm_volume* vols,
                          const std::vector<TileShape>& shapes, int P, int pt) {
-  const double R = resident_waves(ctx, C, m2, pt, true), simds = 4.0 * ctx->num_cu;
+  const double R = resident_waves(ctx, kind, C, m2, pt, true), simds = 4.0 * ctx->num_cu;
   const double groups = (P + pt - 1) / pt;
   int deepest = 1;
   for (size_t b = 0; b < shapes.size(); ++b) deepest = std::max(deepest, vols[b].nz);
   LaunchDepth best{1, 0.0};
   double best_cost = -1.0;
+  if (kind == kRing) {
+    double planes = 0.0;
+    for (size_t b = 0; b < shapes.size(); ++b)
+      planes += groups * ((vols[b].nx + kWaveTileX - 1) / kWaveTileX) *
+                ((vols[b].ny + kWaveTileY - 1) / kWaveTileY) * vols[b].nz;
+    best.depth = ring_depth(ctx, C, m2, planes);
+    return best;
+  }
   for (int depth = 1;; depth = std::min(deepest, depth + std::max(1, depth / 16))) {
     double tiles = 0.0, planes = 0.0, longest = 0.0;
     for (size_t b = 0; b < shapes.size(); ++b) {
@@ -571,7 +613,7 @@ int particles_per_item(pifcm_ctx* ctx, int kind, int C, bool m2, const pifcm_vol
                        const std::vector<TileShape>& shapes, int P, float eps) {
   if (kind != kGather || C != 4 || P < 2) return 1;
   if (shapes[0].pt > 0) return std::min(shapes[0].pt, 2);
-  return eps == 0.f && launch_depth(ctx, C, m2, vols, shapes, P, 1).rounds >= 4.0 ? 2 : 1;
+  return eps == 0.f && launch_depth(ctx, kind, C, m2, vols, shapes, P, 1).rounds >= 4.0 ? 2 : 1;
 }
 
 // Work items a work group takes at a time: one per wave for the tiled
@@ -1370,7 +1412,7 @@ pifcm_status swarm_core(pifcm_ctx* ctx, const pifcm_volume* vols, int32_t B, con
   int pt = 1, depth = 0;
   if (mode == PIFCM_SWARM_BATCHED) {
     pt = particles_per_item(ctx, kind, C, m2, vols, shapes, P, p->eps);
-    depth = launch_depth(ctx, C, m2, vols, shapes, P, pt).depth;
+    depth = launch_depth(ctx, kind, C, m2, vols, shapes, P, pt).depth;
   }
   std::vector<VolDev> vh(B);
   size_t ubytes = 0, slots = 0;

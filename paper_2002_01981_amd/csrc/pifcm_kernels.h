@@ -37,7 +37,7 @@ constexpr int kRing2Waves = 4;
 // Fused step for the two Chebyshev rings of the 5x5x5 cube, C <= 4 (reads
 // VolDev::rinv, the invariants of launch_ring2_invariants).
 hipError_t launch_ring2(int C, const LaunchArgs& a, int grid, bool m2, bool step, hipStream_t s);
-int ring2_occupancy(int C, bool m2, bool step);
+int ring2_occupancy(int C, bool m2, bool step, bool runs = false);
 hipError_t launch_ring2_invariants(const float* x, float* rinv, int nx, int ny, int nz, int q2_sqdist,
                                    hipStream_t s);
 // IFCM step / objective for general neighbourhoods (a.ring, a.W).

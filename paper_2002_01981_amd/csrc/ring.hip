@@ -7,10 +7,12 @@
 // a ring without in-volume cells) and the ratio of eq (7), and adds them with
 // the weight W_r of eq (10).  Then eqs (4), (1), (2) and (3) as in the fused
 // 3x3x3 step.  Work is decomposed like the fused step: a wave owns a tile of
-// 16 x 4 columns and zc planes and its lanes walk their columns along z, so
-// the cells a wave reads (its tile plus the reach of the table in x, y and
-// z) stay in the L1 cache while it moves one plane at a time; neighbours are
-// read from global memory through the caches.
+// 16 x 4 columns and zc planes and its lanes walk their columns along z;
+// neighbours are read from global memory through the caches, which hold most of
+// them where the tile is several planes deep.  Bound by the latency of a chain
+// of hundreds of cached loads per voxel until the resident waves hide it, then
+// by the caches: tiles are shallow (how shallow is the host's rule, with its
+// figures).
 #include "common.h"
 #include "pifcm_kernels.h"
 
@@ -54,7 +56,19 @@ __global__ __launch_bounds__(64 * kRingWaves) void k_ifcm_ring(const LaunchArgs 
     float acc[NV];
 #pragma unroll
     for (int k = 0; k < NV; ++k) acc[k] = 0.f;
-    for (int vz = zlo; vz < zhi && active; ++vz) {
+    // The sums of each run of sc planes go to a slot of their own (as in the
+    // fused step).
+    const int txy = vd.ntx * vd.nty;
+    int slot = tile + tzi * (vd.zc / vd.sc - 1) * txy, left = vd.sc;
+    auto finished = [&](int z) __attribute__((always_inline)) {
+      if (--left > 0 && z + 1 < zhi) return;
+      wave_tile_store<NV>(pr.partials, slot, vd.slots, acc);
+#pragma unroll
+      for (int k = 0; k < NV; ++k) acc[k] = 0.f;
+      slot += txy;
+      left = vd.sc;
+    };
+    auto voxel = [&](int vz) __attribute__((always_inline)) {
       const size_t i = ((size_t)vz * ny + vy) * nx + vx;
       const float xv = X[i];
       float H[C], F[C];
@@ -131,8 +145,11 @@ __global__ __launch_bounds__(64 * kRingWaves) void k_ifcm_ring(const LaunchArgs 
       } else {
         acc[0] += Jv;
       }
+    };
+    for (int vz = zlo; vz < zhi; ++vz) {
+      if (active) voxel(vz);
+      finished(vz);
     }
-    wave_tile_store<NV>(pr.partials, tile, vd.tiles, acc);
   }
 }
 

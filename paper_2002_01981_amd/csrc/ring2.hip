@@ -269,7 +269,9 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 }  // namespace r2
 
-template <int C, bool M2, bool STEP>
+// RUNS: tiles may hold several runs of VolDev::sc planes, whose sums are kept
+// apart (as in the fused step).
+template <int C, bool M2, bool STEP, bool RUNS>
 __global__ __launch_bounds__(64 * kRing2Waves, 2) void k_ifcm_ring2(const LaunchArgs a) {
   static_assert(C >= 2 && C <= 4, "the fused two-ring step holds C <= 4 clusters");
   using namespace r2;
@@ -555,6 +557,19 @@ __global__ __launch_bounds__(64 * kRing2Waves, 2) void k_ifcm_ring2(const Launch
     using Gen = std::integral_constant<bool, true>;
     using Steady = std::integral_constant<bool, false>;
 
+    // The sums of a finished run of sc planes go to its slot (slots are
+    // numbered like tiles of sc planes); without RUNS a tile is one run.
+    const int txy = vd.ntx * vd.nty;
+    int slot = RUNS ? tile + tzi * (vd.zc / vd.sc - 1) * txy : tile, left = vd.sc;
+    auto finished = [&](int z) __attribute__((always_inline)) {
+      if (RUNS && --left > 0 && z + 1 < zhi) return;
+      wave_tile_store<NV>(pr.partials, slot, vd.slots, acc);
+#pragma unroll
+      for (int k = 0; k < NV; ++k) acc[k] = 0.f;
+      slot += txy;
+      left = vd.sc;
+    };
+
     // Prologue: plane zlo-2 staged, zlo-1 prefetched, the own values of zlo
     // (the voxel that enters at plane zlo-2) prefetched.
     load_cells(zlo - 2);
@@ -565,44 +580,49 @@ __global__ __launch_bounds__(64 * kRing2Waves, 2) void k_ifcm_ring2(const Launch
     for (; p < zlo + 2; ++p) plane(p, Gen{});
     // Interior planes: every per-plane test is true (the loads still clamp
     // the plane).  tests/test_plane_walk.py replays this walk.
-    for (; p + 4 <= zhi; ++p) plane(p, Steady{});
-    for (; p <= zhi + 1; ++p) plane(p, Gen{});
-    wave_tile_store<NV>(pr.partials, tile, vd.tiles, acc);
+    for (; p + 4 <= zhi; ++p) {
+      plane(p, Steady{});
+      if constexpr (RUNS) finished(p - 2);
+    }
+    for (; p <= zhi + 1; ++p) {
+      plane(p, Gen{});
+      if constexpr (RUNS) finished(p - 2);
+    }
+    if constexpr (!RUNS) finished(zhi - 1);
   }
 }
 
-template <int C, bool M2>
-static hipError_t launch_ring2_ct(const LaunchArgs& a, int grid, bool step, hipStream_t s) {
-  if (step) hipLaunchKernelGGL((k_ifcm_ring2<C, M2, true>), dim3(grid), dim3(64 * kRing2Waves), 0, s, a);
-  else hipLaunchKernelGGL((k_ifcm_ring2<C, M2, false>), dim3(grid), dim3(64 * kRing2Waves), 0, s, a);
-  return hipGetLastError();
+template <int C, bool M2, bool RUNS>
+static const void* ring2_kernel(bool step) {
+  return step ? reinterpret_cast<const void*>(&k_ifcm_ring2<C, M2, true, RUNS>)
+              : reinterpret_cast<const void*>(&k_ifcm_ring2<C, M2, false, RUNS>);
 }
-
-template <int C, bool M2>
-static int occ_ring2_ct(bool step) {
-  int n = 0;
-  const void* f = step ? reinterpret_cast<const void*>(&k_ifcm_ring2<C, M2, true>)
-                       : reinterpret_cast<const void*>(&k_ifcm_ring2<C, M2, false>);
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 64 * kRing2Waves, 0) != hipSuccess) n = 1;
-  return std::max(1, n);
+template <int C>
+static const void* ring2_kernel(bool m2, bool step, bool runs) {
+  if (m2) return runs ? ring2_kernel<C, true, true>(step) : ring2_kernel<C, true, false>(step);
+  return runs ? ring2_kernel<C, false, true>(step) : ring2_kernel<C, false, false>(step);
+}
+static const void* ring2_kernel(int C, bool m2, bool step, bool runs) {
+  switch (C) {
+    case 2: return ring2_kernel<2>(m2, step, runs);
+    case 3: return ring2_kernel<3>(m2, step, runs);
+    case 4: return ring2_kernel<4>(m2, step, runs);
+    default: return nullptr;
+  }
 }
 
 hipError_t launch_ring2(int C, const LaunchArgs& a, int grid, bool m2, bool step, hipStream_t s) {
-  switch (C) {
-    case 2: return m2 ? launch_ring2_ct<2, true>(a, grid, step, s) : launch_ring2_ct<2, false>(a, grid, step, s);
-    case 3: return m2 ? launch_ring2_ct<3, true>(a, grid, step, s) : launch_ring2_ct<3, false>(a, grid, step, s);
-    case 4: return m2 ? launch_ring2_ct<4, true>(a, grid, step, s) : launch_ring2_ct<4, false>(a, grid, step, s);
-    default: return hipErrorInvalidValue;
-  }
+  const void* f = ring2_kernel(C, m2, step, a.runs != 0);
+  if (!f) return hipErrorInvalidValue;
+  void* args[] = {const_cast<LaunchArgs*>(&a)};
+  return hipLaunchKernel(f, dim3(grid), dim3(64 * kRing2Waves), args, 0, s);
 }
 
-int ring2_occupancy(int C, bool m2, bool step) {
-  switch (C) {
-    case 2: return m2 ? occ_ring2_ct<2, true>(step) : occ_ring2_ct<2, false>(step);
-    case 3: return m2 ? occ_ring2_ct<3, true>(step) : occ_ring2_ct<3, false>(step);
-    case 4: return m2 ? occ_ring2_ct<4, true>(step) : occ_ring2_ct<4, false>(step);
-    default: return 1;
-  }
+int ring2_occupancy(int C, bool m2, bool step, bool runs) {
+  int n = 0;
+  const void* f = ring2_kernel(C, m2, step, runs);
+  if (!f || hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 64 * kRing2Waves, 0) != hipSuccess) n = 1;
+  return std::max(1, n);
 }
 
 }  // namespace pifcm

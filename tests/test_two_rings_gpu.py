@@ -1,11 +1,11 @@
 """The two-ring kernels (V = 2, C <= 4) where their tiles end: the step's tiles
 of 16 x 4 columns with a halo of two, the invariants' tiles of 60 x 2 columns
 and runs of planes, volumes smaller than the neighbourhood, flat rings, both
-eq (7) weightings.
+eq (7) weightings; and tile depth by launch for every general neighbourhood.
 
 Bounds: TOL of gpu_util against the FP64 oracle after one iteration from given
-float32 memberships and centres (the bound
-of test_ring_gpu.py).
+float32 memberships and centres (the bound of test_ring_gpu.py).  Sums are kept
+per run of a volume's default planes, so a swarm has the bits of lone solves.
 """
 import numpy as np
 import pytest
@@ -65,3 +65,23 @@ def test_steps_at_tile_edges(ctx, shape, C, m, flags, flat):
     assert rel(g["c"], o["c"]) <= TOL
     assert abs(g["J"] - o["J"]) <= TOL * abs(o["J"])
     assert rel(g["J_hist"], o["J_hist"]) <= TOL
+
+
+# One plane; a last run shorter than the others; tiles of several runs beside
+# volumes of one tile.
+@pytest.mark.parametrize("shapes,P", [([(1, 9, 20)], 300), ([(23, 17, 66), (8, 32, 32), (7, 5, 18)], 70),
+                                      ([(37, 60, 90)], 24)])
+@pytest.mark.parametrize("C,V,flags", [(4, 2, 0), (3, 2, Q2), (5, 2, 0), (4, 3, 1)])
+def test_swarm_equals_lone_solves(ctx, shapes, P, C, V, flags):
+    from paper_2002_01981_amd import Params
+    rng = np.random.default_rng(73)
+    xs = [dev(_volume(sh, 74 + i, False)) for i, sh in enumerate(shapes)]
+    U0 = [dev(random_memberships_f32(rng, int(np.prod(sh)), C)) for sh in shapes]
+    c0 = np.stack([np.linspace(0.15, 0.85, C).astype(np.float32)] * len(shapes))
+    parts = (rng.random((P, 2)) * 0.5).astype(np.float32)
+    p = Params(C=C, V=V, eps=0.0, max_iter=2, flags=flags)
+    bat = ctx.swarm_evaluate(xs, p, parts, c0, U0)
+    for b in range(len(shapes)):
+        for q in (0, P // 2, P - 1):
+            s = ctx.ifcm_solve(xs[b], p, float(parts[q][0]), float(parts[q][1]), c0[b], U_in=U0[b])
+            assert s["J"] == bat["fitness"][b, q] and np.array_equal(s["c"], bat["centres"][b, q])
