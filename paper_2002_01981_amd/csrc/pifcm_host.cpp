@@ -336,7 +336,8 @@ int ring_zc(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v) {
   return std::min(v.nz, ring_depth(ctx, C, m2, txy * v.nz));
 }
 
-// Planes per tile of the adjoint's forward pass: of the depths ceil(nz / k) and
+// Planes per tile of the adjoint's forward pass (and of an allocation-free solve
+// whose default tiles leave too many sums for the scratch array): of the depths ceil(nz / k) and
 // 32 that are at least min(nz, 32) deep, the one with the fewest rounds of one
 // pair's tiles on the fused step's resident waves times (depth + 4); the deeper
 // one on a tie.  The adjoint keeps it although other depths are faster on small volumes: the gradient at the
@@ -365,13 +366,14 @@ int floored_zc(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v) {
   return best;
 }
 
-TileShape shape_for(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v, int kind, bool adjoint = false) {
+// floored: the adjoint's forward pass and a solve whose sums must stay few.
+TileShape shape_for(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v, int kind, bool floored = false) {
   TileShape t;
   auto it = ctx->tuned.find(std::make_tuple(C, (int)m2, v.nx, v.ny, v.nz));
   if (it != ctx->tuned.end()) t = it->second;
   if (t.zc <= 0) {
-    t.deep = !adjoint && kind != kFcm && kind != kFcmStore;
-    t.zc = adjoint         ? floored_zc(ctx, C, m2, v)
+    t.deep = !floored && kind != kFcm && kind != kFcmStore;
+    t.zc = floored         ? floored_zc(ctx, C, m2, v)
            : kind == kRing ? ring_zc(ctx, C, m2, v)
                            : default_zc(ctx, kind == kRing2 ? kRing2 : kGather, C, m2, v);
   }
@@ -1084,8 +1086,9 @@ struct SolveWs {
 
 // Tile slots of a solve over planes [zbeg, zend) (the larger of the tiled and
 // pointwise decompositions).
-int solve_slots(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_params* p, int kind, int zbeg, int zend) {
-  const VolDev v = make_vol(*vol, nullptr, shape_for(ctx, p->C, p->m == 2.0f, *vol, kind), zbeg, zend);
+int solve_slots(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_params* p, int kind, int zbeg, int zend,
+                bool floored = false) {
+  const VolDev v = make_vol(*vol, nullptr, shape_for(ctx, p->C, p->m == 2.0f, *vol, kind, floored), zbeg, zend);
   return std::max(v.slots, v.tiles1d);
 }
 
@@ -1095,14 +1098,14 @@ pifcm_status solve_run(pifcm_ctx* ctx, const SolveWs& ws, const pifcm_volume* vo
                        const pifcm_params* p, float lambda, float xi, const float* centres_in,
                        const float* U_in, float* U_out, float* centres_out, uint8_t* labels_out,
                        double* J_out, int32_t* iters_out, double* J_hist_out, int zbeg, int zend,
-                       bool fcm_sorted = false) {
+                       bool fcm_sorted = false, bool floored = false) {
   const bool slab = zbeg > 0 || zend < vol->nz;
   const int C = p->C;
   const bool m2 = p->m == 2.0f;
   const int kind = kind_of(p, lambda == 0.0f && xi == 0.0f);
   const size_t N = nvox(*vol);
   const Control dev{ws.control, 1}, host{ws.stage, 1};
-  const TileShape ts = shape_for(ctx, C, m2, *vol, kind);
+  const TileShape ts = shape_for(ctx, C, m2, *vol, kind, floored);
   const VolDev vh = make_vol(*vol, ws.invg, ts, zbeg, zend, kind == kRing2 ? ws.rinv : nullptr);
   PairDev pr{};
   pr.U0 = U_in || kind == kFcm ? U_in : ws.ubuf;
@@ -1292,14 +1295,22 @@ pifcm_status ifcm_solve_noalloc(pifcm_ctx* ctx, const pifcm_volume* vol, const p
   const int C = p->C;
   const size_t N = nvox(*vol);
   const size_t Np = (N + 63) / 64 * 64;
-  const int slots = solve_slots(ctx, vol, p, kGather, 0, vol->nz);
   auto al = [](size_t b) { return (b + 255) / 256 * 256; };
   const size_t o_invg = 0;
   const size_t o_ubuf = o_invg + al(Np * sizeof(float));
   const size_t o_part = o_ubuf + al(N * C * sizeof(float));
-  const size_t o_st = o_part + al((size_t)slots * (2 * C + 1) * sizeof(float));
-  const size_t o_jh = o_st + al(control_bytes(1, 1));
-  const size_t need = o_jh + al((size_t)std::max(1, p->max_iter) * sizeof(double));
+  size_t o_st = 0, o_jh = 0, need = 0;
+  // Where the default tiles' sums are the few thousandths too many, deeper
+  // tiles with fewer sums do.
+  bool floored = false;
+  for (int pass = 0; pass < 2; ++pass) {
+    floored = pass == 1;
+    const int slots = solve_slots(ctx, vol, p, kGather, 0, vol->nz, floored);
+    o_st = o_part + al((size_t)slots * (2 * C + 1) * sizeof(float));
+    o_jh = o_st + al(control_bytes(1, 1));
+    need = o_jh + al((size_t)std::max(1, p->max_iter) * sizeof(double));
+    if (need <= kScratchBytes) break;
+  }
   if (need > kScratchBytes)
     return fail(ctx, PIFCM_E_INVALID,
                 "ifcm_solve_noalloc: this solve needs %zu bytes of scratch (N = %zu, C = %d, max_iter = %d), "
@@ -1324,7 +1335,7 @@ pifcm_status ifcm_solve_noalloc(pifcm_ctx* ctx, const pifcm_volume* vol, const p
   double J = 0.0;
   int32_t T = 0;
   TRY(solve_run(ctx, ws, vol, p, lambda, xi, centres_in, U_in, U_out, c_tmp, labels_out, &J, &T,
-                J_hist_out, 0, vol->nz));
+                J_hist_out, 0, vol->nz, false, floored));
   if (centres_out) std::memcpy(centres_out, c_tmp, sizeof(float) * C);
   if (J_out) *J_out = J;
   if (iters_out) *iters_out = T;
