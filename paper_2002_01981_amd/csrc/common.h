@@ -72,6 +72,14 @@ __device__ __forceinline__ gfloat* at_lane(gfloat* base, uint32_t& off) {
   return at_byte(base, off);
 }
 
+// The value of the lane before / after (0 past the wave's ends).
+__device__ __forceinline__ float from_left_lane(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x138, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float from_right_lane(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x130, 0xf, 0xf, true));
+}
+
 __device__ __forceinline__ int vol_of_item(const LaunchArgs& a, int it) {
   int b = 0;
   while (b + 1 < a.nvol && it >= a.item_begin[b + 1]) ++b;

@@ -57,7 +57,7 @@ struct PairDev {
   float* Ua;           // U^(t) for odd t (plain FCM: U^(T), or NULL)
   float* Ub;           // U^(t) for even t >= 2
   SolveState* st;
-  float* partials;     // [tiles][2C + 1] per-tile sums of one launch
+  float* partials;     // [2C + 1][slots] sums of one launch by tile (of sc planes)
 };
 
 // General neighbourhoods (rings V >= 1, eqs (5), (7), (9), (10)): offsets

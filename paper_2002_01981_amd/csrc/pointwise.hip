@@ -263,13 +263,6 @@ __global__ __launch_bounds__(256) void k_fcm_point(const LaunchArgs a) {
 // 26 neighbours through the caches with a test each took 108 us.
 constexpr int kInvCols = 62, kInvRows = 4;
 
-__device__ __forceinline__ float from_left_lane(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x138, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float from_right_lane(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x130, 0xf, 0xf, true));
-}
-
 __global__ __launch_bounds__(256) void k_invariants(const float* __restrict__ x, float* __restrict__ invg,
                                                     int nx, int ny, int nz, int zbeg, int zend, int zc,
                                                     int nitems, int* __restrict__ flag) {

@@ -51,12 +51,6 @@ namespace pifcm {
 constexpr int kInv2Cols = 60, kInv2Rows = 2;
 
 namespace {
-__device__ __forceinline__ float lane_before(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x138, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float lane_after(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x130, 0xf, 0xf, true));
-}
 // Sums of 1, d^2 and d^4 over the offsets |d| <= r of one axis that stay inside
 // the volume (r = 1, 2).
 struct Axis {
@@ -150,10 +144,10 @@ __global__ __launch_bounds__(256) void k_ring2_invariants(const float* __restric
 #pragma unroll
       for (int r = 0; r < R + 4; ++r) {
         c[r][2] = xs[2][r];
-        c[r][1] = lane_before(c[r][2]);
-        c[r][0] = lane_before(c[r][1]);
-        c[r][3] = lane_after(c[r][2]);
-        c[r][4] = lane_after(c[r][3]);
+        c[r][1] = from_left_lane(c[r][2]);
+        c[r][0] = from_left_lane(c[r][1]);
+        c[r][3] = from_right_lane(c[r][2]);
+        c[r][4] = from_right_lane(c[r][3]);
       }
 #pragma unroll
       for (int r = 0; r < R; ++r)
