@@ -67,10 +67,12 @@ constexpr int kNHalo = kNCell - 64;            // 44 halo cells, one per lane
 
 // The registers are held to what keeps gather_waves waves on a SIMD (some
 // instances come out a few above the step; C = 11: one wave 518 us, two, with
-// a few spilled registers, 387 us for 20 particles on 120x100x50).
-template <int C, int PT>
+// a few spilled registers, 387 us for 20 particles on 120x100x50).  Two particles
+// per item in tiles of one run fit two waves by themselves and are left to the
+// compiler (0: six ragged volumes x 64, 128 planes, 11.84 against 11.68 ms).
+template <int C, int PT, bool RUNS>
 constexpr int gather_waves() {
-  return PT > 1 ? 2 : C == 2 ? 5 : C == 3 ? 4 : C <= 6 ? 3 : C <= 12 ? 2 : 1;
+  return PT > 1 ? (RUNS ? 2 : 0) : C == 2 ? 5 : C == 3 ? 4 : C <= 6 ? 3 : C <= 12 ? 2 : 1;
 }
 
 // RUNS: tiles may hold several runs of planes.  A launch without such tiles
@@ -82,7 +84,7 @@ constexpr int gather_waves() {
 // where u^m is two transcendentals, a step of 162x181x75 takes 35.5 instead of
 // 38.7 us).
 template <int C, bool M2, int NW, bool STEP, int PT, bool RUNS, bool WJ>
-__global__ __launch_bounds__(64 * NW, (gather_waves<C, PT>())) void k_ifcm_gather(const LaunchArgs a) {
+__global__ __launch_bounds__(64 * NW, (gather_waves<C, PT, RUNS>())) void k_ifcm_gather(const LaunchArgs a) {
   constexpr int CP = (C + 3) / 4 * 4;
   constexpr int CH = C - 1;  // clusters whose H is gathered
   constexpr int NV = STEP ? 2 * C + (WJ ? 1 : 0) : 1;  // sums kept (without J its slot is not written)
