@@ -298,13 +298,18 @@ int default_zc(pifcm_ctx* ctx, int kind, int C, bool m2, const pifcm_volume& v) 
   const double R = resident_waves(ctx, kind, C, m2), simds = 4.0 * ctx->num_cu;
   const double txy = (double)((v.nx + kWaveTileX - 1) / kWaveTileX) * ((v.ny + kWaveTileY - 1) / kWaveTileY);
   auto cost_of = [&](int zc) {
-    const double nt = txy * ((v.nz + zc - 1) / zc);
+    const double nt = txy * (((long)v.nz + zc - 1) / zc);
     return launch_cost(nt, nt * zc, zc, R, simds);
+  };
+  // The next smaller depth of the form ceil(nz / k).
+  auto shallower = [&](int zc) {
+    const long k = ((long)v.nz + zc - 2) / (zc - 1);
+    return (int)((v.nz + k - 1) / k);
   };
   int best = v.nz;
   double best_cost = cost_of(v.nz);
-  for (int k = 2; k <= v.nz; ++k) {
-    const int zc = (v.nz + k - 1) / k;
+  for (int zc = v.nz; zc > 1;) {
+    zc = shallower(zc);
     const double cost = cost_of(zc);
     if (cost < best_cost) {
       best_cost = cost;
@@ -313,10 +318,8 @@ int default_zc(pifcm_ctx* ctx, int kind, int C, bool m2, const pifcm_volume& v) 
   }
   // A batched launch stores its sums once per run: of shallow runs, the deepest
   // (up to eight planes) that costs a lone pair at most a twentieth more.
-  for (int k = 1; (v.nz + k - 1) / k > best; ++k) {
-    const int zc = (v.nz + k - 1) / k;
+  for (int zc = v.nz; zc > best; zc = shallower(zc))
     if (zc <= 8 && cost_of(zc) <= 1.05 * best_cost) return zc;
-  }
   return best;
 }
 
