@@ -337,7 +337,7 @@ __global__ __launch_bounds__(64 * NW, (gather_waves<C, PT, RUNS>())) void k_ifcm
     }
 
     // sum_j H_ij of a voxel: 1, or 0 in a volume of one voxel.
-    const float hsum = nx * ny * nz > 1 ? 1.f : 0.f;
+    const float hsum = has_neighbours(nx, ny, nz) ? 1.f : 0.f;
     // Finalise voxel z of slot S; its own cell is in buffer bz:
     // eqs (5)/(7) ratios, (4), (1), (2), (3), per particle.
     auto finalize = [&](int z, auto Sc, int bz, auto GENc) __attribute__((always_inline)) {

@@ -51,6 +51,10 @@ struct VolDev {
   const float* rinv;   // [nz][ny][nx][4] per-ring g_inv and q_inv (two-ring kernel only)
 };
 
+// Whether a voxel has neighbours in a volume of this size.  No product of the
+// sides: a volume may hold more than 2^31 voxels.
+__host__ __device__ inline bool has_neighbours(int nx, int ny, int nz) { return nx > 1 || ny > 1 || nz > 1; }
+
 // One (volume, particle) run of a launch.
 struct PairDev {
   const float* U0;     // U^(0) (plain FCM: NULL = eq (2) from c^(0))
