@@ -341,6 +341,46 @@ __device__ __forceinline__ void block_tile_store(float* partials, int tile, int 
   __syncthreads();
 }
 
+// A thread's sums over its voxels: kRunTerms of them at a time in fp32 and,
+// where it has more (LONG), the runs in fp64.  In one fp32 chain the roundings
+// of a region of one intensity all go the same way: 1.5e-5 of a centre over
+// 4096 terms, 1e-8 in runs of eight.
+template <int NV, bool LONG>
+struct RunSums {
+  float run[NV];
+  double all[LONG ? NV : 1];
+  __device__ __forceinline__ RunSums() {
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      run[k] = 0.f;
+      if constexpr (LONG) all[k] = 0.0;
+    }
+  }
+  // Before voxel k of the thread's (in steps that divide kRunTerms).
+  __device__ __forceinline__ void before(int k) {
+    if constexpr (LONG)
+      if (k % kRunTerms == 0 && k > 0) fold();
+  }
+  __device__ __forceinline__ void fold() {
+    if constexpr (LONG) {
+#pragma unroll
+      for (int k = 0; k < NV; ++k) {
+        all[k] += (double)run[k];
+        run[k] = 0.f;
+      }
+    }
+  }
+  // The totals, in run.
+  __device__ __forceinline__ const float (&total())[NV] {
+    fold();
+    if constexpr (LONG) {
+#pragma unroll
+      for (int k = 0; k < NV; ++k) run[k] = (float)all[k];
+    }
+    return run;
+  }
+};
+
 // One work group per pair: add the pair's tile slots in fp64 (thread t takes
 // slots t, t + 1024, ...; then the wave's tree and the waves in order) and
 // advance its state: new centres (eq (3)), J of the iteration's input state

@@ -12,6 +12,7 @@ constexpr int kWaveTileX = 16;    // columns of a fused-step tile along x
 constexpr int kWaveTileY = 4;     // and along y (16 x 4 = one wavefront)
 constexpr float kDFloor = 1e-12f; // floor of the squared distance of eq (4)
 constexpr int kFcmTiles = 1024;   // work groups a volume's pointwise FCM pass is cut into, at most
+constexpr int kRunTerms = 8;      // voxels a thread of that pass adds in fp32 before fp64 takes over
 
 // Device-side state of one IFCM run (one volume x one particle).
 struct alignas(64) SolveState {
@@ -100,6 +101,7 @@ struct LaunchArgs {
   int32_t nring;       // number of offsets
   int32_t ring_gen;    // which table `ring` holds (part of the graph cache key)
   int32_t max_slots;   // most tile slots of a pair of the launch
+  int32_t max_vpt;     // most voxels per thread of the pointwise kernels
   int32_t runs;        // 1: a volume's tiles hold several runs of planes
   int32_t pt;          // particles per work item of the fused step (1 or 2):
                        // its items are (volume, group of pt particles, tile)

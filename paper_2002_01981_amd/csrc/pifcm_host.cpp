@@ -543,8 +543,10 @@ int kind_of(const pifcm_params* p, bool zero_weights) {
   return ring_params(p) ? (ring2_params(p) ? kRing2 : kRing) : kGather;
 }
 
+// runs: some tile holds several runs of planes; in plain FCM, some thread
+// several runs of terms (long_of).
 int occupancy_of(int kind, int C, int nw, bool m2, bool step, int pt = 1, bool runs = false) {
-  if (kind == kFcm) return fcm_x_occupancy(C, m2, step);
+  if (kind == kFcm) return fcm_x_occupancy(C, m2, step, runs);
   if (kind == kFcmStore) return fcm_occupancy(C, m2, step);
   if (kind == kRing) return ring_occupancy(C, m2, step);
   if (kind == kRing2) return ring2_occupancy(C, m2, step, runs);
@@ -620,6 +622,9 @@ int particles_per_item(pifcm_ctx* ctx, int kind, int C, bool m2, const pifcm_vol
   if (shapes[0].pt > 0) return std::min(shapes[0].pt, 2);
   return eps == 0.f && launch_depth(ctx, kind, C, m2, vols, shapes, P, 1).rounds >= 4.0 ? 2 : 1;
 }
+
+// Whether a launch of `kind` over this volume takes the instance for several runs.
+bool long_of(int kind, const VolDev& v) { return kind == kFcm ? v.vpt > kRunTerms : v.zc > v.sc; }
 
 // Work items a work group takes at a time: one per wave for the tiled
 // kernels, one for the pointwise kernels.
@@ -784,6 +789,7 @@ LaunchArgs make_args(const pifcm_ctx* ctx, const VolDev* vols_dev, const PairDev
   for (int b = 0; b < nvol; ++b) {
     a.item_begin[b] = acc;
     a.max_slots = std::max(a.max_slots, a.use_1d ? vh[b].tiles1d : vh[b].slots);
+    a.max_vpt = std::max(a.max_vpt, vh[b].vpt);
     if (vh[b].zc > vh[b].sc) a.runs = 1;
     acc += groups * (a.use_1d ? vh[b].tiles1d : vh[b].tiles);
   }
@@ -1150,7 +1156,7 @@ pifcm_status solve_run(pifcm_ctx* ctx, const SolveWs& ws, const pifcm_volume* vo
   LaunchArgs a = make_args(ctx, dev.vols(), dev.pairs(), &vh, 1, 1, kind, p);
   a.want_j = p->eps > 0.f || J_hist_out ? 1 : 0;
   a.fcm_sorted = fcm_sorted ? 1 : 0;
-  const int occ = occupancy_of(kind, C, ts.nw, m2, true);
+  const int occ = occupancy_of(kind, C, ts.nw, m2, true, 1, long_of(kind, vh));
   const int grid = grid_for(ctx, a.nitems, occ, items_per_group(kind, ts.nw));
   int t = 0;
   const SolveState* hst = host.st();
@@ -1172,7 +1178,7 @@ pifcm_status solve_run(pifcm_ctx* ctx, const SolveWs& ws, const pifcm_volume* vo
   TRY(timing_end(ctx));
   // Objective of the final state (the fitness).
   LaunchArgs ae = a;
-  const int occe = occupancy_of(kind, C, ts.nw, m2, false);
+  const int occe = occupancy_of(kind, C, ts.nw, m2, false, 1, long_of(kind, vh));
   HIPCHK(launch_step(C, ae, grid_for(ctx, a.nitems, occe, items_per_group(kind, ts.nw)), ts.nw, m2,
                      kind, false, ctx->s));
   double* jh = ws.jh_stage ? ws.jh_stage : J_hist_out;
@@ -1490,8 +1496,8 @@ pifcm_status swarm_core(pifcm_ctx* ctx, const pifcm_volume* vols, int32_t B, con
   if (is_ring(kind)) TRY(prepare_ring(ctx, p));
   const VolDev* vdev = dev.vols();
   const PairDev* pdev = dev.pairs();
-  bool several = false;  // some tiles hold several runs of planes
-  for (int b = 0; b < B; ++b) several = several || vh[b].zc > vh[b].sc;
+  bool several = false;
+  for (int b = 0; b < B; ++b) several = several || long_of(kind, vh[b]);
   const int occ = occupancy_of(kind, C, ts0.nw, m2, true, pt, several);
   const int occe = occupancy_of(kind, C, ts0.nw, m2, false, pt, several);
   const int ipg = items_per_group(kind, ts0.nw);

@@ -27,7 +27,8 @@ hipError_t launch_finalize(int C, const LaunchArgs& a, int npairs, bool step, hi
 // Plain FCM (lambda = xi = 0): an iteration from x and the centres alone, or
 // (step = false) the final memberships and their objective.
 hipError_t launch_fcm_x(int C, const LaunchArgs& a, int grid, bool m2, bool step, hipStream_t s);
-int fcm_x_occupancy(int C, bool m2, bool step);
+// (longer: of threads with more than kRunTerms voxels)
+int fcm_x_occupancy(int C, bool m2, bool step, bool longer);
 // The same iteration with its states kept in memory / the objective of one.
 hipError_t launch_fcm(int C, const LaunchArgs& a, int grid, bool m2, bool step, hipStream_t s);
 // Waves (one tile each) per work group of the general-neighbourhood kernel
