@@ -341,19 +341,20 @@ __device__ __forceinline__ void block_tile_store(float* partials, int tile, int 
   __syncthreads();
 }
 
-// A thread's sums over its voxels: kRunTerms of them at a time in fp32 and,
-// where it has more (LONG), the runs in fp64.  In one fp32 chain the roundings
-// of a region of one intensity all go the same way: 1.5e-5 of a centre over
-// 4096 terms, 1e-8 in runs of eight.
+// A thread's sums over its voxels: in runs of kRunTerms and, where it has more
+// than one (LONG), the sum of the runs.  In one chain the roundings of equal
+// terms (a region of one intensity) all go the same way: 2e-7 of the sum over 32
+// terms, 4e-7 over 64, 1.5e-5 over 4096, against 4e-8 over 8 terms or 8 runs of
+// them; a thread never has more (fcm_vpt).
 template <int NV, bool LONG>
 struct RunSums {
   float run[NV];
-  double all[LONG ? NV : 1];
+  float all[LONG ? NV : 1];
   __device__ __forceinline__ RunSums() {
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
       run[k] = 0.f;
-      if constexpr (LONG) all[k] = 0.0;
+      if constexpr (LONG) all[k] = 0.f;
     }
   }
   // Before voxel k of the thread's (in steps that divide kRunTerms).
@@ -365,7 +366,7 @@ struct RunSums {
     if constexpr (LONG) {
 #pragma unroll
       for (int k = 0; k < NV; ++k) {
-        all[k] += (double)run[k];
+        all[k] += run[k];
         run[k] = 0.f;
       }
     }
@@ -375,7 +376,7 @@ struct RunSums {
     fold();
     if constexpr (LONG) {
 #pragma unroll
-      for (int k = 0; k < NV; ++k) run[k] = (float)all[k];
+      for (int k = 0; k < NV; ++k) run[k] = all[k];
     }
     return run;
   }

@@ -11,8 +11,8 @@ constexpr int kMaxBatchVols = 32; // volumes in one batched launch
 constexpr int kWaveTileX = 16;    // columns of a fused-step tile along x
 constexpr int kWaveTileY = 4;     // and along y (16 x 4 = one wavefront)
 constexpr float kDFloor = 1e-12f; // floor of the squared distance of eq (4)
-constexpr int kFcmTiles = 1024;   // work groups a volume's pointwise FCM pass is cut into, at most
-constexpr int kRunTerms = 8;      // voxels a thread of that pass adds in fp32 before fp64 takes over
+constexpr int kFcmTiles = 1024;   // work groups a volume's pointwise FCM pass is cut into, if fcm_vpt allows
+constexpr int kRunTerms = 8;      // terms a thread of that pass adds in one chain
 
 // Device-side state of one IFCM run (one volume x one particle).
 struct alignas(64) SolveState {
@@ -51,6 +51,14 @@ struct VolDev {
   int32_t vpt;         // voxels per thread of the pointwise kernels
   const float* rinv;   // [nz][ny][nx][4] per-ring g_inv and q_inv (two-ring kernel only)
 };
+
+// Voxels per thread of the pointwise FCM pass over n voxels: as few work groups
+// of 256 threads as kFcmTiles (four waves per SIMD of the card, and as few sums
+// to add per iteration), but no more voxels than kRunTerms runs of kRunTerms.
+inline int fcm_vpt(size_t n) {
+  const size_t most = (size_t)256 * kFcmTiles, v = (n + most - 1) / most;
+  return v < 1 ? 1 : v < kRunTerms * kRunTerms ? (int)v : kRunTerms * kRunTerms;
+}
 
 // Whether a voxel has neighbours in a volume of this size.  No product of the
 // sides: a volume may hold more than 2^31 voxels.

@@ -406,10 +406,8 @@ VolDev make_vol(const pifcm_volume& v, const float* invg, TileShape ts, int zbeg
   d.ntz = (nact + d.zc - 1) / d.zc;
   d.tiles = d.ntx * d.nty * d.ntz;
   d.slots = d.ntx * d.nty * ((nact + d.sc - 1) / d.sc);
-  // Pointwise passes: at most kFcmTiles work groups of 256 threads (four waves
-  // per SIMD of the card, and as few sums to add per iteration).
-  const size_t n1 = (size_t)v.nx * v.ny * nact, most = (size_t)256 * kFcmTiles;
-  d.vpt = (int)std::max<size_t>(1, (n1 + most - 1) / most);
+  const size_t n1 = (size_t)v.nx * v.ny * nact;
+  d.vpt = fcm_vpt(n1);
   d.tiles1d = (int)((n1 + (size_t)256 * d.vpt - 1) / ((size_t)256 * d.vpt));
   return d;
 }

@@ -34,9 +34,8 @@ constexpr int kFcmAhead = 4;
 static_assert(kRunTerms % kFcmAhead == 0, "a run of sums ends between groups");
 
 // One iteration; WJ: J of its input state is wanted (a stop rule or a
-// history); LONG: a thread has more than kRunTerms voxels.  The instance
-// without is for its registers (C = 16: 59 against 123, 8 particles on
-// 40x100x100 voxels 42 against 53 us per iteration).
+// history); LONG: a thread has more than kRunTerms voxels (the instance without
+// has fewer registers: 59 against 93 at C = 16).
 template <int C, bool M2, bool WJ, bool LONG>
 __global__ __launch_bounds__(256) void k_fcm_x(const LaunchArgs a) {
   constexpr int NT = 256;

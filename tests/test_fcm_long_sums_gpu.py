@@ -1,13 +1,13 @@
 """Plain FCM where a thread takes many voxels: its sums stay those of short
-float32 runs.
+float32 chains.
 
 In units of 2^-24, for m = 2: a squared distance carries 3 (difference, doubled
 by the square, and the square's own), the product of C - 1 of them
 4 (C - 1) - 1, their sum C - 1 more, the reciprocal 2 and its product 1; a
 membership is off by at most 9 C - 8 in all, its square by twice that and 1, a
 term of a sum by 4 more (J's squared distance and product).  A thread's run of
-eight terms adds 7, the rounding of its total 1, the tree over the wave and its
-work group 9.  A centre is a ratio of two such sums, and is rounded once.
+eight terms adds 7, its sum of at most eight runs 7, the tree over the wave and
+its work group 9.  A centre is a ratio of two such sums, and is rounded once.
 """
 import numpy as np
 import pytest
@@ -20,7 +20,7 @@ pytestmark = pytest.mark.gpu
 
 
 def bound(C):
-    return (2 * (2 * (9 * C - 8) + 5 + 17) + 1) * 2.0 ** -24
+    return (2 * (2 * (9 * C - 8) + 5 + 23) + 1) * 2.0 ** -24
 
 
 @pytest.fixture(scope="module")
@@ -58,8 +58,8 @@ def test_a_step_matches_the_oracle(ctx, shape, C, m):
 
 @pytest.mark.parametrize("how", ["solve", "adjoint"])
 def test_regions_of_one_intensity(ctx, how):
-    """2^30 voxels of three intensities: thousands of equal terms per thread,
-    whose roundings all go the same way."""
+    """2^30 voxels of three intensities: equal terms, whose roundings all go the
+    same way."""
     import torch
     if torch.cuda.mem_get_info()[0] < 100 << 30:
         pytest.skip("needs 100 GB of free device memory")

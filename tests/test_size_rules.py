@@ -30,3 +30,10 @@ def test_only_a_single_voxel_has_no_neighbours(tmp_path):
              (2048, 1024, 1100), (2048, 1024, 1900), (1, 1, 2147483647), (65536, 1, 60000), (4096, 4096, 256)]
     out = run(tmp_path, "\n".join('std::printf("%%d\\n", (int)has_neighbours(%d, %d, %d));' % s for s in sides))
     assert [int(v) for v in out] == [int(s != (1, 1, 1)) for s in sides]
+
+
+def test_a_thread_of_the_pointwise_pass_has_few_voxels(tmp_path):
+    """At most eight runs of eight, whatever the volume; one up to 2^18 voxels."""
+    sizes = [1, 255, 1 << 18, (1 << 18) + 1, 7109137, 1 << 24, (1 << 24) + 1, 1 << 30, 4000000000]
+    out = run(tmp_path, "\n".join('std::printf("%%d\\n", fcm_vpt(%dull));' % n for n in sizes))
+    assert [int(v) for v in out] == [min(64, max(1, -(-n // (1 << 18)))) for n in sizes]
