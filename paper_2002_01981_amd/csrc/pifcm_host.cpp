@@ -166,7 +166,6 @@ pifcm_status begin(pifcm_ctx* ctx) {
 
 // Order the user's stream after the work queued so far (a call that has waited
 // for its work needs none of it).
-
 pifcm_status finish(pifcm_ctx* ctx) {
   HIPCHK(hipEventRecord(ctx->ev_out, ctx->s));
   HIPCHK(hipStreamWaitEvent(ctx->user, ctx->ev_out, 0));
@@ -339,13 +338,14 @@ int ring_zc(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v) {
   return std::min(v.nz, ring_depth(ctx, C, m2, txy * v.nz));
 }
 
-// Planes per tile of the adjoint's forward pass (and of an allocation-free solve
-// whose default tiles leave too many sums for the scratch array): of the depths ceil(nz / k) and
-// 32 that are at least min(nz, 32) deep, the one with the fewest rounds of one
-// pair's tiles on the fused step's resident waves times (depth + 4); the deeper
-// one on a tie.  The adjoint keeps it although other depths are faster on small volumes: the gradient at the
-// initial centres is what is left of sums that cancel to 1e-5 of their terms,
-// and the order of the forward pass's sums shows in it.
+// Planes per tile of the adjoint's forward pass (and of volumes whose default
+// tiles leave too many sums for the scratch array, see shape_for): of the depths
+// ceil(nz / k) and 32 that are at least min(nz, 32) deep, the one with the fewest
+// rounds of one pair's tiles on the fused step's resident waves times (depth +
+// 4); the deeper one on a tie.  The adjoint keeps it although other depths are
+// faster on small volumes: the gradient at the initial centres is what is left
+// of sums that cancel to 1e-5 of their terms, and the order of the forward
+// pass's sums shows in it.
 int floored_zc(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v) {
   const long R = (long)resident_waves(ctx, kGather, C, m2);
   const long txy = (long)((v.nx + kWaveTileX - 1) / kWaveTileX) * ((v.ny + kWaveTileY - 1) / kWaveTileY);
@@ -367,21 +367,6 @@ int floored_zc(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v) {
   }
   consider(floor_zc);
   return best;
-}
-
-// floored: the adjoint's forward pass and a solve whose sums must stay few.
-TileShape shape_for(pifcm_ctx* ctx, int C, bool m2, const pifcm_volume& v, int kind, bool floored = false) {
-  TileShape t;
-  auto it = ctx->tuned.find(std::make_tuple(C, (int)m2, v.nx, v.ny, v.nz));
-  if (it != ctx->tuned.end()) t = it->second;
-  if (t.zc <= 0) {
-    t.deep = !floored && kind != kFcm && kind != kFcmStore;
-    t.zc = floored         ? floored_zc(ctx, C, m2, v)
-           : kind == kRing ? ring_zc(ctx, C, m2, v)
-                           : default_zc(ctx, kind == kRing2 ? kRing2 : kGather, C, m2, v);
-  }
-  t.zc = std::max(1, std::min(t.zc, max_zc(v, C)));
-  return t;
 }
 
 // Launch descriptor of a volume whose planes [zbeg, zend) are iterated
@@ -412,6 +397,68 @@ VolDev make_vol(const pifcm_volume& v, const float* invg, TileShape ts, int zbeg
   return d;
 }
 
+// Control block of a solve or swarm in device memory: the check flags, the
+// solve states, the pair records and the volume records, laid out together so
+// that one copy uploads them all and one reads flags and states back.
+constexpr size_t kFlagBytes = 64;  // two ints: non-finite intensity, bad membership row
+size_t control_bytes(size_t npairs, size_t nvol) {
+  return kFlagBytes + npairs * (sizeof(SolveState) + sizeof(PairDev)) + nvol * sizeof(VolDev);
+}
+
+// The parts of ifcm_solve_noalloc's workspace, g_inv in front: their offsets in
+// the scratch array and the bytes in all, with sums in `slots` slots.
+struct ScratchLayout {
+  size_t ubuf, partials, control, jhist, need;
+};
+ScratchLayout scratch_layout(const pifcm_volume& v, const pifcm_params* p, int slots) {
+  auto al = [](size_t b) { return (b + 255) / 256 * 256; };
+  const size_t N = nvox(v), C = p->C;
+  ScratchLayout l;
+  l.ubuf = al((N + 63) / 64 * 64 * sizeof(float));
+  l.partials = l.ubuf + al(N * C * sizeof(float));
+  l.control = l.partials + al((size_t)slots * (2 * C + 1) * sizeof(float));
+  l.jhist = l.control + al(control_bytes(1, 1));
+  l.need = l.jhist + al((size_t)std::max(1, p->max_iter) * sizeof(double));
+  return l;
+}
+
+// Slots of sums of a solve of planes [zbeg, zend) (the larger of the tiled and
+// pointwise decompositions).
+int slots_of(const pifcm_volume& v, TileShape ts, int zbeg = 0, int zend = -1) {
+  const VolDev d = make_vol(v, nullptr, ts, zbeg, zend);
+  return std::max(d.slots, d.tiles1d);
+}
+
+// Tile shape of a volume in calls with parameters p.  floored: the adjoint's
+// forward pass.  Where a solve fits the scratch array with the fewer sums of
+// deeper tiles (those of floored_zc, or whole columns) but not with the
+// default's -- volumes a few thousandths below the largest the array takes --
+// every call takes the deeper tiles: ifcm_solve_noalloc solves such a volume,
+// with the bits of the other calls.
+TileShape shape_for(pifcm_ctx* ctx, const pifcm_params* p, const pifcm_volume& v, int kind, bool floored = false) {
+  const int C = p->C;
+  const bool m2 = p->m == 2.0f;
+  TileShape t;
+  auto it = ctx->tuned.find(std::make_tuple(C, (int)m2, v.nx, v.ny, v.nz));
+  if (it != ctx->tuned.end()) t = it->second;
+  const bool chosen = t.zc > 0;
+  auto at_depth = [&](int zc) {
+    t.zc = std::max(1, std::min(zc, max_zc(v, C)));
+    return scratch_layout(v, p, slots_of(v, t)).need <= kScratchBytes;
+  };
+  if (chosen) {
+    at_depth(t.zc);
+    return t;
+  }
+  t.deep = !floored && kind != kFcm && kind != kFcmStore;
+  const int zc = floored         ? floored_zc(ctx, C, m2, v)
+                 : kind == kRing ? ring_zc(ctx, C, m2, v)
+                                 : default_zc(ctx, kind == kRing2 ? kRing2 : kGather, C, m2, v);
+  if (!at_depth(zc) && kind == kGather && !floored && !at_depth(floored_zc(ctx, C, m2, v)) && !at_depth(v.nz))
+    at_depth(zc);
+  return t;
+}
+
 // Work groups for `nitems` work items, `per_group` items in flight per work
 // group (waves of the fused step, 1 for the pointwise kernels): one item per
 // slot when they all fit in 8 waves of resident groups, else a persistent
@@ -425,13 +472,6 @@ int grid_for(pifcm_ctx* ctx, int nitems, int occupancy, int per_group = 1) {
   return (int)std::max<long>(8, g);
 }
 
-// Control block of a solve or swarm in device memory: the check flags, the
-// solve states, the pair records and the volume records, laid out together so
-// that one copy uploads them all and one reads flags and states back.
-constexpr size_t kFlagBytes = 64;  // two ints: non-finite intensity, bad membership row
-size_t control_bytes(size_t npairs, size_t nvol) {
-  return kFlagBytes + npairs * (sizeof(SolveState) + sizeof(PairDev)) + nvol * sizeof(VolDev);
-}
 struct Control {
   char* p;
   size_t npairs;
@@ -1091,28 +1131,20 @@ struct SolveWs {
                                // it straight into the caller's array
 };
 
-// Tile slots of a solve over planes [zbeg, zend) (the larger of the tiled and
-// pointwise decompositions).
-int solve_slots(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_params* p, int kind, int zbeg, int zend,
-                bool floored = false) {
-  const VolDev v = make_vol(*vol, nullptr, shape_for(ctx, p->C, p->m == 2.0f, *vol, kind, floored), zbeg, zend);
-  return std::max(v.slots, v.tiles1d);
-}
-
 // One IFCM solve on the context's stream in the workspace ws.  U_out
 // receives U^(T); host outputs optional.
 pifcm_status solve_run(pifcm_ctx* ctx, const SolveWs& ws, const pifcm_volume* vol,
                        const pifcm_params* p, float lambda, float xi, const float* centres_in,
                        const float* U_in, float* U_out, float* centres_out, uint8_t* labels_out,
                        double* J_out, int32_t* iters_out, double* J_hist_out, int zbeg, int zend,
-                       bool fcm_sorted = false, bool floored = false) {
+                       bool fcm_sorted = false) {
   const bool slab = zbeg > 0 || zend < vol->nz;
   const int C = p->C;
   const bool m2 = p->m == 2.0f;
   const int kind = kind_of(p, lambda == 0.0f && xi == 0.0f);
   const size_t N = nvox(*vol);
   const Control dev{ws.control, 1}, host{ws.stage, 1};
-  const TileShape ts = shape_for(ctx, C, m2, *vol, kind, floored);
+  const TileShape ts = shape_for(ctx, p, *vol, kind);
   const VolDev vh = make_vol(*vol, ws.invg, ts, zbeg, zend, kind == kRing2 ? ws.rinv : nullptr);
   PairDev pr{};
   pr.U0 = U_in || kind == kFcm ? U_in : ws.ubuf;
@@ -1224,7 +1256,7 @@ pifcm_status solve_impl(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_par
   const size_t N = nvox(*vol);
   const size_t Np = (N + 63) / 64 * 64;
   if (is_ring(kind)) TRY(prepare_ring(ctx, p));
-  const int slots = solve_slots(ctx, vol, p, kind, zbeg, zend);
+  const int slots = slots_of(*vol, shape_for(ctx, p, *vol, kind), zbeg, zend);
   if (kind == kGather) TRY(ensure(ctx, ctx->invg, Np * sizeof(float), "iteration invariants"));
   if (kind == kRing2) TRY(ensure(ctx, ctx->rinv, Np * 4 * sizeof(float), "ring invariants"));
   if (kind != kFcm) TRY(ensure(ctx, ctx->ubuf, N * C * sizeof(float), "memberships"));
@@ -1301,28 +1333,12 @@ pifcm_status ifcm_solve_noalloc(pifcm_ctx* ctx, const pifcm_volume* vol, const p
   // The workspace of solve_run, carved out of this device's scratch array.
   const int C = p->C;
   const size_t N = nvox(*vol);
-  const size_t Np = (N + 63) / 64 * 64;
-  auto al = [](size_t b) { return (b + 255) / 256 * 256; };
-  const size_t o_invg = 0;
-  const size_t o_ubuf = o_invg + al(Np * sizeof(float));
-  const size_t o_part = o_ubuf + al(N * C * sizeof(float));
-  size_t o_st = 0, o_jh = 0, need = 0;
-  // Where the default tiles' sums are the few thousandths too many, deeper
-  // tiles with fewer sums do.
-  bool floored = false;
-  for (int pass = 0; pass < 2; ++pass) {
-    floored = pass == 1;
-    const int slots = solve_slots(ctx, vol, p, kGather, 0, vol->nz, floored);
-    o_st = o_part + al((size_t)slots * (2 * C + 1) * sizeof(float));
-    o_jh = o_st + al(control_bytes(1, 1));
-    need = o_jh + al((size_t)std::max(1, p->max_iter) * sizeof(double));
-    if (need <= kScratchBytes) break;
-  }
-  if (need > kScratchBytes)
+  const ScratchLayout l = scratch_layout(*vol, p, slots_of(*vol, shape_for(ctx, p, *vol, kGather)));
+  if (l.need > kScratchBytes)
     return fail(ctx, PIFCM_E_INVALID,
                 "ifcm_solve_noalloc: this solve needs %zu bytes of scratch (N = %zu, C = %d, max_iter = %d), "
                 "more than the %zu bytes the library holds per device; use ifcm_solve",
-                need, N, C, p->max_iter, kScratchBytes);
+                l.need, N, C, p->max_iter, kScratchBytes);
   std::mutex* mu = scratch_call_lock(ctx->device);
   if (!mu) return fail(ctx, PIFCM_E_UNSUPPORTED, "device %d is beyond the scratch table", ctx->device);
   std::lock_guard<std::mutex> lock(*mu);
@@ -1331,18 +1347,18 @@ pifcm_status ifcm_solve_noalloc(pifcm_ctx* ctx, const pifcm_volume* vol, const p
   HIPCHK(scratch_region(ctx->device, &base));
   char* sc = (char*)base;
   SolveWs ws;
-  ws.invg = (float*)(sc + o_invg);
-  ws.ubuf = (float*)(sc + o_ubuf);
-  ws.partials = (float*)(sc + o_part);
-  ws.control = sc + o_st;
-  ws.jhist = (double*)(sc + o_jh);
+  ws.invg = (float*)sc;
+  ws.ubuf = (float*)(sc + l.ubuf);
+  ws.partials = (float*)(sc + l.partials);
+  ws.control = sc + l.control;
+  ws.jhist = (double*)(sc + l.jhist);
   ws.stage = (char*)ctx->pinned;  // allocated at pifcm_create, at least kStageBytes
   ws.jh_stage = nullptr;          // the J history goes straight to J_hist_out
   float c_tmp[kMaxC];
   double J = 0.0;
   int32_t T = 0;
   TRY(solve_run(ctx, ws, vol, p, lambda, xi, centres_in, U_in, U_out, c_tmp, labels_out, &J, &T,
-                J_hist_out, 0, vol->nz, false, floored));
+                J_hist_out, 0, vol->nz));
   if (centres_out) std::memcpy(centres_out, c_tmp, sizeof(float) * C);
   if (J_out) *J_out = J;
   if (iters_out) *iters_out = T;
@@ -1421,10 +1437,10 @@ pifcm_status swarm_core(pifcm_ctx* ctx, const pifcm_volume* vols, int32_t B, con
 
   // Tile shape (the waves per work group are those of the launch) and, in the
   // batched launch, particles per work item and runs of planes per tile.
-  const TileShape ts0 = shape_for(ctx, C, m2, vols[0], kind);
+  const TileShape ts0 = shape_for(ctx, p, vols[0], kind);
   std::vector<TileShape> shapes(B);
   for (int b = 0; b < B; ++b) {
-    shapes[b] = shape_for(ctx, C, m2, vols[b], kind);
+    shapes[b] = shape_for(ctx, p, vols[b], kind);
     shapes[b].nw = ts0.nw;
   }
   int pt = 1, depth = 0;
@@ -1685,10 +1701,10 @@ pifcm_status ifcm_backward(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_
   HIPCHK(hipMemsetAsync(ctx->flags.p, 0, kFlagBytes, ctx->s));
   TRY(prepare_volumes(ctx, vol, 1, C, u0s, off, kind, p, (int*)ctx->flags.p));
   TRY(wait_flags(ctx, Control{(char*)ctx->flags.p, 0}, Control{(char*)ctx->pinned, 0}));
-  const TileShape ts = shape_for(ctx, C, m2, *vol, kind, true);
+  const TileShape ts = shape_for(ctx, p, *vol, kind, true);
   std::vector<VolDev> vh{make_vol(*vol, (const float*)ctx->invg.p, ts)};
   // Recomputed steps need no sums, and take the depth of a lone solve.
-  const TileShape tr = shape_for(ctx, C, m2, *vol, kind);
+  const TileShape tr = shape_for(ctx, p, *vol, kind);
   std::vector<VolDev> vr{make_vol(*vol, (const float*)ctx->invg.p, tr)};
   const int slots = std::max({vh[0].slots, vr[0].slots, vh[0].tiles1d});
   // Workspace: forward ping-pong, checkpoints at t = S, 2S, ... <= K - 1,
