@@ -413,8 +413,9 @@ __global__ __launch_bounds__(NT) void k_finalize(const LaunchArgs a) {
   for (int k = 0; k < NV; ++k) d[k] = 0.0;
   const gfloat* parts = as_global(pr.partials);
   // Four slots in flight per thread (the order of the additions, and so the
-  // result, is that of the plain strided loop).
-  constexpr int kU = 4;
+  // result, is that of the plain strided loop); with 1024 threads fewer where
+  // the 128 registers each then has do not hold more beside the fp64 sums.
+  constexpr int kU = NT < 1024 || 6 * NV <= 114 ? 4 : 4 * NV <= 114 ? 2 : 1;
   int s = threadIdx.x;
   for (; s + (kU - 1) * NT < slots; s += kU * NT) {
     float v[kU][NV];

@@ -66,14 +66,21 @@ constexpr int kNCell = kHX * kHY;              // 108 cells
 constexpr int kNHalo = kNCell - 64;            // 44 halo cells, one per lane
 
 // The registers are held to what keeps gather_waves waves on a SIMD (some
-// instances come out a few above the step; C = 11: one wave 518 us, two, with
-// a few spilled registers, 387 us for 20 particles on 120x100x50).  Two particles
-// per item in tiles of one run fit two waves by themselves and are left to the
-// compiler (0: six ragged volumes x 64, 128 planes, 11.84 against 11.68 ms).
-template <int C, int PT, bool RUNS>
+// instances come out a few above the step; C = 11: one wave 518 us, two 363 us
+// for 20 particles on 120x100x50).  Two particles per item in tiles of one run
+// fit two waves by themselves and are left to the compiler (0: six ragged
+// volumes x 64, 128 planes, 11.84 against 11.68 ms).
+// At C = 6 with m != 2 and at C = 11 and 12 that takes spilled registers (1 to
+// 70; C = 12 most), whose memory the runtime has to find.  LEAN is an instance
+// without, for ifcm_solve_noalloc: as many waves as fit unspilled.  Register
+// allocation alone differs, the results have the same bits.
+template <int C, int PT, bool RUNS, bool LEAN>
 constexpr int gather_waves() {
+  if (LEAN) return C <= 6 ? 2 : 1;
   return PT > 1 ? (RUNS ? 2 : 0) : C == 2 ? 5 : C == 3 ? 4 : C <= 6 ? 3 : C <= 12 ? 2 : 1;
 }
+template <int C, bool M2>
+constexpr bool kGatherSpills = (C == 6 && !M2) || C == 11 || C == 12;
 
 // RUNS: tiles may hold several runs of planes.  A launch without such tiles
 // takes the instance without the test after every plane (13.0 against 13.3 ms
@@ -83,8 +90,8 @@ constexpr int gather_waves() {
 // per three planes at C = 4, which the memory system hides; at C = 3, m = 2.5,
 // where u^m is two transcendentals, a step of 162x181x75 takes 35.5 instead of
 // 38.7 us).
-template <int C, bool M2, int NW, bool STEP, int PT, bool RUNS, bool WJ>
-__global__ __launch_bounds__(64 * NW, (gather_waves<C, PT, RUNS>())) void k_ifcm_gather(const LaunchArgs a) {
+template <int C, bool M2, int NW, bool STEP, int PT, bool RUNS, bool WJ, bool LEAN = false>
+__global__ __launch_bounds__(64 * NW, (gather_waves<C, PT, RUNS, LEAN>())) void k_ifcm_gather(const LaunchArgs a) {
   constexpr int CP = (C + 3) / 4 * 4;
   constexpr int CH = C - 1;  // clusters whose H is gathered
   constexpr int NV = STEP ? 2 * C + (WJ ? 1 : 0) : 1;  // sums kept (without J its slot is not written)
@@ -607,17 +614,19 @@ __global__ __launch_bounds__(64 * NW, (gather_waves<C, PT, RUNS>())) void k_ifcm
 // Launch / occupancy of one C with NW waves per work group and PT particles
 // per work item.  NW and PT variants exist only where ALL_NW is set (the
 // C = 4 fast path); elsewhere NW = 4 and PT = 1.
-template <int C, bool M2, int NW, int PT, bool RUNS>
+template <int C, bool M2, int NW, int PT, bool RUNS, bool LEAN = false>
 static hipError_t launch_gather_ctr(const LaunchArgs& a, int grid, bool step, hipStream_t s) {
   const dim3 g(grid), t(64 * NW);
-  if (!step) hipLaunchKernelGGL((k_ifcm_gather<C, M2, NW, false, PT, RUNS, true>), g, t, 0, s, a);
-  else if (a.want_j) hipLaunchKernelGGL((k_ifcm_gather<C, M2, NW, true, PT, RUNS, true>), g, t, 0, s, a);
-  else hipLaunchKernelGGL((k_ifcm_gather<C, M2, NW, true, PT, RUNS, false>), g, t, 0, s, a);
+  if (!step) hipLaunchKernelGGL((k_ifcm_gather<C, M2, NW, false, PT, RUNS, true, LEAN>), g, t, 0, s, a);
+  else if (a.want_j) hipLaunchKernelGGL((k_ifcm_gather<C, M2, NW, true, PT, RUNS, true, LEAN>), g, t, 0, s, a);
+  else hipLaunchKernelGGL((k_ifcm_gather<C, M2, NW, true, PT, RUNS, false, LEAN>), g, t, 0, s, a);
   return hipGetLastError();
 }
 
 template <int C, bool M2, int NW, int PT>
 static hipError_t launch_gather_ct(const LaunchArgs& a, int grid, bool step, hipStream_t s) {
+  if constexpr (kGatherSpills<C, M2>)
+    if (a.lean) return a.runs ? hipErrorInvalidValue : launch_gather_ctr<C, M2, NW, PT, false, true>(a, grid, step, s);
   return a.runs ? launch_gather_ctr<C, M2, NW, PT, true>(a, grid, step, s)
                 : launch_gather_ctr<C, M2, NW, PT, false>(a, grid, step, s);
 }

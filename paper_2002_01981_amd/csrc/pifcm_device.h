@@ -115,6 +115,7 @@ struct LaunchArgs {
                        // its items are (volume, group of pt particles, tile)
   int32_t want_j;      // 1: J of an iteration's input state is needed (a stop
                        // rule or a history)
+  int32_t lean;        // 1: no kernel may need private memory
   float W[kMaxRings + 1];  // eq (10) weight of ring r at W[r]
 };
 

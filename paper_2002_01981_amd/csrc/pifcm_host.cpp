@@ -1129,6 +1129,7 @@ struct SolveWs {
   char* stage = nullptr;       // host, kStageBytes (pinned or pageable)
   double* jh_stage = nullptr;  // host [max_iter] staging of the J history, or NULL to copy
                                // it straight into the caller's array
+  bool lean = false;           // kernels that need no private memory
 };
 
 // One IFCM solve on the context's stream in the workspace ws.  U_out
@@ -1185,6 +1186,7 @@ pifcm_status solve_run(pifcm_ctx* ctx, const SolveWs& ws, const pifcm_volume* vo
 
   LaunchArgs a = make_args(ctx, dev.vols(), dev.pairs(), &vh, 1, 1, kind, p);
   a.want_j = p->eps > 0.f || J_hist_out ? 1 : 0;
+  a.lean = ws.lean ? 1 : 0;
   a.fcm_sorted = fcm_sorted ? 1 : 0;
   const int occ = occupancy_of(kind, C, ts.nw, m2, true, 1, long_of(kind, vh));
   const int grid = grid_for(ctx, a.nitems, occ, items_per_group(kind, ts.nw));
@@ -1354,6 +1356,7 @@ pifcm_status ifcm_solve_noalloc(pifcm_ctx* ctx, const pifcm_volume* vol, const p
   ws.jhist = (double*)(sc + l.jhist);
   ws.stage = (char*)ctx->pinned;  // allocated at pifcm_create, at least kStageBytes
   ws.jh_stage = nullptr;          // the J history goes straight to J_hist_out
+  ws.lean = true;
   float c_tmp[kMaxC];
   double J = 0.0;
   int32_t T = 0;
