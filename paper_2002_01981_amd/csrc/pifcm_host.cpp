@@ -462,14 +462,17 @@ TileShape shape_for(pifcm_ctx* ctx, const pifcm_params* p, const pifcm_volume& v
 // Work groups for `nitems` work items, `per_group` items in flight per work
 // group (waves of the fused step, 1 for the pointwise kernels): one item per
 // slot when they all fit in 8 waves of resident groups, else a persistent
-// grid of the resident groups.  Always a multiple of 8 (one share per XCD).
-int grid_for(pifcm_ctx* ctx, int nitems, int occupancy, int per_group = 1) {
-  const long resident = (long)occupancy * ctx->num_cu;
+// grid of `persistent` groups per CU.  Always a multiple of 8 (one share per
+// XCD).
+int grid_for(pifcm_ctx* ctx, int nitems, int occupancy, int per_group, int persistent) {
   const long groups = ((long)nitems + per_group - 1) / per_group;
   long g;
-  if (groups <= 8 * resident) g = (groups + 7) / 8 * 8;
-  else g = resident / 8 * 8;
+  if (groups <= 8L * occupancy * ctx->num_cu) g = (groups + 7) / 8 * 8;
+  else g = (long)persistent * ctx->num_cu / 8 * 8;
   return (int)std::max<long>(8, g);
+}
+int grid_for(pifcm_ctx* ctx, int nitems, int occupancy, int per_group = 1) {
+  return grid_for(ctx, nitems, occupancy, per_group, occupancy);
 }
 
 struct Control {
@@ -660,6 +663,15 @@ int particles_per_item(pifcm_ctx* ctx, int kind, int C, bool m2, const pifcm_vol
   if (shapes[0].pt > 0) return std::min(shapes[0].pt, 2);
   return eps == 0.f && launch_depth(ctx, kind, C, m2, vols, shapes, P, 1).rounds >= 4.0 ? 2 : 1;
 }
+
+// Work groups per CU of a persistent grid of the step, of the `occ` that fit.
+// Such launches are bound by memory.  At C = 6, where gather_waves holds the
+// registers to three waves per SIMD, two are faster there: us per 6 iterations
+// of 20 particles on 181x217x181, m = 2, 15515 against 17028, of 47 on
+// 22x217x164 4694 against 5004; m = 2.5: 16597 against 17314, 5000 against 5088.
+// Grids with a slot for every item keep three (36 particles on 22x217x164, m =
+// 2: 3074; 3851 in an instance of two).
+int persistent_groups(int kind, int C, int occ) { return kind == kGather && C == 6 ? std::min(occ, 2) : occ; }
 
 // Whether a launch of `kind` over this volume takes the instance for several runs.
 bool long_of(int kind, const VolDev& v) { return kind == kFcm ? v.vpt > kRunTerms : v.zc > v.sc; }
@@ -1189,7 +1201,7 @@ pifcm_status solve_run(pifcm_ctx* ctx, const SolveWs& ws, const pifcm_volume* vo
   a.lean = ws.lean ? 1 : 0;
   a.fcm_sorted = fcm_sorted ? 1 : 0;
   const int occ = occupancy_of(kind, C, ts.nw, m2, true, 1, long_of(kind, vh));
-  const int grid = grid_for(ctx, a.nitems, occ, items_per_group(kind, ts.nw));
+  const int grid = grid_for(ctx, a.nitems, occ, items_per_group(kind, ts.nw), persistent_groups(kind, C, occ));
   int t = 0;
   const SolveState* hst = host.st();
   auto read_back = [&]() -> pifcm_status {
@@ -1534,7 +1546,7 @@ pifcm_status swarm_core(pifcm_ctx* ctx, const pifcm_volume* vols, int32_t B, con
 
   if (mode == PIFCM_SWARM_BATCHED) {
     LaunchArgs a = make_args(ctx, vdev, pdev, vh, B, P, kind, p, pt);
-    const int grid = grid_for(ctx, a.nitems, occ, ipg);
+    const int grid = grid_for(ctx, a.nitems, occ, ipg, persistent_groups(kind, C, occ));
     const int chunk = p->eps > 0.f ? std::min(kChunk, std::max(1, p->max_iter)) : std::max(1, p->max_iter);
     // Capture `chunk` fused launches once; replay until every pair stops.
     std::vector<char> key(sizeof(LaunchArgs) + 5 * sizeof(int));
@@ -1584,7 +1596,7 @@ pifcm_status swarm_core(pifcm_ctx* ctx, const pifcm_volume* vols, int32_t B, con
       for (int q = 0; q < P; ++q) {
         const size_t k = (size_t)b * P + q;
         args[k] = make_args(ctx, vdev + b, pdev + k, one, 1, 1, kind, p);
-        grids[k] = grid_for(ctx, args[k].nitems, occ, ipg);
+        grids[k] = grid_for(ctx, args[k].nitems, occ, ipg, persistent_groups(kind, C, occ));
         gride[k] = grid_for(ctx, args[k].nitems, occe, ipg);
       }
     }
@@ -1797,7 +1809,7 @@ pifcm_status ifcm_backward(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_
   HIPCHK(hipMemcpyAsync(c_hist, hvol + 2, C * sizeof(float), hipMemcpyHostToDevice, ctx->s));
   LaunchArgs a = make_args(ctx, (const VolDev*)ctx->tvol.p, tp, vh, 1, 1, kind, &pf);
   const int occ = occupancy_of(kind, C, ts.nw, m2, true);
-  const int grid = grid_for(ctx, a.nitems, occ, items_per_group(kind, ts.nw));
+  const int grid = grid_for(ctx, a.nitems, occ, items_per_group(kind, ts.nw), persistent_groups(kind, C, occ));
   const int occe = occupancy_of(kind, C, ts.nw, m2, false);
   const int gride = grid_for(ctx, a.nitems, occe, items_per_group(kind, ts.nw));
   const int gridr = grid_for(ctx, kind == kGather ? vr[0].tiles : vr[0].tiles1d,
