@@ -984,8 +984,6 @@ pifcm_status pifcm_create(int device, void* hip_stream, pifcm_ctx** out) {
     }
     ctx->arch[n] = 0;
   }
-  ensure(ctx, ctx->tvol, sizeof(VolDev) * kMaxBatchVols, "volume table");
-  ensure(ctx, ctx->tpair, sizeof(PairDev) * kMaxPairs, "pair table");
   if (ensure(ctx, ctx->norm, 2 * sizeof(NormSlot), "normalisation") != PIFCM_OK ||
       hipHostMalloc((void**)&ctx->norm_seen, sizeof(int), hipHostMallocDefault) != hipSuccess ||
       ensure(ctx, ctx->work, 16 * sizeof(int32_t), "item counters") != PIFCM_OK ||
@@ -1745,6 +1743,7 @@ pifcm_status ifcm_backward(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_
   const size_t rs_states = ((size_t)std::max(R, 1) * sizeof(SolveState) + 255) / 256 * 256;
   const size_t rs_bytes = rs_states + (size_t)std::max(R, 1) * sizeof(PairDev);
   TRY(ensure(ctx, ctx->adj_rs, rs_bytes, "recompute states"));
+  TRY(ensure(ctx, ctx->tvol, 2 * sizeof(VolDev), "volume records"));
   TRY(ensure(ctx, ctx->tpair, (size_t)K * sizeof(PairDev), "pair records"));
   const size_t pin_fixed = (size_t)(S + 2) * (sizeof(SolveState) + sizeof(PairDev)) + 2 * sizeof(VolDev) +
                            (size_t)(K + 1) * C * sizeof(float) + 64 * sizeof(double) + 4096;
