@@ -211,9 +211,16 @@ __global__ __launch_bounds__(64 * kAdjPW) void k_adj_point(const AdjArgs a) {
     // the first C - 1 clusters (the last H is 1 minus their sum, as in the
     // forward step), F numerators, the stored g_inv, the centre value that
     // forms g (shifted by -1 for a flat neighbourhood) and (iteration pass)
-    // dJ/dU^(t+1).
+    // dJ/dU^(t+1).  From C = 12 on, where the registers are spilled already, the
+    // centre value is read back from LDS (C = 16, m = 2, four iterations of
+    // 77 x 128 x 128: 4547 against 5039 us; C = 11: 1750 either way).
     constexpr int CH = C - 1;
+    constexpr bool XS = C < 12;
     float hn[3][C], fn[3][C], gs[3], xs[3], gns[3][C];
+    auto centre = [&](int buf, float g) -> float {
+      const float xv = cell_at(buf, 0, 0)[0];
+      return g < 0.f ? xv - 1.f : xv;
+    };
 #pragma unroll
     for (int s2 = 0; s2 < 3; ++s2) {
       gs[s2] = 1.f;
@@ -321,7 +328,7 @@ __global__ __launch_bounds__(64 * kAdjPW) void k_adj_point(const AdjArgs a) {
       const bool doA = p - 1 >= zlo, doB = p >= zlo && p < zhi, doC = p + 1 < zhi;
       __builtin_amdgcn_wave_barrier();
       // Centre values for g: voxels p-1 and p from their slots, p+1 prefetched.
-      const float xcA = xs[SA], xcB = xs[SB];
+      const float xcA = XS ? xs[SA] : centre(bprev, gs[SA]), xcB = XS ? xs[SB] : centre(bp, gs[SB]);
       const float xC = rg < 0.f ? rx - 1.f : rx;
       float hC[C], E[C], Co[C], Pc[C];
 #pragma unroll
