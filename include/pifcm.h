@@ -123,15 +123,17 @@ pifcm_status ifcm_solve(pifcm_ctx* ctx, const pifcm_volume* vol, const pifcm_par
 
 /* ifcm_solve for callers that cannot allocate device memory (code under HIP
  * graph capture elsewhere in the program, serving loops, harnesses that
- * forbid hipMalloc): the same solve, the same kernels, the same arguments,
- * outputs and decomposition -- results are bit-identical to ifcm_solve's on
- * the same context -- but no hipMalloc, hipFree or other allocating call.
+ * forbid hipMalloc): the same solve, the same arguments, outputs and
+ * decomposition -- results are bit-identical to ifcm_solve's on the same
+ * context -- but no hipMalloc, hipFree or other allocating call, and only
+ * kernels without spilled registers (whose memory the runtime would allocate).
  * Its workspace (g_inv, the second membership buffer, tile sums, solve
  * state, objective history; about 4 * (C + 1) bytes per voxel) lives in a
  * device array of 256 MiB that the library holds on every GPU it runs on
  * until the process ends; a C = 4 volume of up to about 13 million voxels
- * fits.  Its host staging is the pinned buffer pifcm_create allocates.  A solve that needs more fails with PIFCM_E_INVALID (naming the
- * bytes needed) before any work is queued; V > 1 is PIFCM_E_UNSUPPORTED.
+ * fits.  Its host staging is the pinned buffer pifcm_create allocates.  A
+ * solve that needs more fails with PIFCM_E_INVALID (naming the bytes needed)
+ * before any work is queued; V > 1 is PIFCM_E_UNSUPPORTED.
  * The array is shared by every call on that GPU and keeps the last call's
  * contents (each call initialises what it reads): calls on one device are
  * serialised inside the library, and every call finishes its work before

@@ -264,7 +264,10 @@ bool is_ring(int kind) { return kind == kRing || kind == kRing2; }
 // m = 2; 0.8 + 0.44 k at C = 3, m = 2.5; 1.2 + 0.6 k at C = 8, fitted over
 // depths of 8 to 181 planes within 5 %), so a launch costs its passes per SIMD
 // and twice the passes of its longest-working wave, where the tiles run in
-// rounds of `resident`.
+// rounds of `resident`.  Beyond the three fits it was held against depths of at
+// least 32 planes: lone solves at C = 2, 4, 6, 11, 12 and 16, m = 2 and 2.5, on
+// seven shapes from 512x64x4 to 3x2048x2048, and swarms at C = 2 to 14 and 16,
+// took no longer beyond the spread of the runs.
 double launch_cost(double tiles, double planes, double longest, double resident, double simds) {
   const double passes = planes + 4.0 * tiles, mean = passes / tiles;
   return passes / simds + 2.0 * (std::ceil(tiles / resident) * mean + (longest + 4.0 - mean));
@@ -656,7 +659,11 @@ LaunchDepth launch_depth(pifcm_ctx* ctx, int kind, int C, bool m2, const pifcm_v
 // 64 13.2 against 12.2 ms); below, the memberships fit the last-level cache or
 // the two-particle tiles, half as many on two thirds of the wave slots, leave
 // waves idle (181x217x181: 4 particles 297 against 329 us, 60x128x128: 8
-// particles 75 against 92 us).
+// particles 75 against 92 us).  These are at m = 2.  At m = 1.5 and 2.5, where a
+// voxel costs more issue, two gain less and later: us per 4 iterations at m =
+// 2.5, one against two, 181x217x181 x 20 7478 and 7035, x 64 23143 and 22566;
+// 104x251x204 x 8 2211 and 2250, 60x128x128 x 40 1912 and 1940, 75x181x162 x 12
+// 1391 and 1431.
 int particles_per_item(pifcm_ctx* ctx, int kind, int C, bool m2, const pifcm_volume* vols,
                        const std::vector<TileShape>& shapes, int P, float eps) {
   if (kind != kGather || C != 4 || P < 2) return 1;

@@ -27,8 +27,9 @@
 // waves per SIMD: the ring invariants wait in LDS for their voxel instead of in
 // the slots, ring 1 has no slot p+2, cells beside the volume are zeroed once per
 // tile and their lanes store to a spare cell, so loads need no test and plane
-// bases are scalar.  A step of 8 particles on 204 x 251 x 104, C = 4: 1659 ->
-// 1065 us.
+// bases are scalar.  At C = 4 two waves leave 256 registers and 8 to 20 are
+// spilled (writes 1.08 x the new memberships); C = 2 and 3 fit.  A step of 8
+// particles on 204 x 251 x 104, C = 4: 1659 -> 1065 us.
 #include "common.h"
 #include "pifcm_kernels.h"
 
@@ -230,11 +231,8 @@ constexpr int NBUF = 4;
 __host__ __device__ constexpr int cls(int a, int b) {
   return (a > b ? cls(b, a) : (b < 2 ? a + b : 3 + a));
 }
-__host__ __device__ constexpr int cls_a(int c) { return c == 2 ? 1 : c == 4 ? 1 : c == 5 ? 2 : 0; }
-__host__ __device__ constexpr int cls_b(int c) { return c == 0 ? 0 : c <= 2 ? 1 : 2; }
 static_assert(cls(0, 0) == 0 && cls(1, 0) == 1 && cls(1, 1) == 2, "classes");
 static_assert(cls(2, 0) == 3 && cls(1, 2) == 4 && cls(2, 2) == 5, "classes");
-static_assert(cls_a(4) == 1 && cls_b(4) == 2 && cls_a(3) == 0 && cls_b(3) == 2, "class members");
 // Halo cell h (0 .. 95) of the 20 x 8 staged plane: two rows above, two
 // below, two columns on each side of the 16 x 4 tile.
 __device__ __forceinline__ void halo_cell(int h, int& cx, int& cy) {
